@@ -1,223 +1,334 @@
-// Shared "NT" GEMMs of the libseg translation units (gfx950, bf16 MFMA):
-//   C[m][n] = sum_k A[m][k] * B[n][k]     (both operands k-contiguous)
-// Two block shapes with one epilogue interface (a functor called by every
-// thread with its accumulators and a Tile that says where they sit):
-//  - k_gemm_nt: 128x128 blocks, 4 waves of 64x64, K in steps of 32, the next
-//    step staged in registers; two blocks per CU.  For grids too small to
-//    fill the chip with 256-wide tiles.
-//  - k_gemm_big: 256x256 blocks, 8 waves of 128x64 (two per SIMD), K in
-//    steps of 64 fetched by direct buffer->LDS loads into two 64 KB stages;
-//    XCD-aware grouped tile order.
-//  - k_gemm_big_tn: the same block with transposed operands (both row-major
-//    over K), fragments by transpose reads; up to three problems per launch.
+// Shared GEMM of the libseg translation units (gfx950, bf16 MFMA):
+//   C(m, n) = sum_k A(m, k) B(n, k)
+// with each operand k-contiguous or row-major over K, read in place; one
+// kernel (k_gemm) with one epilogue interface: a functor called by every
+// thread with its accumulators and a Tile that says where they sit.
 #pragma once
+
+#include <type_traits>
 
 #include "common.h"
 
 namespace seg {
 namespace gemm {
 
-constexpr int BM = 128, BN = 128, BK = 32;
+typedef int gemm_i32x4 __attribute__((ext_vector_type(4)));
+typedef short gemm_v4i16 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) gemm_v4i16 gemm_lds_v4i16;
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
-// Where a wave's accumulators sit: rows m0 + wr + bm*32 + 8*(r/4) + 4*hh + r%4,
-// columns n0 + wc + bn*32 + col for register r of acc[bm][bn]; (wr, wc) is the
-// wave tile's corner inside the block, brows the block's row count.
+// Where a wave's accumulators sit.  (wr, wc) is the wave tile's corner inside
+// the block at (m0, n0).  Register r of acc[i][j] holds, in the lane with
+// col = lane % 16 and grp = lane / 16,
+//   row wr + 16 i + 4 grp + r, column wc + 16 j + col
+// or, for an epilogue with kSwap (the products' operands swapped, so that a
+// lane holds runs of a row),
+//   row wr + 16 i + col, column wc + 16 j + 4 grp + r.
+// lds: at least 16 KB that belong to the wave alone.  split: which part of K.
 struct Tile {
-  int m0, n0, M, N, wr, wc, col, hh, brows;
-  __device__ __forceinline__ int row(int bm, int r) const {
-    return m0 + wr + bm * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
-  }
-  __device__ __forceinline__ int column(int bn) const { return n0 + wc + bn * 32 + col; }
+  int m0, n0, M, N, wr, wc, col, grp, split;
+  char *lds;
 };
 
-// Raw buffer resource over [base, base + bytes): loads at or past the end
-// return zeros.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_rsrc(const void *base, long bytes) {
-  const long lim = bytes < 0x7fffffffL ? bytes : 0x7fffffffL;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)lim, 0x00020000);
+__device__ __forceinline__ f32x4 mfma16(const bf16x8 &a, const bf16x8 &b, const f32x4 &c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Calls f(m, n, v) for every accumulator of the wave inside [0, M) x [0, N)
-// (plain global stores: with two waves per SIMD they measured faster than
-// stores through a buffer resource).
-template <int TM, int TN, class F>
-__device__ __forceinline__ void tile_apply(const f32x16 (&acc)[TM][TN], const Tile &t, F &&f) {
-#pragma unroll
-  for (int bm = 0; bm < TM; ++bm)
-#pragma unroll
-    for (int bn = 0; bn < TN; ++bn) {
-      const int n = t.column(bn);
-      if (n >= t.N) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = t.row(bm, r);
-        if (m < t.M) f(m, n, acc[bm][bn][r]);
-      }
-    }
+__device__ __forceinline__ unsigned pack2(float a, float b) {
+  return (unsigned)f2bf_bits(a) | ((unsigned)f2bf_bits(b) << 16);
 }
 
-// C = scale * A B^T stored as TO (leading dimension ldc)
-template <class TO>
-struct EpiStore {
+// Output of a product: 32 rows at a time go through the wave's LDS so that a
+// lane ends with 8 consecutive columns of a row and stores (and, for the
+// accumulating kinds, loads) them with 16-byte accesses, 8 lanes to a
+// 128-byte (bf16) or 256-byte (fp32) piece of a row.  The reads of the next
+// 32 rows are issued before the stores of the current ones.
+//   ST    C = scale A B^T            (TO bf16 or fp32)
+//   RESID C = R + scale A B^T        (bf16, a residual connection; R may be C)
+//   ACC   C = first ? scale A B^T : C + scale A B^T  (fp32: gradients summed
+//         over row chunks, in chunk order)
+// vec: C (and R) rows start on 16-byte boundaries; otherwise, and in a ragged
+// last column group, elements are handled one by one.
+enum OutMode { ST, RESID, ACC };
+
+template <class TO, OutMode MODE>
+struct EpiOut {
+  static constexpr bool kSwap = true;
   TO *c;
-  long ldc;
-  float scale;
-  template <int TM, int TN>
-  __device__ __forceinline__ void operator()(const f32x16 (&acc)[TM][TN], const Tile &t) const {
-    TO *cc = c;
-    const long ld = ldc;
-    const float s = scale;
-    tile_apply(acc, t, [&](int m, int n, float v) { store_val(cc, (long)m * ld + n, v * s); });
-  }
-};
-
-// C = R + scale * A B^T in bf16 (a residual connection); R may alias C
-struct EpiResid {
-  unsigned short *c;
   long ldc;
   const unsigned short *r;
   long ldr;
   float scale;
-  template <int TM, int TN>
-  __device__ __forceinline__ void operator()(const f32x16 (&acc)[TM][TN], const Tile &t) const {
-    unsigned short *cc = c;
-    const unsigned short *rr = r;
-    const long ld = ldc, lr = ldr;
-    const float s = scale;
-    tile_apply(acc, t, [&](int m, int n, float v) {
-      cc[(long)m * ld + n] = f2bf_bits(bf_bits2f(rr[(long)m * lr + n]) + v * s);
-    });
+  int vec, first;
+  long split_stride;  // elements between the partial sums of the parts of K
+
+  static EpiOut make(TO *c, long ldc, float scale = 1.f, const unsigned short *r = nullptr,
+                     long ldr = 0, bool first = true, long split_stride = 0) {
+    EpiOut e{c, ldc, r, ldr, scale, 0, first ? 1 : 0, split_stride};
+    const bool cv = (reinterpret_cast<uintptr_t>(c) & 15) == 0 && ldc * sizeof(TO) % 16 == 0;
+    const bool rv = MODE != RESID || ((reinterpret_cast<uintptr_t>(r) & 15) == 0 && ldr % 8 == 0);
+    e.vec = cv && rv ? 1 : 0;
+    return e;
   }
-};
 
-// C += scale * A B^T in fp32 (gradients summed over row chunks, in chunk order)
-struct EpiAccum {
-  float *c;
-  long ldc;
-  float scale;
-  template <int TM, int TN>
-  __device__ __forceinline__ void operator()(const f32x16 (&acc)[TM][TN], const Tile &t) const {
-    float *cc = c;
-    const long ld = ldc;
-    const float s = scale;
-    tile_apply(acc, t, [&](int m, int n, float v) { cc[(long)m * ld + n] += v * s; });
-  }
-};
-
-// lda, ldb and K must be multiples of 8 (16-byte chunks); rows beyond M / N
-// and chunks beyond K read as zero.  Grid: (ceil(N/BN), ceil(M/BM)).
-template <class Epi>
-__global__ void __launch_bounds__(256, 2) k_gemm_nt(const unsigned short *__restrict__ A, long lda,
-                                                    const unsigned short *__restrict__ B, long ldb,
-                                                    int M, int N, int K, Epi ep) {
-  __shared__ unsigned short sA[2][BM * BK];
-  __shared__ unsigned short sB[2][BN * BK];
-  const int n0 = blockIdx.x * BN, m0 = blockIdx.y * BM;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wm = wave >> 1, wn = wave & 1, col = lane & 31, hh = lane >> 5;
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
-
-  // each thread stages two 16-byte chunks of A and of B per K step
-  u16x8 ra[2], rb[2];
-  auto fetch = [&](int kt) {
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      const int c = tid + it * 256;
-      const int row = c >> 2, ch = c & 3;
-      const int gk = kt * BK + ch * 8;
-      ra[it] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
-      rb[it] = ra[it];
-      if (m0 + row < M && gk < K) ra[it] = *reinterpret_cast<const u16x8 *>(A + (long)(m0 + row) * lda + gk);
-      if (n0 + row < N && gk < K) rb[it] = *reinterpret_cast<const u16x8 *>(B + (long)(n0 + row) * ldb + gk);
-    }
+  struct Pre {
+    u16x8 r;
+    f32x4 a, b;
   };
-  auto stash = [&](int buf) {
+  __device__ __forceinline__ Pre load(const TO *cc, int m, int n, const Tile &t) const {
+    Pre p{};
+    if (m >= t.M || n >= t.N) return p;
+    const bool whole = vec && n + 8 <= t.N;
+    if constexpr (MODE == RESID) {
+      const unsigned short *s = r + (long)m * ldr + n;
+      if (whole) p.r = *reinterpret_cast<const u16x8 *>(s);
+      else
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      const int c = tid + it * 256;
-      const int row = c >> 2, ch = c & 3;
-      const int sw = (ch ^ ((row >> 2) & 3)) * 8;
-      *reinterpret_cast<u16x8 *>(&sA[buf][row * BK + sw]) = ra[it];
-      *reinterpret_cast<u16x8 *>(&sB[buf][row * BK + sw]) = rb[it];
-    }
-  };
-
-  const int nk = (K + BK - 1) / BK;
-  fetch(0);
-  stash(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    const bool more = kt + 1 < nk;
-    if (more) fetch(kt + 1);
+        for (int j = 0; j < 8; ++j)
+          if (n + j < t.N) p.r[j] = s[j];
+    } else if constexpr (MODE == ACC) {
+      if (first) return p;
+      const float *s = reinterpret_cast<const float *>(cc) + (long)m * ldc + n;
+      if (whole) {
+        p.a = *reinterpret_cast<const f32x4 *>(s);
+        p.b = *reinterpret_cast<const f32x4 *>(s + 4);
+      } else {
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const int ch = kk * 2 + hh;
-      bf16x8 a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int ra_ = wm * 64 + i * 32 + col;
-        const int rb_ = wn * 64 + i * 32 + col;
-        a[i] = *reinterpret_cast<const bf16x8 *>(&sA[buf][ra_ * BK + ((ch ^ ((ra_ >> 2) & 3)) * 8)]);
-        b[i] = *reinterpret_cast<const bf16x8 *>(&sB[buf][rb_ * BK + ((ch ^ ((rb_ >> 2) & 3)) * 8)]);
+        for (int j = 0; j < 4; ++j) {
+          if (n + j < t.N) p.a[j] = s[j];
+          if (n + 4 + j < t.N) p.b[j] = s[4 + j];
+        }
       }
+    }
+    return p;
+  }
+
+  template <int NI, int NJ>
+  __device__ __forceinline__ void operator()(const f32x4 (&acc)[NI][NJ], const Tile &t) const {
+    static_assert(NJ == 4, "64-column wave tiles");
+    constexpr int TM = NI / 2;
+    const int lane = t.grp * 16 + t.col, lr = lane >> 3, q = lane & 7;
+    const int m_base = t.m0 + t.wr + lr, n = t.n0 + t.wc + q * 8;
+    TO *const cc = c + (long)t.split * split_stride;
+    f32x4 *w = reinterpret_cast<f32x4 *>(t.lds);
+    Pre pre[2][4];
+    if constexpr (MODE != ST) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) pre[0][p] = load(cc, m_base + p * 8, n, t);
+    }
+#pragma unroll
+    for (int bm = 0; bm < TM; ++bm) {
+      if constexpr (MODE != ST) {
+        if (bm + 1 < TM) {
+#pragma unroll
+          for (int p = 0; p < 4; ++p)
+            pre[(bm + 1) & 1][p] = load(cc, m_base + (bm + 1) * 32 + p * 8, n, t);
+        }
+      }
+      // [32 rows][16 chunks of 4 columns], chunk c of row m in slot c ^ (m & 15)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma32(a[i], b[j], acc[i][j]);
+        for (int j = 0; j < 4; ++j)
+          w[(i * 16 + t.col) * 16 + ((j * 4 + t.grp) ^ t.col)] = acc[bm * 2 + i][j] * scale;
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int row = p * 8 + lr, m = m_base + bm * 32 + p * 8;
+        f32x4 a = w[row * 16 + ((2 * q) ^ (row & 15))];
+        f32x4 b = w[row * 16 + ((2 * q + 1) ^ (row & 15))];
+        if (m >= t.M || n >= t.N) continue;
+        const Pre &pr = pre[bm & 1][p];
+        if constexpr (MODE == RESID) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            a[j] += bf_bits2f(pr.r[j]);
+            b[j] += bf_bits2f(pr.r[4 + j]);
+          }
+        } else if constexpr (MODE == ACC) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            a[j] += pr.a[j];
+            b[j] += pr.b[j];
+          }
+        }
+        TO *d = cc + (long)m * ldc + n;
+        if (vec && n + 8 <= t.N) {
+          if constexpr (sizeof(TO) == 2) {
+            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+            *reinterpret_cast<u32x4 *>(d) =
+                u32x4{pack2(a[0], a[1]), pack2(a[2], a[3]), pack2(b[0], b[1]), pack2(b[2], b[3])};
+          } else {
+            *reinterpret_cast<f32x4 *>(d) = a;
+            *reinterpret_cast<f32x4 *>(d + 4) = b;
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if (n + j < t.N) store_val(d, j, a[j]);
+            if (n + 4 + j < t.N) store_val(d, 4 + j, b[j]);
+          }
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
     }
-    if (more) stash(buf ^ 1);
-    __syncthreads();
   }
-  ep(acc, Tile{m0, n0, M, N, wm * 64, wn * 64, col, hh, BM});
+};
+
+// ------------------------------------------------------------------ kernel
+//
+// One block of 8 waves computes 64 TM x 256, each wave 32 TM x 64 (TM = 4:
+// 128 accumulator registers).  The schedule keeps one wave of every SIMD on
+// products all the time: the waves form two groups of four (one wave of each
+// group per SIMD) that run half a step apart.  In a phase one group issues the
+// 16 TM products of a K step of 64 (1,024 cycles of its SIMD's matrix core at
+// TM = 4) while the other reads its 4 TM + 8 fragments of the next step from
+// LDS and issues its share of the direct global->LDS loads; a barrier ends the
+// phase and the groups change places.  Group 0 loads A (two ring slots, two
+// phases ahead of use), group 1 loads B (three slots, three phases ahead): 160
+// KB of LDS at TM = 4.
+//
+// What bounds it is power: at 8192^3 with random operands the matrix cores are
+// 84% busy at 1.65 GHz (the card's 2.4 GHz needs less switching).  Hence
+// 16x16x32 products (they move half the accumulator bits of 32x32x16 ones: N
+// operands 1,360 -> 1,500 TFLOP/s) and an order in which one operand changes
+// from product to product.  Measured rates at 8192^3, TFLOP/s, both operands
+// k-contiguous / one / none: one-barrier-per-step kernels with 32x32x16
+// products 1,160-1,240; this schedule with steps of 32 (64-byte row pieces,
+// half a cache line) 1,240 / 1,230 / 1,150; steps of 64 1,370 / 1,360 / 1,330;
+// 16x16x32 1,500 / 1,460 / 1,310; loads issued between the fragment reads
+// instead of after them 1,470 / 1,470 / 1,450 (kept).  TM = 2: 1,190 / 1,130 /
+// 1,150.
+//
+// LDS tiles.  N: [rows][64 k], 128 B per row, 16-byte chunk c of row r in slot
+// c ^ ((r >> 1) & 7): a 16-lane fragment read of 16 rows hits 16 distinct
+// 16-byte slots of the 64 banks.  T: [64 k][columns], chunk c of row r in slot
+// c ^ t_swizzle(r): a 32-lane transpose read (rows 0-3 and 8-11 of a slice x
+// 32 bytes) hits 16 distinct slots.  SQ_LDS_BANK_CONFLICT reads 0 for both.
+constexpr int BN = 256, BK = 64, THREADS = 512, SLOTS_A = 2, SLOTS_B = 3;
+constexpr int bm_of(int TM) { return 64 * TM; }
+
+// Raw buffer descriptor over [base, base + bytes): loads at or past the end
+// return zeros.
+__device__ __forceinline__ gemm_i32x4 gemm_desc(const void *base, long bytes) {
+  const unsigned long p = (unsigned long)base;
+  const long lim = bytes < 0x7fffffffL ? bytes : 0x7fffffffL;
+  return gemm_i32x4{(int)(unsigned)p, (int)((unsigned)(p >> 32) & 0xffffu), (int)lim, 0x00020000};
 }
 
-inline dim3 grid(int M, int N) { return dim3((unsigned)((N + BN - 1) / BN), (unsigned)((M + BM - 1) / BM)); }
+// 64 lanes x 16 bytes from rs (byte offset voff per lane) to LDS at byte
+// address dst (scalar).  Written as an instruction so that the compiler does
+// not wait for it before LDS reads of other slots; it has no register
+// result, and the phases below wait for it by count before its slot is read.
+__device__ __forceinline__ void dma16(unsigned dst, int voff, gemm_i32x4 rs) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dwordx4 %1, %2, 0 offen lds"
+      :
+      : "s"(dst), "v"(voff), "s"(rs)
+      : "memory");
+#endif
+}
 
-// ---------------------------------------------------------------- 256x256
+// chunk swizzle of k row r of a T tile
+__device__ __forceinline__ int t_swizzle(int r) { return 4 * (r & 3) ^ 2 * ((r >> 3) & 1); }
 
-constexpr int BIG = 256, BKB = 64;
-constexpr int BIG_STAGE = 2 * BIG * BKB;  // bf16 elements of one stage (A then B): 64 KB
+// The direct loads of one operand (R rows of it per block): R / 32 loads of
+// 1 KB per step by each of the four waves (w = 0..3) of the group that loads
+// it.  prep() sets up a step, load() issues its j-th load.
+struct Loader {
+  const unsigned short *x;  // T: column c0 of row 0
+  long ld;
+  int width;                // T: columns of the last row, whole 16-byte chunks
+  gemm_i32x4 rs;
+  int voff[2], kchunk, stride, add;
 
-
-// LDS layout of a 256 x 64 operand tile: row-major, 128 B per row, 16-byte
-// chunk c of row r stored in slot c ^ ((r >> 1) & 7).  Sixteen consecutive
-// rows then hit sixteen distinct 16-byte slots of the 64 banks (row parity
-// picks the half of the 256-byte bank line), so a fragment read of 32 rows x
-// 16 bytes is conflict-free.  A direct load writes 64 lanes x 16 bytes
-// = 8 rows in slot order; each lane fetches the chunk that belongs there.
-// The 8 waves of a block issue 4 such loads per operand and K step.
-struct BigFill {
-  int voff[4];   // byte offset of the lane's chunk in each of its 4 row groups
-  int kchunk;    // the lane's logical k chunk (0..7)
-  __device__ __forceinline__ void init(int wave, int lane, long ld) {
-    const int rr = lane >> 3, slot = lane & 7;
-    // row group j*8 + wave starts at a multiple of 8 rows; (row >> 1) & 7
-    // depends only on the wave's parity and rr
-    kchunk = slot ^ ((((wave & 1) * 8 + rr) >> 1) & 7);
+  template <bool T, int R>
+  __device__ __forceinline__ void init(const unsigned short *X, long ld_, int row0, int rows, int w,
+                                       int lane) {
+    ld = ld_;
+    if constexpr (T) {
+      constexpr int CPR = R / 8, RPL = 64 / CPR;  // chunks per row, rows per load
+      x = X + row0;
+      // the last row stops at the operand's last row rounded up to a 16-byte
+      // chunk: ld is a multiple of 8 and every k row holds ld elements, so
+      // that end stays inside the matrix
+      width = (rows - row0 + 7) & ~7;
+      stride = (int)(4 * RPL * ld * 2);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = (j * 8 + wave) * 8 + rr;
-      voff[j] = (int)(row * ld * 2) + kchunk * 16;
+      for (int j = 0; j < 2; ++j) {  // load j: k rows RPL (w + 4 j) ..; the swizzle repeats with j + 2
+        const int r = RPL * (w + 4 * j) + lane / CPR;
+        voff[j] = (int)(r * ld * 2) + ((lane % CPR) ^ t_swizzle(r)) * 16;
+      }
+    } else {
+      // the descriptor covers the block's own rows only (< 2^30 bytes)
+      rs = gemm_desc(X + (long)row0 * ld, (long)(rows - row0 < R ? rows - row0 : R) * ld * 2);
+      const int r = w * 8 + (lane >> 3);  // load j: rows 8 (w + 4 j) .. + 7
+      kchunk = (lane & 7) ^ ((r >> 1) & 7);
+      stride = (int)(32 * ld * 2);
+      voff[0] = (int)(r * ld * 2) + kchunk * 16;
+      voff[1] = voff[0] + stride;
     }
   }
-  // loads the 64-column K step starting at k0 (chunks at or past K read
-  // zero; so does a whole step past the end); wave is wave-uniform
-  __device__ __forceinline__ void issue(unsigned short *__restrict__ tile,
-                                        __amdgpu_buffer_rsrc_t rs, int k0, int K, int wave) const {
-#if defined(__HIP_DEVICE_COMPILE__)
-    const int add = k0 + kchunk * 8 < K ? k0 * 2 : 0x40000000;
+  // step at k0 of K: what lies at or past K (the whole step where k0 >= K)
+  // reads as zero
+  template <bool T>
+  __device__ __forceinline__ void prep(int k0, int K) {
+    if constexpr (T) {
+      const int rows = K - k0 < BK ? K - k0 : BK;
+      rs = gemm_desc(x + (long)k0 * ld, rows > 0 ? ((long)(rows - 1) * ld + width) * 2 : 0);
+      add = 0;
+    } else {
+      add = k0 + kchunk * 8 < K ? k0 * 2 : 0x40000000;
+    }
+  }
+  __device__ __forceinline__ void load(unsigned dst, int j, int w) const {
+    dma16(dst + (w + 4 * j) * 1024, voff[j & 1] + add + (j >> 1) * 2 * stride, rs);
+  }
+};
+
+// Fragment reads of NB 16-row blocks from the tile corner `c0` (rows of the
+// operand): lane l holds row l % 16, k = 8 (l / 16) .. + 7 of 32-wide slice kk.
+template <bool T, int R, int NB>
+struct Frag;
+
+template <int R, int NB>
+struct Frag<false, R, NB> {
+  int off[2];
+  __device__ __forceinline__ void init(int ring, int c0, int lane) {
+    const int col = lane & 15, grp = lane >> 4;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rs, (__attribute__((address_space(3))) void *)(tile + (j * 8 + wave) * 8 * BKB), 16,
-          voff[j] + add, 0, 0, 0);
-#endif
+    for (int kk = 0; kk < 2; ++kk)
+      off[kk] = ring + (c0 + col) * 128 + (((4 * kk + grp) ^ (col >> 1)) << 4);
+  }
+  __device__ __forceinline__ bf16x8 read(const char *lds, int slot, int kk, int i) const {
+    return *reinterpret_cast<const bf16x8 *>(lds + (off[kk] + slot) + i * 2048);
+  }
+};
+
+template <int R, int NB>
+struct Frag<true, R, NB> {
+  static constexpr int ROW = R * 2;  // bytes of one k row
+  int off[NB];
+  __device__ __forceinline__ void init(int ring, int c0, int lane) {
+    const int l16 = lane & 15, r = 8 * (lane >> 4) + (l16 >> 2);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int c = c0 + 16 * i + 4 * (l16 & 3);
+      off[i] = ring + r * ROW + (((c >> 3) ^ t_swizzle(r)) << 4) + (c & 7) * 2;
+    }
+  }
+  __device__ __forceinline__ bf16x8 read(const char *lds, int slot, int kk, int i) const {
+    const char *p = lds + (off[i] + slot) + kk * 32 * ROW;
+    const gemm_v4i16 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((gemm_lds_v4i16 *)p);
+    const gemm_v4i16 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((gemm_lds_v4i16 *)(p + 4 * ROW));
+    const bf16x4 a4 = __builtin_bit_cast(bf16x4, a), b4 = __builtin_bit_cast(bf16x4, b);
+    bf16x8 r;
+    r[0] = a4[0]; r[1] = a4[1]; r[2] = a4[2]; r[3] = a4[3];
+    r[4] = b4[0]; r[5] = b4[1]; r[6] = b4[2]; r[7] = b4[3];
+    return r;
   }
 };
 
@@ -225,12 +336,12 @@ struct BigFill {
 // on XCD b % 8; XCD x takes the contiguous tile range [x*C, (x+1)*C) so its
 // concurrent blocks share an L2, and tiles are ordered in groups of 8 M-tiles
 // (column by column inside a group) so those blocks reuse A and B rows.
-__device__ __forceinline__ int big_index(int total) {
+__device__ __forceinline__ int xcd_index(int total) {
   const int per = (total + 7) / 8;
   return (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
 }
 
-__device__ __forceinline__ void big_tile_of(int idx, int nM, int nN, int &mt, int &nt) {
+__device__ __forceinline__ void tile_of(int idx, int nM, int nN, int &mt, int &nt) {
   const int G = 8;
   const int group = idx / (G * nN);
   const int first = group * G;
@@ -240,412 +351,256 @@ __device__ __forceinline__ void big_tile_of(int idx, int nM, int nN, int &mt, in
   nt = in / gs;
 }
 
-__device__ __forceinline__ bool big_tile(int nM, int nN, int &mt, int &nt) {
-  const int idx = big_index(nM * nN);
-  if (idx >= nM * nN) return false;
-  big_tile_of(idx, nM, nN, mt, nt);
-  return true;
-}
-
-inline unsigned big_blocks(int M, int N) {
-  const long t = (long)((M + BIG - 1) / BIG) * ((N + BIG - 1) / BIG);
-  return (unsigned)((t + 7) / 8 * 8);
-}
-
-// Both 256x256 kernels: a wave tile of 128 rows x 64 columns (8 waves, 2 x 4,
-// two per SIMD): per slice 4 A and 2 B fragments feed 8 products.
-struct NtFrags {
-  bf16x8 a[4], b[2];
-};
-
-__device__ __forceinline__ void nt_load(NtFrags &f, const char *pa, const char *pb, int sw) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) f.a[i] = *reinterpret_cast<const bf16x8 *>(pa + i * 32 * 128 + sw);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) f.b[i] = *reinterpret_cast<const bf16x8 *>(pb + i * 32 * 128 + sw);
-}
-
-__device__ __forceinline__ void nt_mma(f32x16 (&acc)[4][2], const NtFrags &f) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = mfma32(f.a[i], f.b[j], acc[i][j]);
-}
-
-// Scheduling of one slice: the six fragment reads of the next slice ride
-// with the first six of its eight products, so their LDS latency hides under
-// the MFMA pipe; the first slice of a step also carries the eight direct
-// loads of the next step.
-__device__ __forceinline__ void nt_interleave(bool with_loads) {
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    if (i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
-    if (with_loads) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // one global load
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-  }
-}
-
-// First three slices of a K step: issue the next step's direct loads (past
-// the end of K they read zeros into the idle buffer), then multiply slices
-// 0-2 of the current stage while reading slices 1-3.  f0 holds slice 0 on
-// entry; f1 holds slice 3 on exit.
-__device__ __forceinline__ void nt_step(const unsigned short *__restrict__ rA,
-                                        const unsigned short *__restrict__ rB,
-                                        unsigned short *__restrict__ wA,
-                                        unsigned short *__restrict__ wB, const BigFill &fa,
-                                        const BigFill &fb, __amdgpu_buffer_rsrc_t ra,
-                                        __amdgpu_buffer_rsrc_t rb, int k_next, int K, int wave,
-                                        int offA, int offB, const int (&sw)[4], NtFrags &f0,
-                                        NtFrags &f1, f32x16 (&acc)[4][2]) {
-  fa.issue(wA, ra, k_next, K, wave);
-  fb.issue(wB, rb, k_next, K, wave);
-  const char *pa = reinterpret_cast<const char *>(rA) + offA;
-  const char *pb = reinterpret_cast<const char *>(rB) + offB;
-  nt_load(f1, pa, pb, sw[1]);
-  nt_mma(acc, f0);
-  nt_interleave(true);
-  nt_load(f0, pa, pb, sw[2]);
-  nt_mma(acc, f1);
-  nt_interleave(false);
-  nt_load(f1, pa, pb, sw[3]);
-  nt_mma(acc, f0);
-  nt_interleave(false);
-}
-
-// lda, ldb and K must be multiples of 8 and 256 * ld * 2 < 2^30; rows beyond
-// M / N and chunks beyond K read as zero.  Grid: big_blocks(M, N) x BIG_THREADS.
-constexpr int BIG_THREADS = 512;
-
-template <class Epi>
-__global__ void __launch_bounds__(BIG_THREADS, 1) k_gemm_big(const unsigned short *__restrict__ A,
-                                                             long lda,
-                                                             const unsigned short *__restrict__ B,
-                                                             long ldb, int M, int N, int K, Epi ep) {
-  __shared__ __attribute__((aligned(1024))) unsigned short lds[2 * BIG_STAGE];
-  const int nM = (M + BIG - 1) / BIG, nN = (N + BIG - 1) / BIG;
-  int mt, nt;
-  if (!big_tile(nM, nN, mt, nt)) return;
-  const int m0 = mt * BIG, n0 = nt * BIG;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 2, wn = wave & 3, col = lane & 31, hh = lane >> 5;
-
-  // each resource covers only the block's own rows (< 2^30 bytes), so the
-  // offset of a chunk past K (+2^30) is out of range and reads zero
-  const __amdgpu_buffer_rsrc_t ra =
-      gemm_rsrc(A + (long)m0 * lda, (long)(M - m0 < BIG ? M - m0 : BIG) * lda * 2);
-  const __amdgpu_buffer_rsrc_t rb =
-      gemm_rsrc(B + (long)n0 * ldb, (long)(N - n0 < BIG ? N - n0 : BIG) * ldb * 2);
-  BigFill fa, fb;
-  fa.init(wave, lane, lda);
-  fb.init(wave, lane, ldb);
-
-  // fragment reads: row (wave corner + i*32 + col), logical chunk 2*kk + hh
-  const int sx = (col >> 1) & 7;
-  int sw[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) sw[kk] = ((2 * kk + hh) ^ sx) * 16;
-  const int offA = (wm * 128 + col) * 128, offB = (wn * 64 + col) * 128;
-
-  f32x16 acc[4][2];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
-
-  unsigned short *s0 = lds, *s1 = lds + BIG_STAGE;
-  const int nk = (K + BKB - 1) / BKB;
-  fa.issue(s0, ra, 0, K, wave);
-  fb.issue(s0 + BIG * BKB, rb, 0, K, wave);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  NtFrags f0, f1;
-  nt_load(f0, reinterpret_cast<const char *>(s0) + offA,
-          reinterpret_cast<const char *>(s0 + BIG * BKB) + offB, sw[0]);
-  for (int kt = 0; kt < nk; ++kt) {
-    unsigned short *cur = (kt & 1) ? s1 : s0;
-    unsigned short *nxt = (kt & 1) ? s0 : s1;
-    nt_step(cur, cur + BIG * BKB, nxt, nxt + BIG * BKB, fa, fb, ra, rb, (kt + 1) * BKB, K, wave,
-            offA, offB, sw, f0, f1, acc);
-    // every wave is done reading this stage and the next one has landed; the
-    // last slice's products then cover the reads of the next stage's first
-    // slice (after the last step they read the zero-filled idle buffer)
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    nt_load(f0, reinterpret_cast<const char *>(nxt) + offA,
-            reinterpret_cast<const char *>(nxt + BIG * BKB) + offB, sw[0]);
-    nt_mma(acc, f1);
-    nt_interleave(false);
-  }
-  ep(acc, Tile{m0, n0, M, N, wm * 128, wn * 64, col, hh, BIG});
-}
-
-// ------------------------------------------------- 256x256, transposed operands
-// C[m][n] = sum_k At[k][m] * Bt[k][n] with At [K][lda], Bt [K][ldb] row-major
-// (the weight gradients W^T-style: both operands run along the rows of a
-// chunk); lda and ldb are multiples of 8 with lda >= M and ldb >= N.  Tiles hold 64 k-rows x 256 columns (512 B per row); 16-byte chunk
-// c of row r sits in slot c ^ 4*(r & 3), so a 32-lane transpose read (4 rows x
-// 64 bytes) hits 16 distinct slots of the 64 banks.  Fragments come from
-// ds_read_b64_tr_b16 pairs: lane l gets column (l % 32) of rows
-// {4h..4h+3, 8+4h..8+4h+3} (h = l / 32) of the slice; A and B use the same
-// row order, so every product pairs equal k.
-
-typedef short gemm_v4i16 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) gemm_v4i16 gemm_lds_v4i16;
-
-struct BigFillT {
-  int voff[4];  // byte offset of the lane's chunk in each of its 4 row pairs
-  __device__ __forceinline__ void init(int wave, int lane, long ld) {
-    const int rr = lane >> 5, p = lane & 31;
-    // op j of a wave covers rows 2*(8j + wave) + {0, 1}; row & 3 = (2*wave + rr) & 3
-    const int c = p ^ (4 * ((2 * wave + rr) & 3));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) voff[j] = (int)((2 * (j * 8 + wave) + rr) * ld * 2) + c * 16;
-  }
-  // rs covers the step's rows (from k0) of the block's columns
-  __device__ __forceinline__ void issue(unsigned short *__restrict__ tile,
-                                        __amdgpu_buffer_rsrc_t rs, int wave) const {
-#if defined(__HIP_DEVICE_COMPILE__)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rs, (__attribute__((address_space(3))) void *)(tile + (j * 8 + wave) * 2 * BIG), 16,
-          voff[j], 0, 0, 0);
-#endif
-  }
-};
-
-// resource over rows [k0, min(K, k0 + 64)) of columns [c0, C) of a [K][ld]
-// matrix (zero rows past K).  The last row stops at column C rounded up to
-// a 16-byte chunk, so the range never ends inside a chunk or a dword whose
-// first element is in range; ld is a multiple of 8 and every row holds ld
-// elements, so the rounded end stays inside the matrix.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tn_rsrc(const unsigned short *X, long ld, int k0,
-                                                         int K, int c0, int C) {
-  const int rows = K - k0 < BKB ? K - k0 : BKB;
-  const long bytes = rows > 0 ? ((long)(rows - 1) * ld + ((C - c0 + 7) & ~7)) * 2 : 0;
-  return gemm_rsrc(X + (long)k0 * ld + c0, bytes);
-}
-
-__device__ __forceinline__ bf16x8 tr_frag(const char *p) {
-  const gemm_v4i16 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((gemm_lds_v4i16 *)p);
-  const gemm_v4i16 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((gemm_lds_v4i16 *)(p + 8 * 512));
-  const bf16x4 a4 = __builtin_bit_cast(bf16x4, a), b4 = __builtin_bit_cast(bf16x4, b);
-  bf16x8 r;
-  r[0] = a4[0]; r[1] = a4[1]; r[2] = a4[2]; r[3] = a4[3];
-  r[4] = b4[0]; r[5] = b4[1]; r[6] = b4[2]; r[7] = b4[3];
-  return r;
-}
-
-// slice kk of the stage: rows 16*kk.. ; oa/ob: per-lane byte offsets of the
-// four 32-column blocks (row part included)
-__device__ __forceinline__ void big_load_tn(NtFrags &f, const char *pa, const char *pb,
-                                            const int (&oa)[4], const int (&ob)[2], int kk) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) f.a[i] = tr_frag(pa + kk * 16 * 512 + oa[i]);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) f.b[i] = tr_frag(pb + kk * 16 * 512 + ob[i]);
-}
-
-// the twelve transpose reads of the next slice ride with its eight products
-__device__ __forceinline__ void big_interleave_tn(bool with_loads) {
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    if (i < 4) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // two LDS reads
-    else __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);       // one LDS read
-    if (with_loads) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // one global load
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                 // one MFMA
-  }
-}
-
-__device__ __forceinline__ void big_step_tn(const unsigned short *__restrict__ rA,
-                                            const unsigned short *__restrict__ rB,
-                                            unsigned short *__restrict__ wA,
-                                            unsigned short *__restrict__ wB, const BigFillT &fa,
-                                            const BigFillT &fb, __amdgpu_buffer_rsrc_t ra,
-                                            __amdgpu_buffer_rsrc_t rb, int wave, const int (&oa)[4],
-                                            const int (&ob)[2], NtFrags &f0, NtFrags &f1,
-                                            f32x16 (&acc)[4][2]) {
-  fa.issue(wA, ra, wave);
-  fb.issue(wB, rb, wave);
-  const char *pa = reinterpret_cast<const char *>(rA);
-  const char *pb = reinterpret_cast<const char *>(rB);
-  big_load_tn(f1, pa, pb, oa, ob, 1);
-  nt_mma(acc, f0);
-  big_interleave_tn(true);
-  big_load_tn(f0, pa, pb, oa, ob, 2);
-  nt_mma(acc, f1);
-  big_interleave_tn(false);
-  big_load_tn(f1, pa, pb, oa, ob, 3);
-  nt_mma(acc, f0);
-  big_interleave_tn(false);
-}
-
-// Up to three transposed-operand problems over the same K rows, run by one
-// launch (their tiles in sequence), so a short last wave of one problem is
-// filled by the next.  Each: C_p[M_p][N_p] (+)= At_p^T Bt_p.
-template <class Epi, int NP>
-struct TnGroup {
-  const unsigned short *At[NP], *Bt[NP];
-  long lda[NP], ldb[NP];
+// NP problems run by one launch (their tiles in sequence, so a short last
+// wave of one is filled by the next); each sums NS products over their own K:
+//   C_p = sum_s A_ps B_ps^T
+// lda, ldb multiples of 8 (and at least the operand's width); N operands need
+// K a multiple of 8; 256 * ld * 2 < 2^30 (N), 64 * ld * 2 < 2^31 (T).  With
+// NS = 1 the K range may be cut into `splits` parts of k_part rows (a multiple
+// of 64), each a set of tiles of its own: the epilogue then gets partial sums.
+template <class Epi, int NP, int NS>
+struct Problems {
+  const unsigned short *A[NP][NS], *B[NP][NS];
+  long lda[NP][NS], ldb[NP][NS];
+  int K[NS];
   int M[NP], N[NP];
   Epi ep[NP];
   int start[NP + 1];  // first tile of each problem; start[NP] = all tiles
+  int splits, k_part;
 };
 
-// lda, ldb multiples of 8, 64 * ld * 2 < 2^30; K >= 0 rows (rows past K read
-// as zero); columns past M / N are computed from whatever the rows hold there
-// and dropped by the epilogue.  Grid: 8 * ceil(tiles / 8) x 256.
-template <class Epi, int NP>
-__global__ void __launch_bounds__(512, 1) k_gemm_big_tn(const TnGroup<Epi, NP> g, int K) {
-  __shared__ __attribute__((aligned(1024))) unsigned short lds[2 * BIG_STAGE];
-  const int idx = big_index(g.start[NP]);
-  if (idx >= g.start[NP]) return;
+#define GEMM_FENCE() asm volatile("" ::: "memory")
+
+// Grid: 8 * ceil(tiles * splits / 8) x 512.
+template <bool TA, bool TB, int TM, class Epi, int NP, int NS>
+__global__ void __launch_bounds__(THREADS, 1) k_gemm(const Problems<Epi, NP, NS> g) {
+  constexpr int BM = bm_of(TM), SA = BM * BK * 2, SB = BN * BK * 2;  // bytes of a slot
+  constexpr int LDS_B = SA * SLOTS_A;                                // the B ring follows the A ring
+  __shared__ __attribute__((aligned(1024))) char lds[LDS_B + SB * SLOTS_B];
+  int idx = xcd_index(g.start[NP] * g.splits);
+  if (idx >= g.start[NP] * g.splits) return;
+  int split = 0;
+  if constexpr (NS == 1) {
+    split = idx / g.start[NP];
+    idx -= split * g.start[NP];
+  }
   // the problem's fields by unrolled selects (no dynamic indexing of the
   // kernel argument, which would copy it to scratch)
-  const unsigned short *At = g.At[0], *Bt = g.Bt[0];
-  long lda = g.lda[0], ldb = g.ldb[0];
   int M = g.M[0], N = g.N[0], first = 0;
+  const unsigned short *pA[NS], *pB[NS];
+  long la[NS], lb[NS];
   Epi ep = g.ep[0];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    pA[s] = g.A[0][s];
+    pB[s] = g.B[0][s];
+    la[s] = g.lda[0][s];
+    lb[s] = g.ldb[0][s];
+  }
 #pragma unroll
   for (int q = 1; q < NP; ++q)
     if (idx >= g.start[q]) {
-      At = g.At[q];
-      Bt = g.Bt[q];
-      lda = g.lda[q];
-      ldb = g.ldb[q];
       M = g.M[q];
       N = g.N[q];
       first = g.start[q];
       ep = g.ep[q];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        pA[s] = g.A[q][s];
+        pB[s] = g.B[q][s];
+        la[s] = g.lda[q][s];
+        lb[s] = g.ldb[q][s];
+      }
     }
   int mt, nt;
-  big_tile_of(idx - first, (M + BIG - 1) / BIG, (N + BIG - 1) / BIG, mt, nt);
-  const int m0 = mt * BIG, n0 = nt * BIG;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 2, wn = wave & 3, col = lane & 31, hh = lane >> 5;
+  tile_of(idx - first, (M + BM - 1) / BM, (N + BN - 1) / BN, mt, nt);
+  const int m0 = mt * BM, n0 = nt * BN;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = wave >> 2;  // waves w and w + 4 share a SIMD
+  const int wm = grp, wn = wave & 3, w4 = wave & 3;
 
-  BigFillT fa, fb;
-  fa.init(wave, lane, lda);
-  fb.init(wave, lane, ldb);
-  // transpose-read offsets: row 4*hh + (lane%16)/4 of the slice, column
-  // (wave corner) + 32*i + 16*((lane/16)%2) + 4*(lane%4)
-  const int l16 = lane & 15, r = 4 * hh + (l16 >> 2), sx = 4 * (r & 3);
-  int oa[4], ob[2];
+  Loader ldr;
+  auto open = [&](int s) __attribute__((always_inline)) {  // the group's operand of product s
+    if (grp == 0) ldr.init<TA, BM>(pA[s], la[s], m0, M, w4, lane);
+    else ldr.init<TB, BN>(pB[s], lb[s], n0, N, w4, lane);
+  };
+  open(0);
+  Frag<TA, BM, 2 * TM> fA;
+  Frag<TB, BN, 4> fB;
+  fA.init(0, wm * 32 * TM, lane);
+  fB.init(LDS_B, wn * 64, lane);
+
+  f32x4 acc[2 * TM][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int ca = wm * 128 + 32 * i + 16 * ((lane >> 4) & 1) + 4 * (l16 & 3);
-    oa[i] = r * 512 + (((ca >> 3) ^ sx) << 4) + (ca & 7) * 2;
+  for (int i = 0; i < 2 * TM; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{};
+
+  int nk = 0, seg = 0, k_next = 0, K_seg = g.K[0];
+  if constexpr (NS == 1) {
+    k_next = split * g.k_part;
+    K_seg = min(K_seg, k_next + g.k_part);
+    nk = (K_seg - k_next + BK - 1) / BK;
+  } else {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) nk += (g.K[s] + BK - 1) / BK;
   }
+  const unsigned base = (unsigned)(unsigned long)(__attribute__((address_space(3))) char *)lds;
+  // sets up the group's next step of loads
+  auto prep = [&]() __attribute__((always_inline)) {
+    if constexpr (NS > 1) {
+      if (k_next >= K_seg && seg + 1 < NS) {
+        ++seg;
+        k_next = 0;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int cb = wn * 64 + 32 * i + 16 * ((lane >> 4) & 1) + 4 * (l16 & 3);
-    ob[i] = r * 512 + (((cb >> 3) ^ sx) << 4) + (cb & 7) * 2;
-  }
-
-  f32x16 acc[4][2];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
-
-  unsigned short *s0 = lds, *s1 = lds + BIG_STAGE;
-  const int nk = (K + BKB - 1) / BKB;
-  fa.issue(s0, tn_rsrc(At, lda, 0, K, m0, M), wave);
-  fb.issue(s0 + BIG * BKB, tn_rsrc(Bt, ldb, 0, K, n0, N), wave);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  NtFrags f0, f1;
-  big_load_tn(f0, reinterpret_cast<const char *>(s0), reinterpret_cast<const char *>(s0 + BIG * BKB),
-              oa, ob, 0);
-  for (int kt = 0; kt < nk; ++kt) {
-    unsigned short *cur = (kt & 1) ? s1 : s0;
-    unsigned short *nxt = (kt & 1) ? s0 : s1;
-    const int k1 = (kt + 1) * BKB;
-    big_step_tn(cur, cur + BIG * BKB, nxt, nxt + BIG * BKB, fa, fb, tn_rsrc(At, lda, k1, K, m0, M),
-                tn_rsrc(Bt, ldb, k1, K, n0, N), wave, oa, ob, f0, f1, acc);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    big_load_tn(f0, reinterpret_cast<const char *>(nxt),
-                reinterpret_cast<const char *>(nxt + BIG * BKB), oa, ob, 0);
-    nt_mma(acc, f1);
-    big_interleave_tn(false);
-  }
-  ep(acc, Tile{m0, n0, M, N, wm * 128, wn * 64, col, hh, BIG});
-}
-
-inline int big_tiles(int M, int N) {
-  return M <= 0 || N <= 0 ? 0 : ((M + BIG - 1) / BIG) * ((N + BIG - 1) / BIG);
-}
-
-template <class Epi, int NP>
-inline void gemm_launch_tn(TnGroup<Epi, NP> g, int K, hipStream_t st) {
-  g.start[0] = 0;
-  for (int q = 0; q < NP; ++q) g.start[q + 1] = g.start[q] + big_tiles(g.M[q], g.N[q]);
-  if (g.start[NP] == 0) return;
-  k_gemm_big_tn<Epi, NP><<<(unsigned)((g.start[NP] + 7) / 8 * 8), 512, 0, st>>>(g, K);
-}
-
-template <class Epi>
-inline void gemm_launch_tn(const unsigned short *At, long lda, const unsigned short *Bt, long ldb,
-                           int M, int N, int K, const Epi &ep, hipStream_t st) {
-  TnGroup<Epi, 1> g{};
-  g.At[0] = At;
-  g.Bt[0] = Bt;
-  g.lda[0] = lda;
-  g.ldb[0] = ldb;
-  g.M[0] = M;
-  g.N[0] = N;
-  g.ep[0] = ep;
-  gemm_launch_tn(g, K, st);
-}
-
-// Block shape for a problem: the 256-wide tiles unless they would leave more
-// than a quarter of the CUs idle in the first wave.
-inline bool gemm_use_big(int M, int N) {
-  return (long)((M + BIG - 1) / BIG) * ((N + BIG - 1) / BIG) >= 192;
-}
-
-template <class Epi>
-inline void gemm_launch(const unsigned short *A, long lda, const unsigned short *B, long ldb, int M,
-                        int N, int K, const Epi &ep, hipStream_t st) {
-  if (M <= 0 || N <= 0) return;
-  if (gemm_use_big(M, N))
-    k_gemm_big<Epi><<<big_blocks(M, N), BIG_THREADS, 0, st>>>(A, lda, B, ldb, M, N, K, ep);
-  else
-    k_gemm_nt<Epi><<<grid(M, N), 256, 0, st>>>(A, lda, B, ldb, M, N, K, ep);
-}
-
-// y[c][r] = x[r][c] for a [rows][cols] matrix (ldx), output [cols][ldy]; x is
-// bf16 bits or fp32 (rounded); optional row gather; zero for r >= rows up to
-// pad_rows.
-template <class TI>
-__global__ void __launch_bounds__(256) k_transpose2d(const TI *__restrict__ x, long ldx,
-                                                     const int32_t *__restrict__ rowmap, int rows,
-                                                     int cols, int pad_rows,
-                                                     unsigned short *__restrict__ y, long ldy) {
-  __shared__ unsigned short t[64][66];
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4) {
-    const int r = r0 + i, c = c0 + tx;
-    unsigned short b = 0;
-    if (r < rows && c < cols) {
-      const long sr = rowmap ? rowmap[r] : r;
-      b = load_bf(x, sr * ldx + c);
+        for (int s = 1; s < NS; ++s)
+          if (s == seg) {
+            K_seg = g.K[s];
+            open(s);
+          }
+      }
     }
-    t[i][tx] = b;
+    if (TA == TB || grp == 0) ldr.prep<TA>(k_next, K_seg);
+    else ldr.prep<TB>(k_next, K_seg);
+    if constexpr (NS > 1) {
+      // carried through the change of products in vector registers
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ldr.rs[i] = __builtin_amdgcn_readfirstlane(ldr.rs[i]);
+    }
+    k_next += BK;
+  };
+  constexpr int LA = BM / 32, LB = BN / 32;  // loads per wave of an A and of a B step
+  const unsigned ring = base + (grp == 0 ? 0 : LDS_B);
+  auto load = [&](int slot, int j) __attribute__((always_inline)) {
+    if (LA == LB || j < LA || grp == 1) ldr.load(ring + slot, j, w4);
+  };
+  prep();
+#pragma unroll
+  for (int j = 0; j < LB; ++j) load(0, j);
+  if (grp == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else {
+    prep();
+#pragma unroll
+    for (int j = 0; j < LB; ++j) load(SB, j);
+    if (nk > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LB) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
-  __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    const int c = c0 + i, r = r0 + tx;
-    if (c < cols && r < pad_rows) y[(long)c * ldy + r] = t[tx][i];
+  __builtin_amdgcn_s_barrier();
+  GEMM_FENCE();
+  if (grp == 1 && nk > 0) __builtin_amdgcn_s_barrier();  // half a step behind group 0
+  GEMM_FENCE();
+
+  // Both groups pass the same number of barriers (group 1 one more before the
+  // loop and none after its last products).  Before the barrier that opens
+  // group 0's reads of step t + 1, group 0 has waited for its A loads of that
+  // step (issued with step t) and group 1 for its B loads of it (issued with
+  // step t - 1; those of t + 2 stay in flight).  A slot is overwritten by
+  // loads issued behind a barrier that both groups reach with their reads of
+  // it complete.  One loop body for every slot: unrolled with an exit in each
+  // copy, the accumulators went through memory at the exits.
+  int slot_b = 0, slot_b2 = 2 * SB;  // of steps t and t + 2
+#pragma unroll 1
+  for (int t = 0; t < nk; ++t) {
+    const int slot_a = (t & 1) * SA;
+    const int slot_n = grp == 0 ? SA - slot_a : slot_b2;
+    bf16x8 a[2][2 * TM], b[2][4];
+    // the loads (of A for step t + 1, of B for t + 2; past the end they read
+    // zeros into a free slot) go out between the fragment reads, so that the
+    // two queues work side by side
+    prep();
+    constexpr int NR = 2 * TM + 4, PER = LB / 2;  // reads and loads per slice
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int f = 0; f < NR; ++f) {
+#pragma unroll
+        for (int j = f * PER / NR; j < PER; ++j)
+          if (j * NR / PER == f) load(slot_n, kk * PER + j);
+        if (f < 4) b[kk][f] = fB.read(lds, slot_b, kk, f);
+        else a[kk][f - 4] = fA.read(lds, slot_a, kk, f - 4);
+      }
+    }
+    if (grp == 0)
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    else if (t + 2 < nk)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LB) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    GEMM_FENCE();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int i = 0; i < 2 * TM; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          const int j = (i & 1) ? 3 - jj : jj;  // one operand changes at a time
+          acc[i][j] = Epi::kSwap ? mfma16(b[kk][j], a[kk][i], acc[i][j])
+                                 : mfma16(a[kk][i], b[kk][j], acc[i][j]);
+        }
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    slot_b = slot_b == 2 * SB ? 0 : slot_b + SB;
+    slot_b2 = slot_b2 == 2 * SB ? 0 : slot_b2 + SB;
+    if (grp == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (grp == 0 || t + 1 < nk) __builtin_amdgcn_s_barrier();
+    GEMM_FENCE();
   }
+  // every load has landed and every slot has been read: a wave may use its
+  // own eighth of the LDS in the epilogue
+  ep(acc, Tile{m0, n0, M, N, wm * 32 * TM, wn * 64, lane & 15, lane >> 4, split,
+               lds + wave * (int)(sizeof(lds) / 8)});
 }
 
-inline dim3 grid64(long cols, long rows) {
-  return dim3((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64));
+inline int tiles_of(int M, int N, int TM) {
+  return M <= 0 || N <= 0 ? 0 : ((M + bm_of(TM) - 1) / bm_of(TM)) * ((N + BN - 1) / BN);
+}
+
+template <bool TA, bool TB, int TM, class Epi, int NP, int NS>
+inline void launch_tm(Problems<Epi, NP, NS> &g, hipStream_t st) {
+  g.start[0] = 0;
+  for (int q = 0; q < NP; ++q) g.start[q + 1] = g.start[q] + tiles_of(g.M[q], g.N[q], TM);
+  const long total = (long)g.start[NP] * g.splits;
+  if (total == 0) return;
+  k_gemm<TA, TB, TM, Epi, NP, NS><<<(unsigned)((total + 7) / 8 * 8), THREADS, 0, st>>>(g);
+  SEG_LAUNCH_CHECK();
+}
+
+constexpr int NUM_CU = 256;
+
+// Whole waves of blocks over the chip (one block per CU), in units of a
+// 256-row tile's time.  A 128-row tile takes 0.62 of that (1,190 against
+// 1,470 TFLOP/s at 8192^3).
+inline double wave_cost(long tiles, int TM) {
+  const double per = TM == 4 ? 1.0 : 0.62;
+  return per * (double)((tiles + NUM_CU - 1) / NUM_CU);
+}
+
+// All products of the group with one launch.  Tiles of 128 rows where the last
+// wave of 256-row ones would leave so much of the chip idle that they lose.
+template <bool TA, bool TB, class Epi, int NP, int NS>
+inline void launch(Problems<Epi, NP, NS> g, hipStream_t st) {
+  g.splits = 1;
+  g.k_part = 0x7fffffff;
+  long t4 = 0, t2 = 0;
+  for (int q = 0; q < NP; ++q) {
+    t4 += tiles_of(g.M[q], g.N[q], 4);
+    t2 += tiles_of(g.M[q], g.N[q], 2);
+  }
+  if (wave_cost(t2, 2) < wave_cost(t4, 4)) launch_tm<TA, TB, 2>(g, st);
+  else launch_tm<TA, TB, 4>(g, st);
+}
+
+// One product.
+template <bool TA, bool TB, class Epi>
+inline void launch_one(const unsigned short *A, long lda, const unsigned short *B, long ldb, int M,
+                       int N, int K, const Epi &ep, hipStream_t st) {
+  Problems<Epi, 1, 1> g{{{A}}, {{B}}, {{lda}}, {{ldb}}, {K}, {M}, {N}, {ep}, {}, 1, 0};
+  launch<TA, TB>(g, st);
 }
 
 }  // namespace gemm

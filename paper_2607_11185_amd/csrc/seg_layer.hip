@@ -5,9 +5,9 @@
 // token's row inside its segment as position, the segmented attention of
 // seg_attn.hip, output projection, RMSNorm and a SwiGLU MLP, with residual
 // connections; forward and backward on gfx950.  Projections and the MLP run
-// over row chunks with the shared GEMMs (gemm.h): data products with the NT
-// kernel (weights transposed once per call), weight gradients with the
-// transposed-operand kernel straight from the chunk's row-major activations.
+// over row chunks with the shared GEMM (gemm.h), which reads weights and
+// activations in place in either orientation: a data gradient contracts over
+// the weight's rows, a weight gradient over the chunk's rows.
 // Weight gradients are summed chunk after chunk and the norm-weight gradients
 // through fixed-order partial sums, so results are bitwise reproducible.
 #include <cmath>
@@ -28,10 +28,14 @@ extern "C" size_t seg_attn_workspace_bytes(const seg_sizes *, seg_dtype, int32_t
 namespace seg {
 namespace {
 
-using gemm::EpiAccum;
-using gemm::EpiResid;
-using gemm::EpiStore;
-using gemm::k_transpose2d;
+using gemm::ACC;
+using gemm::EpiOut;
+using gemm::RESID;
+using gemm::ST;
+typedef EpiOut<unsigned short, ST> OutBf;
+typedef EpiOut<unsigned short, RESID> OutResid;
+typedef EpiOut<float, ST> OutF32;
+typedef EpiOut<float, ACC> OutGrad;
 
 constexpr int MAX_CH = 16;   // hidden <= 8 * 64 * MAX_CH
 constexpr int RMS_ROWS = 32; // rows per block of the norm backward
@@ -257,35 +261,63 @@ __global__ void k_interleave_gu(const unsigned short *__restrict__ wg,
   }
 }
 
-// Epilogue of the GEMM against wgu (the 256-wide NT kernel): m = silu(g) * u
-// for the wave's 32 features, in fp32 from the accumulators (acc[.][0] holds
-// the gate, acc[.][1] the up values of the same rows and features); with g
-// and u set, also stores the gate and up values (the backward's recompute).
-// Outputs are [rows][ld] bf16 at feature columns.
+// Epilogue of the GEMM against wgu: m = silu(g) * u for the wave's 32
+// features, in fp32 from the accumulators (columns 0..31 of the wave tile hold
+// the gate, 32..63 the up values of the same features); with g and u set,
+// also stores the gate and up values (the backward's recompute).  Outputs are
+// workspace arrays [rows][ld] bf16 at feature columns, ld a multiple of 8.  32
+// rows x 32 features at a time go through the wave's LDS, so a lane stores 8
+// features (16 bytes) of a row.
 struct EpiSwiGLU {
+  static constexpr bool kSwap = true;
   unsigned short *m, *g, *u;
   long ld;
   int I;
-  template <int TM, int TN>
-  __device__ __forceinline__ void operator()(const f32x16 (&acc)[TM][TN],
+  template <int NI, int NJ>
+  __device__ __forceinline__ void operator()(const f32x4 (&acc)[NI][NJ],
                                              const gemm::Tile &t) const {
-    static_assert(TN == 2, "SwiGLU epilogue expects 64-column wave tiles");
-    const int f = (t.n0 + t.wc) / 2 + t.col;  // the lane's feature
-    if (f >= I) return;
+    static_assert(NJ == 4, "SwiGLU epilogue expects 64-column wave tiles");
+    const int lane = t.grp * 16 + t.col, q = lane & 3;
+    const int f = (t.n0 + t.wc) / 2 + q * 8;  // the lane's features when storing
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    // [3 outputs][32 rows][8 chunks of 4 features] (2 KB each), chunk c of row
+    // r in slot c ^ (r & 6): pairs of chunks stay together
+    gemm::u32x2 *w = reinterpret_cast<gemm::u32x2 *>(t.lds);
 #pragma unroll
-    for (int bm = 0; bm < TM; ++bm)
+    for (int bm = 0; bm < NI / 2; ++bm) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = t.row(bm, r);
-        if (row >= t.M) continue;
-        const float gv = acc[bm][0][r], uv = acc[bm][1][r];
-        const long off = (long)row * ld + f;
-        m[off] = f2bf_bits(gv * sigmoidf_(gv) * uv);
-        if (g) {
-          g[off] = f2bf_bits(gv);
-          u[off] = f2bf_bits(uv);
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const f32x4 gv = acc[bm * 2 + i][j], uv = acc[bm * 2 + i][j + 2];
+          float mv[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mv[r] = gv[r] * sigmoidf_(gv[r]) * uv[r];
+          const int at = (i * 16 + t.col) * 8 + ((j * 4 + t.grp) ^ (t.col & 6));
+          w[at] = gemm::u32x2{gemm::pack2(mv[0], mv[1]), gemm::pack2(mv[2], mv[3])};
+          if (g) {
+            w[256 + at] = gemm::u32x2{gemm::pack2(gv[0], gv[1]), gemm::pack2(gv[2], gv[3])};
+            w[512 + at] = gemm::u32x2{gemm::pack2(uv[0], uv[1]), gemm::pack2(uv[2], uv[3])};
+          }
+        }
+      __builtin_amdgcn_wave_barrier();
+      if (f < I) {  // I is a multiple of 8
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const int r = p * 16 + (lane >> 2), row = t.m0 + t.wr + bm * 32 + r;
+          const int at = r * 8 + ((2 * q) ^ (r & 6));
+          if (row < t.M) {
+            const long off = (long)row * ld + f;
+            *reinterpret_cast<u32x4 *>(m + off) = *reinterpret_cast<const u32x4 *>(w + at);
+            if (g) {
+              *reinterpret_cast<u32x4 *>(g + off) = *reinterpret_cast<const u32x4 *>(w + 256 + at);
+              *reinterpret_cast<u32x4 *>(u + off) = *reinterpret_cast<const u32x4 *>(w + 512 + at);
+            }
+          }
         }
       }
+      __builtin_amdgcn_wave_barrier();
+    }
   }
 };
 
@@ -351,7 +383,7 @@ Dims dims_of(const seg_sizes &sz, const seg_layer_cfg &c) {
 
 struct LayerWs {
   size_t pos, a, m, wgu, attn;                                   // forward
-  size_t wdT, wgT, wuT, woT, wqT, wkT, wvT, dy1, dO, dq, dk, dv;  // backward
+  size_t dy1, dO, dq, dk, dv;  // backward
   size_t g, u, dm, dg, du, dbf, part;
   size_t total;
 };
@@ -373,13 +405,6 @@ LayerWs layer_ws(const seg_sizes &sz, const seg_layer_cfg &c, int bwd) {
   w.wgu = take(2 * Ip * H * 2);
   w.attn = take(seg_attn_workspace_bytes(&sz, SEG_BF16, c.hq, c.hkv, c.d, bwd));
   if (bwd) {
-    w.wdT = take(I * H * 2);
-    w.wgT = take(H * I * 2);
-    w.wuT = take(H * I * 2);
-    w.woT = take((size_t)m.QD * H * 2);
-    w.wqT = take(H * m.QD * 2);
-    w.wkT = take(H * m.KD * 2);
-    w.wvT = take(H * m.KD * 2);
     w.dy1 = take(P * H * 2);
     w.dO = take(P * m.QD * 2);
     w.dq = take(P * m.QD * 2);
@@ -423,13 +448,6 @@ void check_layer(const seg_layout *L, const seg_sizes *sz, const seg_layer_cfg *
 #define US(p) reinterpret_cast<unsigned short *>(p)
 #define CUS(p) reinterpret_cast<const unsigned short *>(p)
 
-template <class Epi>
-void gemm_nt(const unsigned short *A, long lda, const unsigned short *B, long ldb, int M, int N, int K,
-             const Epi &ep, hipStream_t st) {
-  gemm::gemm_launch(A, lda, B, ldb, M, N, K, ep, st);
-  SEG_LAUNCH_CHECK();
-}
-
 void build_wgu(const seg_layer_weights &w, int I, int H, unsigned short *wgu, hipStream_t st) {
   const long rows2 = 2L * ((I + GU_BLOCK - 1) / GU_BLOCK * GU_BLOCK);
   k_interleave_gu<<<blocks_for(rows2 * (H / 8)), 256, 0, st>>>(CUS(w.wg), CUS(w.wu), I, H, rows2, wgu);
@@ -437,30 +455,12 @@ void build_wgu(const seg_layer_weights &w, int I, int H, unsigned short *wgu, hi
 }
 
 // rows x [gate | up] of a chunk against the interleaved weights, consumed by
-// the SwiGLU epilogue (always the 256-wide tiles: it pairs the two 32-column
-// halves of a 64-column wave tile)
+// the SwiGLU epilogue (which pairs the two 32-column halves of a 64-column
+// wave tile)
 void gate_up(const unsigned short *a, const unsigned short *wgu, int rows, int H, int I,
              const EpiSwiGLU &ep, hipStream_t st) {
   const int N = 2 * ((I + GU_BLOCK - 1) / GU_BLOCK * GU_BLOCK);
-  if (rows <= 0) return;
-  gemm::k_gemm_big<EpiSwiGLU><<<gemm::big_blocks(rows, N), gemm::BIG_THREADS, 0, st>>>(
-      a, H, wgu, H, rows, N, H, ep);
-  SEG_LAUNCH_CHECK();
-}
-
-// C[M][N] (+)= At^T Bt over K rows; At [K][lda], Bt [K][ldb]
-template <class Epi>
-void gemm_tn(const unsigned short *At, long lda, const unsigned short *Bt, long ldb, int M, int N,
-             int K, const Epi &ep, hipStream_t st) {
-  gemm::gemm_launch_tn(At, lda, Bt, ldb, M, N, K, ep, st);
-  SEG_LAUNCH_CHECK();
-}
-
-void transpose(const unsigned short *x, long ldx, int rows, int cols, int pad_rows,
-               unsigned short *y, hipStream_t st) {
-  k_transpose2d<unsigned short><<<gemm::grid64(cols, pad_rows), 256, 0, st>>>(
-      x, ldx, nullptr, rows, cols, pad_rows, y, pad_rows);
-  SEG_LAUNCH_CHECK();
+  gemm::launch_one<false, false>(a, H, wgu, H, rows, N, H, ep, st);
 }
 
 void rms_fwd(const unsigned short *x, long ldx, const void *g, float eps, int rows, int H,
@@ -533,9 +533,12 @@ void layer_fwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
       rms_fwd(x + r0 * H, H, w.g1, c.rms_eps, cr, H, pos + r0, a, sv.rstd1 + r0, st);
     }
     ProfScope prof("ly_proj", st);
-    gemm_nt(a, H, CUS(w.wq), H, cr, m.QD, H, EpiStore<unsigned short>{q + r0 * m.QD, m.QD, 1.f}, st);
-    gemm_nt(a, H, CUS(w.wk), H, cr, m.KD, H, EpiStore<unsigned short>{k + r0 * m.KD, m.KD, 1.f}, st);
-    gemm_nt(a, H, CUS(w.wv), H, cr, m.KD, H, EpiStore<unsigned short>{v + r0 * m.KD, m.KD, 1.f}, st);
+    gemm::Problems<OutBf, 3, 1> g{
+        {{a}, {a}, {a}}, {{CUS(w.wq)}, {CUS(w.wk)}, {CUS(w.wv)}}, {{H}, {H}, {H}}, {{H}, {H}, {H}}, {H},
+        {cr, cr, cr}, {m.QD, m.KD, m.KD},
+        {OutBf::make(q + r0 * m.QD, m.QD), OutBf::make(k + r0 * m.KD, m.KD),
+         OutBf::make(v + r0 * m.KD, m.KD)}, {}, 1, 0};
+    gemm::launch<false, false>(g, st);
   }
   {
     ProfScope prof("ly_rope", st);
@@ -553,8 +556,8 @@ void layer_fwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
     const int cr = (int)std::min<long>(m.C, P - r0);
     {
       ProfScope prof("ly_proj", st);
-      gemm_nt(o + r0 * m.QD, m.QD, CUS(w.wo), m.QD, cr, H, m.QD,
-              EpiResid{y1 + r0 * H, H, x + r0 * H, H, 1.f}, st);
+      gemm::launch_one<false, false>(o + r0 * m.QD, m.QD, CUS(w.wo), m.QD, cr, H, m.QD,
+                                     OutResid::make(y1 + r0 * H, H, 1.f, x + r0 * H, H), st);
     }
     {
       ProfScope prof("ly_norm", st);
@@ -562,7 +565,8 @@ void layer_fwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
     }
     ProfScope prof("ly_mlp", st);
     gate_up(a, wgu, cr, H, I, EpiSwiGLU{mb, nullptr, nullptr, I, I}, st);
-    gemm_nt(mb, I, CUS(w.wd), I, cr, H, I, EpiResid{y + r0 * H, H, y1 + r0 * H, H, 1.f}, st);
+    gemm::launch_one<false, false>(mb, I, CUS(w.wd), I, cr, H, I,
+                                   OutResid::make(y + r0 * H, H, 1.f, y1 + r0 * H, H), st);
   }
 }
 
@@ -576,9 +580,6 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
   int32_t *pos = reinterpret_cast<int32_t *>(base + W.pos);
   unsigned short *a = US(base + W.a), *gb = US(base + W.g), *ub = US(base + W.u), *mb = US(base + W.m),
                  *wgu = US(base + W.wgu);
-  unsigned short *wdT = US(base + W.wdT), *wgT = US(base + W.wgT), *wuT = US(base + W.wuT);
-  unsigned short *woT = US(base + W.woT), *wqT = US(base + W.wqT), *wkT = US(base + W.wkT),
-                 *wvT = US(base + W.wvT);
   unsigned short *dy1 = US(base + W.dy1), *dO = US(base + W.dO), *dq = US(base + W.dq),
                  *dk = US(base + W.dk), *dv = US(base + W.dv);
   unsigned short *dm = US(base + W.dm), *dgb = US(base + W.dg), *dub = US(base + W.du);
@@ -588,17 +589,10 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
                        *y1 = CUS(sv.y1);
   {
     ProfScope prof("ly_misc", st);
-    zero_grads(gr, c, st);
+    fill32(gr.g1, H, 0u, st);
+    fill32(gr.g2, H, 0u, st);
     positions(L, sz, P, pos, st);
     build_wgu(w, I, H, wgu, st);
-    // transposed weights (k-contiguous operands of the data-gradient GEMMs)
-    transpose(CUS(w.wd), I, H, I, H, wdT, st);        // wd [H, I] -> [I, H]
-    transpose(CUS(w.wg), H, I, H, I, wgT, st);        // wg [I, H] -> [H, I]
-    transpose(CUS(w.wu), H, I, H, I, wuT, st);
-    transpose(CUS(w.wo), m.QD, H, m.QD, H, woT, st);  // wo [H, QD] -> [QD, H]
-    transpose(CUS(w.wq), H, m.QD, H, m.QD, wqT, st);  // wq [QD, H] -> [H, QD]
-    transpose(CUS(w.wk), H, m.KD, H, m.KD, wkT, st);
-    transpose(CUS(w.wv), H, m.KD, H, m.KD, wvT, st);
     // dy1 starts as dy with the padding rows zeroed
     k_mask_rows<<<blocks_for(P * (H / 8)), 256, 0, st>>>(dy, pos, P, H, dy1);
     SEG_LAUNCH_CHECK();
@@ -614,30 +608,35 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
     {
       ProfScope prof("ly_mlp", st);
       gate_up(a, wgu, cr, H, I, EpiSwiGLU{mb, gb, ub, I, I}, st);  // m, g, u
-      gemm_nt(dy1c, H, wdT, H, cr, I, H, EpiStore<unsigned short>{dm, I, 1.f}, st);  // dm = dy wd
+      gemm::launch_one<false, true>(dy1c, H, CUS(w.wd), I, cr, I, H, OutBf::make(dm, I), st);  // dm = dy wd
       const long n8 = (long)cr * I / 8;
       k_swiglu_bwd<<<blocks_for(n8), 256, 0, st>>>(gb, ub, dm, dgb, dub, n8);
       SEG_LAUNCH_CHECK();
-      gemm_nt(dgb, I, wgT, I, cr, H, I, EpiStore<float>{dbf, H, 1.f}, st);  // db = dg wg + du wu
-      gemm_nt(dub, I, wuT, I, cr, H, I, EpiAccum{dbf, H, 1.f}, st);
+      // db = dg wg + du wu, one sum over both contractions
+      gemm::Problems<OutF32, 1, 2> g{{{dgb, dub}}, {{CUS(w.wg), CUS(w.wu)}}, {{I, I}}, {{H, H}}, {I, I},
+                                     {cr}, {H}, {OutF32::make(dbf, H)}, {}, 1, 0};
+      gemm::launch<false, true>(g, st);
     }
     {
       // dWd += dy^T m, dWg += dg^T b, dWu += du^T b in one launch
       ProfScope prof("ly_wgrad", st);
-      gemm::TnGroup<EpiAccum, 3> g{{dy1c, dgb, dub}, {mb, a, a}, {H, I, I}, {I, H, H}, {H, I, I},
-                                   {I, H, H},
-                                   {EpiAccum{gr.wd, I, 1.f}, EpiAccum{gr.wg, H, 1.f},
-                                    EpiAccum{gr.wu, H, 1.f}}, {}};
-      gemm::gemm_launch_tn(g, cr, st);
-      SEG_LAUNCH_CHECK();
+      const bool first = r0 == 0;
+      gemm::Problems<OutGrad, 3, 1> g{
+          {{dy1c}, {dgb}, {dub}}, {{mb}, {a}, {a}}, {{H}, {I}, {I}}, {{I}, {H}, {H}}, {cr}, {H, I, I},
+          {I, H, H},
+          {OutGrad::make(gr.wd, I, 1.f, nullptr, 0, first), OutGrad::make(gr.wg, H, 1.f, nullptr, 0, first),
+           OutGrad::make(gr.wu, H, 1.f, nullptr, 0, first)}, {}, 1, 0};
+      gemm::launch<true, true>(g, st);
     }
     {
       ProfScope prof("ly_norm", st);
       rms_bwd(y1 + r0 * H, w.g2, sv.rstd2 + r0, dbf, cr, H, pos + r0, dy1c, dy1c, part, gr.g2, st);
     }
     ProfScope prof("ly_proj", st);
-    gemm_tn(dy1c, H, o + r0 * m.QD, m.QD, H, m.QD, cr, EpiAccum{gr.wo, m.QD, 1.f}, st);  // dWo
-    gemm_nt(dy1c, H, woT, H, cr, m.QD, H, EpiStore<unsigned short>{dO + r0 * m.QD, m.QD, 1.f}, st);
+    gemm::launch_one<true, true>(dy1c, H, o + r0 * m.QD, m.QD, H, m.QD, cr,
+                                 OutGrad::make(gr.wo, m.QD, 1.f, nullptr, 0, r0 == 0), st);  // dWo
+    gemm::launch_one<false, true>(dy1c, H, CUS(w.wo), m.QD, cr, m.QD, H,
+                                  OutBf::make(dO + r0 * m.QD, m.QD), st);
   }
   check_status(seg_attn_bwd(L, sz, SEG_BF16, m.hq, m.hkv, m.d, 1.f / std::sqrt((float)m.d), q, k, v,
                             o, sv.lse, dO, dq, dk, dv, base + W.attn, ws_bytes - W.attn, st));
@@ -661,19 +660,23 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
     }
     {
       ProfScope prof("ly_proj", st);
-      gemm_nt(dq + r0 * m.QD, m.QD, wqT, m.QD, cr, H, m.QD, EpiStore<float>{dbf, H, 1.f}, st);
-      gemm_nt(dk + r0 * m.KD, m.KD, wkT, m.KD, cr, H, m.KD, EpiAccum{dbf, H, 1.f}, st);
-      gemm_nt(dv + r0 * m.KD, m.KD, wvT, m.KD, cr, H, m.KD, EpiAccum{dbf, H, 1.f}, st);
+      // da = dq wq + dk wk + dv wv, one sum over the three contractions
+      gemm::Problems<OutF32, 1, 3> g{{{dq + r0 * m.QD, dk + r0 * m.KD, dv + r0 * m.KD}},
+                                     {{CUS(w.wq), CUS(w.wk), CUS(w.wv)}}, {{m.QD, m.KD, m.KD}},
+                                     {{H, H, H}}, {m.QD, m.KD, m.KD}, {cr}, {H},
+                                     {OutF32::make(dbf, H)}, {}, 1, 0};
+      gemm::launch<false, true>(g, st);
     }
     {
       // dWq += dq^T a, dWk += dk^T a, dWv += dv^T a in one launch
       ProfScope prof("ly_wgrad", st);
-      gemm::TnGroup<EpiAccum, 3> g{{dq + r0 * m.QD, dk + r0 * m.KD, dv + r0 * m.KD}, {a, a, a},
-                                   {m.QD, m.KD, m.KD}, {H, H, H}, {m.QD, m.KD, m.KD}, {H, H, H},
-                                   {EpiAccum{gr.wq, H, 1.f}, EpiAccum{gr.wk, H, 1.f},
-                                    EpiAccum{gr.wv, H, 1.f}}, {}};
-      gemm::gemm_launch_tn(g, cr, st);
-      SEG_LAUNCH_CHECK();
+      const bool first = r0 == 0;
+      gemm::Problems<OutGrad, 3, 1> g{
+          {{dq + r0 * m.QD}, {dk + r0 * m.KD}, {dv + r0 * m.KD}}, {{a}, {a}, {a}},
+          {{m.QD}, {m.KD}, {m.KD}}, {{H}, {H}, {H}}, {cr}, {m.QD, m.KD, m.KD}, {H, H, H},
+          {OutGrad::make(gr.wq, H, 1.f, nullptr, 0, first), OutGrad::make(gr.wk, H, 1.f, nullptr, 0, first),
+           OutGrad::make(gr.wv, H, 1.f, nullptr, 0, first)}, {}, 1, 0};
+      gemm::launch<true, true>(g, st);
     }
     ProfScope prof("ly_norm", st);
     rms_bwd(x + r0 * H, w.g1, sv.rstd1 + r0, dbf, cr, H, pos + r0, dy1 + r0 * H, dx + r0 * H, part,

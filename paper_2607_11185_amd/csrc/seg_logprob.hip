@@ -8,11 +8,11 @@
 //      target logit;
 //   2. per row: LSE from the partials (fixed order), logp, rho, loss, the
 //      clipped flag and g = d loss_sum / d logp;
-//   3. dz = g * (onehot(target) - softmax(z)) as bf16, written in both
-//      orientations (one pass over zT);
+//   3. dzT = g * (onehot(target) - softmax(z))^T as bf16 (one pass over zT);
 //   4. dH = s * dz W and dW = s * dz^T h (MFMA).
-// All GEMMs use the shared "NT" kernel of gemm.h: C[m][n] = sum_k A[m][k] B[n][k]
-// with both operands k-contiguous.
+// All products use the shared kernel of gemm.h, which reads each operand in
+// the orientation it has: dzT [V][R] serves dH (contracting over its rows)
+// and dW (contracting along them), W and h serve as they are.
 #include <climits>
 #include <cmath>
 
@@ -22,7 +22,8 @@
 namespace seg {
 namespace {
 
-using gemm::EpiStore;
+using gemm::EpiOut;
+using gemm::ST;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -36,45 +37,66 @@ struct EpiLogits {
   const int32_t *target;  // [N]
   float *ztgt;      // [N]
   float scale;
-  // for the 256-wide NT kernel: a wave covers one 128-row slab of M; the two
-  // lane halves of a column are combined by a shuffle
-  template <int TM, int TN>
-  __device__ __forceinline__ void operator()(const f32x16 (&acc)[TM][TN],
+  static constexpr bool kSwap = false;
+  // A lane holds 32 of the 128 vocabulary rows of one column n (three other
+  // lanes the rest), so maximum, exponentials and sum mostly stay in the lane;
+  // a wave covers one 128-row slab.  Only the slab that the vocabulary ends in
+  // tests its rows, and only waves that hold a target look for it.
+  template <int NI, int NJ>
+  __device__ __forceinline__ void operator()(const f32x4 (&acc)[NI][NJ],
                                              const gemm::Tile &t) const {
-    static_assert(TM == 4, "logits epilogue expects 128-row wave tiles");
+    static_assert(NI == 8, "logits epilogue expects 128-row wave tiles");
     const int slab_row = t.m0 + t.wr;
+    if (slab_row >= t.M) return;
+    if (slab_row + 128 <= t.M) slab<true>(acc, t, slab_row);
+    else slab<false>(acc, t, slab_row);
+  }
+  template <bool WHOLE, int NI, int NJ>
+  __device__ __forceinline__ void slab(const f32x4 (&acc)[NI][NJ], const gemm::Tile &t,
+                                       int slab_row) const {
 #pragma unroll
-    for (int bn = 0; bn < TN; ++bn) {
-      const int n = t.column(bn);
+    for (int j = 0; j < NJ; ++j) {
+      const int n = t.n0 + t.wc + j * 16 + t.col;
       const bool nok = n < t.N;
-      const int tgt = nok ? target[n] : -1;
+      // the lane's rows are base + k, k = 16 i + r
+      const int base = slab_row + 4 * t.grp, left = t.M - base;
+      float *zp = zt + (long)base * ldz + n;
       float mx = -INFINITY;
 #pragma unroll
-      for (int bm = 0; bm < TM; ++bm)
+      for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int m = t.row(bm, r);
-          const float z = acc[bm][bn][r] * scale;
-          if (nok && m < t.M) {
-            zt[(long)m * ldz + n] = z;
-            if (m == tgt) ztgt[n] = z;
-            mx = fmaxf(mx, z * LOG2E);
+        for (int r = 0; r < 4; ++r) {
+          const int k = 16 * i + r;
+          const float z = acc[i][j][r] * scale;
+          if (WHOLE || k < left) {
+            if (nok) zp[(long)k * ldz] = z;
+            mx = fmaxf(mx, z);
           }
         }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float mx2 = mx * LOG2E, s2 = scale * LOG2E;
       float sm = 0.f;
       if (mx != -INFINITY) {
 #pragma unroll
-        for (int bm = 0; bm < TM; ++bm)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int m = t.row(bm, r);
-            if (m < t.M) sm += exp2f(acc[bm][bn][r] * scale * LOG2E - mx);
-          }
+          for (int r = 0; r < 4; ++r)
+            if (WHOLE || 16 * i + r < left)
+              sm += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], s2, -mx2));
       }
+      sm += __shfl_xor(sm, 16, 64);
       sm += __shfl_xor(sm, 32, 64);
-      if (t.hh == 0 && nok && slab_row < t.M)
-        stats[(long)(slab_row / 128) * nrows + n] = make_float2(mx, sm);
+      if (t.grp == 0 && nok) stats[(long)(slab_row / 128) * nrows + n] = make_float2(mx2, sm);
+      const int at = (nok ? target[n] : -1) - base;  // the target as a k of the lane
+      const bool mine = at >= 0 && at < min(116, left) && !(at & 12);
+      if (__any(mine)) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (mine && at == 16 * i + r) ztgt[n] = acc[i][j][r] * scale;
+      }
     }
   }
 };
@@ -164,36 +186,52 @@ __global__ void __launch_bounds__(256) k_loss_sum(const float *__restrict__ loss
   if (t == 0) *out = (float)(red[0] * (double)scale);
 }
 
-// dz = g[r] * (onehot(target[r]) - exp(z - lse[r])), from zT [V][ldz] to
-// dz [Rp][Vp] and dzT [Vp][Rp] (bf16, zero in the padding).  64x64 tiles.
-__global__ void __launch_bounds__(256) k_dz(const float *__restrict__ zt, long ldz, int V, int R,
-                                            int Vp, int Rp, const float *__restrict__ lse,
+// dzT = g[r] * (onehot(target[r]) - exp(z - lse[r])) from zT [V][Rp] to bf16
+// [V][Rp], zero in the padded columns.  Bound by HBM (6 bytes an element):
+// a thread keeps lse, g and target of its 8 columns in registers and walks
+// down the vocabulary rows of its block with 16-byte accesses.
+constexpr int DZ_COLS = 256, DZ_ROWS = 64;  // of a block of 256 threads
+
+__global__ void __launch_bounds__(256) k_dz(const float *__restrict__ zt, int V, int R, int Rp,
+                                            const float *__restrict__ lse,
                                             const float *__restrict__ g,
                                             const int32_t *__restrict__ target,
-                                            unsigned short *__restrict__ dz,
                                             unsigned short *__restrict__ dzt) {
-  __shared__ unsigned short t[64][66];
-  const int v0 = blockIdx.y * 64, r0 = blockIdx.x * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int r = r0 + tx;
-  const bool rok = r < R;
-  const float lr = rok ? lse[r] : 0.f, gr = rok ? g[r] : 0.f;
-  const int tg = rok ? target[r] : -1;
-  for (int i = ty; i < 64; i += 4) {
-    const int v = v0 + i;
-    float val = 0.f;
-    if (rok && v < V) {
-      const float p = expf(zt[(long)v * ldz + r] - lr);
-      val = gr * ((v == tg ? 1.f : 0.f) - p);
-    }
-    const unsigned short b = f2bf_bits(val);
-    if (v < Vp && r < Rp) dzt[(long)v * Rp + r] = b;
-    t[i][tx] = b;
+  const int r0 = blockIdx.x * DZ_COLS + (threadIdx.x & 31) * 8;
+  if (r0 >= Rp) return;  // Rp is a multiple of 32
+  float l[8], gr[8];
+  int tg[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const bool ok = r0 + j < R;
+    l[j] = ok ? lse[r0 + j] : 0.f;
+    gr[j] = ok ? g[r0 + j] : 0.f;
+    tg[j] = ok ? target[r0 + j] : -1;
   }
-  __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    const int rr = r0 + i, v = v0 + tx;
-    if (rr < Rp && v < Vp) dz[(long)rr * Vp + v] = t[tx][i];
+  const int v1 = min(V, (int)(blockIdx.y + 1) * DZ_ROWS);
+#pragma unroll 4
+  for (int v = blockIdx.y * DZ_ROWS + (threadIdx.x >> 5); v < v1; v += 8) {
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(zt + (long)v * Rp + r0);
+    const f32x4 a = src[0], b = src[1];
+    u16x8 o;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float z = j < 4 ? a[j] : b[j - 4];
+      const float p = __builtin_amdgcn_exp2f((z - l[j]) * LOG2E);
+      o[j] = r0 + j < R ? f2bf_bits(gr[j] * ((v == tg[j] ? 1.f : 0.f) - p)) : 0;
+    }
+    *reinterpret_cast<u16x8 *>(dzt + (long)v * Rp + r0) = o;
+  }
+}
+
+// out = scale * (part[0] + part[1] + ...) over n elements, in that order
+template <class TO>
+__global__ void __launch_bounds__(256) k_sum_parts(const float *__restrict__ part, int parts, long n,
+                                                   float scale, TO *__restrict__ out) {
+  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256) {
+    float s = 0.f;
+    for (int k = 0; k < parts; ++k) s += part[k * n + i];
+    store_val(out, i, s * scale);
   }
 }
 
@@ -211,14 +249,13 @@ __global__ void k_gather_rows(const TI *__restrict__ x, long ldx, const int32_t 
 }
 
 struct LpWs {
-  size_t hb, wb, zt, stats, ztgt, lse, g, dz, dzt, total;
-  int Rp, Vp, ntiles;
+  size_t hb, wb, zt, stats, ztgt, lse, g, dzt, total;
+  int Rp, ntiles;
 };
 
 LpWs lp_ws(int rows, int hidden, int vocab, seg_dtype dt) {
   LpWs w{};
   w.Rp = (rows + 31) / 32 * 32;
-  w.Vp = (vocab + 31) / 32 * 32;
   w.ntiles = (vocab + 127) / 128;  // 128-row slabs of the logits epilogue
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -226,7 +263,7 @@ LpWs lp_ws(int rows, int hidden, int vocab, seg_dtype dt) {
     off = align_up(off + std::max<size_t>(bytes, 1));
     return o;
   };
-  const size_t Rp = w.Rp, Vp = w.Vp, H = hidden;
+  const size_t Rp = w.Rp, H = hidden;
   w.hb = take(Rp * H * 2);
   w.wb = dt == SEG_F32 ? take((size_t)vocab * H * 2) : 0;
   w.zt = take((size_t)vocab * Rp * 4);
@@ -234,14 +271,31 @@ LpWs lp_ws(int rows, int hidden, int vocab, seg_dtype dt) {
   w.ztgt = take(Rp * 4);
   w.lse = take(Rp * 4);
   w.g = take(Rp * 4);
-  w.dz = take(Rp * Vp * 2);
-  w.dzt = take(Vp * Rp * 2);
+  w.dzt = take((size_t)vocab * Rp * 2);
   w.total = off;
   return w;
 }
 
-dim3 grid2(long cols, long rows, int t = 64) {
-  return dim3((unsigned)((cols + t - 1) / t), (unsigned)((rows + t - 1) / t));
+// Parts to cut dH's contraction over the vocabulary into: its R x H output has
+// few tiles (32 for 1,024 rows of width 2,048), so whole-K tiles would leave
+// most of the chip idle or its last wave nearly empty.  Cost of s parts: the
+// waves of tiles at 1/s of the K range each, plus the fp32 partial sums
+// written and read again (about 4 TB/s against 5.6 TFLOP/s per CU).  Measured,
+// 1,024 rows x 2,048 x vocabulary 32,000: 783 us in one part, 112 us in eight.
+// The partials take the place of zT, which is no longer needed.
+int dh_parts(int rows, int H, int V, int Rp, int *k_part) {
+  const long tiles = gemm::tiles_of(rows, H, 4);
+  const double tile_us = 2.0 * 256 * 256 * V / 5.6e6;
+  int best = 1;
+  double best_us = 0;
+  for (int s = 1; s <= 16; ++s) {
+    if (s > 1 && ((long)s * rows * H > (long)V * Rp || V / s < 1024)) break;
+    const double waves = (double)((tiles * s + gemm::NUM_CU - 1) / gemm::NUM_CU);
+    const double us = waves * (tile_us / s + 4) + (s > 1 ? 8.0 * s * rows * H / 4e6 + 5 : 0);
+    if (s == 1 || us < best_us) best = s, best_us = us;
+  }
+  *k_part = ((V + best - 1) / best + gemm::BK - 1) / gemm::BK * gemm::BK;
+  return (V + *k_part - 1) / *k_part;
 }
 
 template <class TI, class TO>
@@ -251,14 +305,13 @@ void logprob_impl(int rows, int H, int V, const TI *h, const int32_t *row_index,
                   const seg_loss_cfg &cfg, float *logp, float *loss_tok, uint8_t *clipped,
                   float *kl_tok, float *loss_sum, void *dh, float *dw, char *base,
                   const LpWs &L, hipStream_t st) {
-  const int Rp = L.Rp, Vp = L.Vp;
+  const int Rp = L.Rp;
   unsigned short *hb = reinterpret_cast<unsigned short *>(base + L.hb);
   float *zt = reinterpret_cast<float *>(base + L.zt);
   float2 *stats = reinterpret_cast<float2 *>(base + L.stats);
   float *ztgt = reinterpret_cast<float *>(base + L.ztgt);
   float *lse = reinterpret_cast<float *>(base + L.lse);
   float *g = reinterpret_cast<float *>(base + L.g);
-  unsigned short *dz = reinterpret_cast<unsigned short *>(base + L.dz);
   unsigned short *dzt = reinterpret_cast<unsigned short *>(base + L.dzt);
 
   // gathered action rows (bf16)
@@ -287,9 +340,9 @@ void logprob_impl(int rows, int H, int V, const TI *h, const int32_t *row_index,
   {
     EpiLogits e{zt, Rp, stats, rows, target, ztgt, cfg.logit_scale};
     ProfScope prof("logits", st);
-    gemm::k_gemm_big<EpiLogits><<<gemm::big_blocks(V, rows), gemm::BIG_THREADS, 0, st>>>(
-        wb, H, hb, H, V, rows, H, e);
-    SEG_LAUNCH_CHECK();
+    gemm::Problems<EpiLogits, 1, 1> g{{{wb}}, {{hb}}, {{H}}, {{H}}, {H}, {V}, {rows}, {e}, {}, 1,
+                                      0x7fffffff};
+    gemm::launch_tm<false, false, 4>(g, st);
   }
   // 2. per-row loss
   {
@@ -301,27 +354,40 @@ void logprob_impl(int rows, int H, int V, const TI *h, const int32_t *row_index,
   SEG_LAUNCH_CHECK();
   }
   if (!cfg.want_grad) return;
-  // 3. dz in both orientations
+  // 3. dz
   {
-  ProfScope prof("dz", st);
-  k_dz<<<grid2(Rp, Vp), 256, 0, st>>>(zt, Rp, V, rows, Vp, Rp, lse, g, target, dz, dzt);
-  SEG_LAUNCH_CHECK();
+    ProfScope prof("dz", st);
+    k_dz<<<dim3((Rp + DZ_COLS - 1) / DZ_COLS, (V + DZ_ROWS - 1) / DZ_ROWS), 256, 0, st>>>(
+        zt, V, rows, Rp, lse, g, target, dzt);
+    SEG_LAUNCH_CHECK();
   }
-  // 4. dH = s * dz W = s (dz^T)^T W: the transposed-operand GEMM over the
-  //    vocabulary (At = dz^T [V][Rp], Bt = W [V][H]; M = rows, N = H, K = V)
+  // 4. dH = s * dz W: A = dz^T [V][Rp], B = W [V][H], contracting over the
+  //    vocabulary rows of both
   {
-    EpiStore<TO> e{static_cast<TO *>(dh), H, cfg.logit_scale};
     ProfScope prof("dh", st);
-    gemm::gemm_launch_tn(dzt, Rp, wb, H, rows, H, V, e, st);
-    SEG_LAUNCH_CHECK();
+    TO *out = static_cast<TO *>(dh);
+    int k_part = 0;
+    const int parts = dh_parts(rows, H, V, Rp, &k_part);
+    if (parts == 1) {
+      gemm::launch_one<true, true>(dzt, Rp, wb, H, rows, H, V,
+                                   EpiOut<TO, ST>::make(out, H, cfg.logit_scale), st);
+    } else {
+      const long n = (long)rows * H;
+      gemm::Problems<EpiOut<float, ST>, 1, 1> p{
+          {{dzt}}, {{wb}}, {{Rp}}, {{H}}, {V}, {rows}, {H},
+          {EpiOut<float, ST>::make(zt, H, 1.f, nullptr, 0, true, n)}, {}, parts, k_part};
+      gemm::launch_tm<true, true, 4>(p, st);
+      k_sum_parts<TO><<<(int)std::min<long>(8192, (n + 255) / 256), 256, 0, st>>>(
+          zt, parts, n, cfg.logit_scale, out);
+      SEG_LAUNCH_CHECK();
+    }
   }
-  //    dW = s * dz^T h over the rows (At = dz [Rp][Vp], Bt = h [Rp][H];
-  //    M = V, N = H, K = rows)
+  //    dW = s * dz^T h: A = dz^T along its rows (zero in the padded columns),
+  //    B = h [Rp][H] (zero in the padded rows)
   {
-    EpiStore<float> e{dw, H, cfg.logit_scale};
     ProfScope prof("dw", st);
-    gemm::gemm_launch_tn(dz, Vp, hb, H, V, H, rows, e, st);
-    SEG_LAUNCH_CHECK();
+    gemm::launch_one<false, true>(dzt, Rp, hb, H, V, H, Rp,
+                                  EpiOut<float, ST>::make(dw, H, cfg.logit_scale), st);
   }
 }
 

@@ -268,3 +268,41 @@ def test_no_loss_rows():
     torch.cuda.synchronize()
     assert float(out["loss_sum"][0]) == 0.0
     assert torch.count_nonzero(out["dw"]).item() == 0
+
+
+# rows, hidden and vocabulary at the edges of the products' 256 x 256 and
+# 128 x 256 tiles, 64-wide steps and 8-element chunks; the last four cut dH's
+# contraction over the vocabulary into parts (few output tiles, a long K)
+GEMM_EDGES = [(1, 8, 1), (31, 8, 127), (33, 24, 129), (127, 56, 256), (128, 64, 255), (129, 72, 384),
+              (255, 248, 257), (257, 264, 513), (64, 328, 2049), (40, 520, 16401), (300, 256, 12288),
+              (257, 136, 9001)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("R,H,V", GEMM_EDGES)
+def test_gemm_edges(R, H, V, dtype):
+    import torch
+    rng = np.random.default_rng([R, H, V])
+    cfg = WL.TINY.with_(dtype="bf16")
+    h, w = (as_model_dtype(WL.bf16_bits_to_f64(WL.bf16_round_np(x.astype(np.float32))), cfg)
+            for x in (rng.standard_normal((R, H)), 0.3 * rng.standard_normal((V, H))))
+    tgt = rng.integers(0, V, R).astype(np.int32)
+    adv = rng.standard_normal(3).astype(np.float32)
+    traj = rng.integers(0, 3, R).astype(np.int32)
+    cur, _, _ = OLS.logprob(h, w, tgt)
+    old = (cur + 0.05 * rng.standard_normal(R)).astype(np.float32)
+    ref = OLS.loss_and_grads(h, w, tgt, old.astype(np.float64), adv[traj].astype(np.float64), 0.5, 0.5,
+                             loss_scale=1.0, dual_clip_c=0.0, want_grad=True, ref_logp=None, kl_coef=0.0)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    t = [torch.from_numpy(x).to("cuda") for x in (tgt, old, adv, traj)]
+    out = S.seg_logprob_loss(torch.from_numpy(h).to("cuda").to(dt), None,
+                             torch.from_numpy(w).to("cuda").to(dt), *t, S.LossCfg(0.5, 0.5))
+    torch.cuda.synchronize()
+    # fp32 sums of H exact products of values below 16: 1e-5 of the largest
+    lp = out["logp"].cpu().numpy()
+    assert np.abs(lp - ref["logp"]).max() < 1e-5 * max(1.0, np.abs(ref["logp"]).max())
+    # one bf16 rounding (2^-9) of each dz (and of dH on output): the errors of a
+    # sum are independent, so its relative error stays below 2^-8
+    for n in ("dh", "dw"):
+        if np.linalg.norm(ref[n]) > 1e-6:
+            assert rel(out[n].float().cpu().numpy(), ref[n]) < 2.0 ** -8, n
