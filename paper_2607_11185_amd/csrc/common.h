@@ -92,7 +92,6 @@ struct Carver {
 // ---------------------------------------------------------------- device
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
@@ -128,17 +127,8 @@ __device__ __forceinline__ void store_val<float>(float *p, long i, float v) {
   p[i] = v;
 }
 
-__device__ __forceinline__ f32x16 mfma32(const bf16x8 &a, const bf16x8 &b, const f32x16 &c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-// Position p (0..15) inside a 16-element chunk of a transposed tile holds the
-// element of offset kperm(p) of that chunk.  It matches the order in which the
-// 32x32 MFMA accumulator of a lane holds its rows: lane half h, register j of a
-// 16-row chunk holds row 8*(j/4) + 4*h + j%4, and an operand lane half h reads
-// positions 8h..8h+7.  The map is an involution (it swaps 4..7 with 8..11).
-__host__ __device__ __forceinline__ int kperm(int p) {
-  return (p & ~12) | ((p & 4) << 1) | ((p & 8) >> 1);
+__device__ __forceinline__ f32x4 mfma16(const bf16x8 &a, const bf16x8 &b, const f32x4 &c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
 // dst[i] = value for i < n 32-bit words.  Compute entry points clear their

@@ -30,10 +30,6 @@ struct Tile {
   char *lds;
 };
 
-__device__ __forceinline__ f32x4 mfma16(const bf16x8 &a, const bf16x8 &b, const f32x4 &c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
 __device__ __forceinline__ unsigned pack2(float a, float b) {
   return (unsigned)f2bf_bits(a) | ((unsigned)f2bf_bits(b) << 16);
 }

@@ -7,12 +7,17 @@
 // q-tile, the k-tiles that hold at least one visible pair (CSR) and marks them
 // FULL (every pair visible: no predicate) or PARTIAL (per-element predicate).
 //
-// MFMA v_mfma_f32_32x32x16_bf16 lane layout used throughout (lane l, c = l%32,
-// h = l/32):  A[i][k]: i = c, k = 8h + 0..7;  B[k][j]: j = c, k = 8h + 0..7;
-// D[i][j] (16 regs r): j = c, i = 8*(r/4) + 4h + r%4.
-// Products that contract over the rows held in accumulator registers take
-// their other operand from LDS through transpose reads in the same row order
-// (kperm() in common.h).
+// MFMA v_mfma_f32_16x16x32_bf16 lane layout used throughout (lane l, c = l%16,
+// g = l/16):  A[i][k]: i = c, k = 8g + 0..7;  B[k][j]: j = c, k = 8g + 0..7;
+// D[i][j] (4 regs r): j = c, i = 4g + r.
+// This shape moves half the accumulator bits of 32x32x16 products: on the
+// benchmark batch the clock under load rose from 1.82 / 1.81 / 1.97 to 2.03 /
+// 2.02 / 2.21 GHz (forward, dQ, dK/dV) and the kernels took 132.5 -> 128.5,
+// 179.2 -> 168.5 and 265.5 -> 257.0 ms.
+// Products that contract over 32 rows held in the accumulators of two 16-row
+// blocks take rows {4g..4g+3, 16+4g..16+4g+3} as a lane's eight k (any order
+// serves as long as both operands use it); their other operand comes from LDS
+// through transpose reads in the same row order.
 #include <climits>
 #include <cmath>
 #include <mutex>
@@ -65,11 +70,25 @@ __device__ __forceinline__ bf16x8 lds8(const unsigned short *p) {
   return *reinterpret_cast<const bf16x8 *>(p);
 }
 
-__device__ __forceinline__ bf16x8 pack8(const f32x16 &v, int base) {
+// a lane's rows of two 16-row accumulator blocks as one operand fragment
+__device__ __forceinline__ bf16x8 pack8(const f32x4 &lo, const f32x4 &hi) {
   bf16x8 r;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) r[j] = (__bf16)v[base + j];
+  for (int j = 0; j < 4; ++j) {
+    r[j] = (__bf16)lo[j];
+    r[4 + j] = (__bf16)hi[j];
+  }
   return r;
+}
+
+// a row's value summed or maximised over the four lanes that share it
+__device__ __forceinline__ float row_sum(float x) {
+  x += __shfl_xor(x, 16, 64);
+  return x + __shfl_xor(x, 32, 64);
+}
+__device__ __forceinline__ float row_max(float x) {
+  x = fmaxf(x, __shfl_xor(x, 16, 64));
+  return fmaxf(x, __shfl_xor(x, 32, 64));
 }
 
 __device__ __forceinline__ u16x8 load8_bf(const unsigned short *p) {
@@ -166,35 +185,55 @@ __global__ void __launch_bounds__(256) k_key_norm(const unsigned short *__restri
               __float_as_uint(fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]))));
 }
 
+// Order of a block of products whose operand fragments come from LDS: `ahead`
+// reads first, then PROD products and READ reads in turn, so that a product
+// finds its fragments read `ahead` reads before.  The compiler alone issues a
+// read one or two products ahead and waits on it.
+template <int READS, int AHEAD, int PROD, int READ>
+__device__ __forceinline__ void read_ahead() {
+  static_assert(AHEAD <= READS && AHEAD % READ == 0 && READS % READ == 0, "whole groups");
+  __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);  // LDS reads
+#pragma unroll
+  for (int i = 0; i < (READS - AHEAD) / READ; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, PROD, 0);  // products
+    __builtin_amdgcn_sched_group_barrier(0x100, READ, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, AHEAD / READ * PROD, 0);
+}
+
 // ------------------------------------------------------------- pipelined kernels
 //
 // Tiles of 64 rows x d (row-major, bf16) are multi-buffered in LDS: the
 // loads of the next unit are in flight while the current one is computed.
-// Every kernel fills them with direct 16-byte buffer->LDS loads (see the
-// note on wait counts below).  All tile loads go through buffer resources
-// that start at the segment's first row, so a lane's offset inside a tile is
+// Every kernel fills them with direct 16-byte buffer->LDS loads.  All tile
+// loads go through buffer resources that start at the segment's first row, so a lane's offset inside a tile is
 // fixed for the kernel and a unit adds one scalar; rows past the segment read
 // as zeros.  Rows are stored with a 16-byte-chunk swizzle that keeps both
 // 16-byte row reads (MFMA operands contracting over d; 16 lanes per LDS
-// cycle) and 4x16 transpose reads (ds_read_b64_tr_b16: operands contracting
-// over the rows; 32 lanes per cycle) free of bank conflicts on 64 four-byte
-// banks, so no transposed copy of any tensor is needed.  Every lane's swizzled offsets are computed once;
-// inside the loops a read is a register offset plus an immediate.
+// cycle) and transpose reads (ds_read_b64_tr_b16: operands contracting over
+// the rows; 32 lanes per cycle) free of bank conflicts on 64 four-byte banks,
+// so no transposed copy of any tensor is needed.  Every lane's swizzled
+// offsets are computed once; inside the loops a read is a register offset plus an immediate.
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-// 16-byte chunk swizzle of row `row`: a bijection on row % 16 (a 16-lane row
-// read of one logical chunk hits 16 distinct chunks), and rows 4m..4m+3 differ
-// in bits 2-3 (a 32-lane transpose read of 4 rows x 4 chunks hits 16 distinct
-// chunks).  For d = 64 two rows share one 256-byte bank line, so the same two
-// properties are built from row / 2.
+// 16-byte chunk swizzle of row `row`.  Two properties make both kinds of read
+// conflict-free.  Rows 8m..8m+7 differ in bits 1-3: a 32-lane transpose read
+// of 8 rows x 2 chunks hits 16 distinct chunks.  And a 16-byte read, which
+// takes 16 lanes at a time as {0-3, 12-15, 20-27} and the rest (rows 0-3 and
+// 12-15 of one chunk with rows 4-11 of the next), hits 16 distinct chunks:
+// rows of equal bits 1-3 (r and 8 + (r ^ 4)) fall on the same side of that
+// split and differ in bit 0.  (With the plain rotation (row & 7) << 1 | row >>
+// 3 half of a row read conflicts: dQ 175 against 169 ms on the benchmark batch.)  For d = 64 two rows
+// share one 256-byte bank line, so the same properties are built from row / 2.
 template <int D>
 __device__ __forceinline__ int swz(int row) {
-  if constexpr (D == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
-  else return (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+  constexpr int H = D == 128 ? 8 : 4;  // rows, or row pairs, of half a pattern
+  const int r = (D == 128 ? row : row >> 1) & (2 * H - 1), hi = r / H;
+  return (((r & (H - 1)) ^ (hi * (H / 2))) << 1) | hi;
 }
 
 // element offset of (row, col) in a swizzled row-major tile of d columns
@@ -207,21 +246,16 @@ __device__ __forceinline__ int toff(int row, int col) {
 // a multiple of 16 (the swizzle depends on row % 16 only).
 template <int D>
 struct LaneOffsets {
-  static constexpr int KK = D / 16, DB = D / 32;
-  int row[KK];     // 16-byte read of row R + lane%32, chunk 2*kk + lane/32
-  int tra[DB];     // transpose reads: rows R + 4h + (lane%16)/4 (+8 for trb),
-  int trb[DB];     // columns nb0 + 32*db + 16*((lane/16)%2) + 4*(lane%4)
-  __device__ __forceinline__ void init(int lane, int nb0) {
-    const int col = lane & 31, hh = lane >> 5, l16 = lane & 15, g = lane >> 4;
+  static constexpr int KK = D / 32, DB = D / 16;
+  int row[KK];  // 16-byte read of row R + lane%16, chunk 4*kk + lane/16
+  int tr[DB];   // transpose reads: rows R + 4g + (lane%16)/4 (and 16 below), columns
+                // 16*db + 4*(lane%4)
+  __device__ __forceinline__ void init(int lane) {
+    const int c = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) row[kk] = toff<D>(col, (kk * 2 + hh) * 8) * 2;
-    const int r = 4 * hh + (l16 >> 2);
+    for (int kk = 0; kk < KK; ++kk) row[kk] = toff<D>(c, (kk * 4 + g) * 8) * 2;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const int c = nb0 + db * 32 + 16 * (g & 1) + 4 * (l16 & 3);
-      tra[db] = toff<D>(r, c) * 2;
-      trb[db] = toff<D>(r + 8, c) * 2;
-    }
+    for (int db = 0; db < DB; ++db) tr[db] = toff<D>(4 * g + (c >> 2), db * 16 + 4 * (c & 3)) * 2;
   }
 };
 
@@ -230,17 +264,16 @@ __device__ __forceinline__ bf16x8 frag_row(const char *tile, int R, int off) {
   return *reinterpret_cast<const bf16x8 *>(tile + R * D * 2 + off);
 }
 
-// Operand fragment contracting over tile rows: lane l receives column
-// n(l) of rows R + kperm(8h + j), j = 0..7 (h = l/32), the MFMA k-order of
+// Operand fragment contracting over tile rows: lane l receives column c(l) of
+// rows R + 4g + 0..3 and R + 16 + 4g + 0..3 (g = l/16), the k order of
 // accumulator-held operands.
-// `bias` is a constant already added to offa and offb (see the dK/dV kernel).
+// `bias` is a constant already added to off (see the dK/dV kernel).
 template <int D>
-__device__ __forceinline__ bf16x8 frag_tr(const char *tile, int R, int offa, int offb,
-                                          int bias = 0) {
+__device__ __forceinline__ bf16x8 frag_tr(const char *tile, int R, int off, int bias = 0) {
   const v4i16 a =
-      __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(tile + (R * D * 2 - bias + offa)));
+      __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(tile + (R * D * 2 - bias + off)));
   const v4i16 b =
-      __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(tile + (R * D * 2 - bias + offb)));
+      __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(tile + ((R + 16) * D * 2 - bias + off)));
   const bf16x4 a4 = __builtin_bit_cast(bf16x4, a), b4 = __builtin_bit_cast(bf16x4, b);
   bf16x8 r;
   r[0] = a4[0]; r[1] = a4[1]; r[2] = a4[2]; r[3] = a4[3];
@@ -248,11 +281,55 @@ __device__ __forceinline__ bf16x8 frag_tr(const char *tile, int R, int offa, int
   return r;
 }
 
+// four consecutive output values (as a whole where `vec`: the tensor starts
+// on an 8-byte, for fp32 a 16-byte boundary)
+__device__ __forceinline__ void store4(unsigned short *p, const f32x4 &v, bool vec) {
+  const u16x4 b = {f2bf_bits(v[0]), f2bf_bits(v[1]), f2bf_bits(v[2]), f2bf_bits(v[3])};
+  if (vec) *reinterpret_cast<u16x4 *>(p) = b;
+  else
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p[j] = b[j];
+}
+__device__ __forceinline__ void store4(float *p, const f32x4 &v, bool vec) {
+  if (vec) *reinterpret_cast<f32x4 *>(p) = v;
+  else
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p[j] = v[j];
+}
+template <class T>
+__device__ __forceinline__ bool aligned4(const T *p) {
+  return (reinterpret_cast<uintptr_t>(p) & (4 * sizeof(T) - 1)) == 0;
+}
+
 // Raw buffer resource over [base, base + bytes): loads past the end return
 // zeros, so a tile fill needs no clamping of its rows.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes,
-                                           0x00020000);
+__device__ __forceinline__ i32x4 make_rsrc(const void *base, unsigned bytes) {
+  const unsigned long p = (unsigned long)base;
+  return i32x4{(int)(unsigned)p, (int)((unsigned)(p >> 32) & 0xffffu), (int)bytes, 0x00020000};
+}
+
+__device__ __forceinline__ unsigned lds_addr(const void *p) {
+  return (unsigned)(unsigned long)(__attribute__((address_space(3))) const char *)p;
+}
+
+// Direct loads of 64 lanes x 16 (or 4) bytes from rs (byte offset voff per lane
+// plus the scalar soff) to LDS at byte address dst.  Written as instructions:
+// with the builtin the compiler makes every LDS wait drain the LDS queue while
+// such a load is in flight.  They have no register result; the end of a step
+// waits for them (wait_loads_and_sync).  No memory clobber: LDS is only read
+// again behind that barrier, and a clobber would turn the scalar loads of the
+// walking order into vector loads, whose waits drain these loads.
+__device__ __forceinline__ void dma16(unsigned dst, int voff, i32x4 rs, int soff) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(dst), "v"(voff), "s"(rs), "s"(soff));
+#endif
+}
+__device__ __forceinline__ void dma4(unsigned dst, int voff, i32x4 rs, int soff) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+               :: "s"(dst), "v"(voff), "s"(rs), "s"(soff));
+#endif
 }
 
 // Direct buffer->LDS fill of a 64-row tile by NW waves: per-lane byte offsets
@@ -270,40 +347,25 @@ struct BufFill {
       voff[i] = row * row_bytes + ((s % CPR) ^ swz<D>(row)) * 16;
     }
   }
-  __device__ __forceinline__ void issue(unsigned short *tile, __amdgpu_buffer_rsrc_t rs, int soff,
-                                        int wave) const {
-#if defined(__HIP_DEVICE_COMPILE__)
+  __device__ __forceinline__ void issue(unsigned short *tile, i32x4 rs, int soff, int wave) const {
 #pragma unroll
-    for (int i = 0; i < PW; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rs, (__attribute__((address_space(3))) void *)(tile + (wave * PW + i) * 64 * 8), 16,
-          voff[i], soff, 0, 0);
-#endif
+    for (int i = 0; i < PW; ++i) dma16(lds_addr(tile) + (wave * PW + i) * 1024, voff[i], rs, soff);
   }
 };
 
 // one dword per lane (lane l: byte l*4 + soff) into 64 consecutive dwords of LDS
-__device__ __forceinline__ void buf64_dw(void *dst, __amdgpu_buffer_rsrc_t rs, int lane, int soff) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)dst, 4,
-                                           lane * 4, soff, 0, 0);
-#endif
+__device__ __forceinline__ void buf64_dw(void *dst, i32x4 rs, int lane, int soff) {
+  dma4(lds_addr(dst), lane * 4, rs, soff);
 }
 
-// Software pipelining over units.  The loads of unit n+1 are issued, then
-// unit n is computed from the other buffer, then a barrier ends the step.
-// With direct loads, both happen inside one always-inline step whose LDS
-// buffers are distinct __restrict__ parameters: a direct load's LDS write is
-// counted with the global loads, and without the no-alias facts the compiler
-// would wait for the loads in flight before the first LDS read of the
-// compute.  Every LDS access of a step goes through those parameters (an
-// access without them, such as one indexed by a run-time buffer number, waits
-// for every direct load in flight).  While a direct load is in flight the
-// compiler also gives up counted LDS waits (every wait becomes lgkmcnt(0)),
-// which serialises read-ahead.
+// Software pipelining over units.  The loads of unit n+1 are issued, then unit
+// n is computed from the other buffer, then a barrier behind the loads ends the
+// step.  Both happen inside one always-inline step whose LDS buffers are
+// distinct __restrict__ parameters.
 
-__device__ __forceinline__ void wait_all_and_sync() {
-  __builtin_amdgcn_s_waitcnt(0);
+// the direct loads in flight have landed, for every wave
+__device__ __forceinline__ void wait_loads_and_sync() {
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
   __syncthreads();
 }
 
@@ -414,25 +476,26 @@ __device__ __forceinline__ void walk_units(Unit u, const Step &step, const Issue
                                            unsigned short *__restrict__ v1, int *__restrict__ m1) {
   Unit nu;
   issue(u, k0, v0, m0);
-  wait_all_and_sync();
+  wait_loads_and_sync();
   for (;;) {
     bool more = next(u, nu);
     step(u, more, nu, k0, v0, m0, k1, v1, m1);
-    __syncthreads();
+    wait_loads_and_sync();
     if (!more) return;
     u = nu;
     more = next(u, nu);
     step(u, more, nu, k1, v1, m1, k0, v0, m0);
-    __syncthreads();
+    wait_loads_and_sync();
     if (!more) return;
     u = nu;
   }
 }
 
 // Forward: one block = one q-tile x one query head, 4 waves of 32 query rows;
-// units are 64-key halves of the listed k-tiles.  S^T = K Q^T keeps one query
-// per lane, so the online softmax is in-lane (plus one exchange with the
-// other half-wave); O^T += V^T P^T with V^T by transpose reads.
+// units are 64-key halves of the listed k-tiles.  S^T = K Q^T keeps a lane on
+// two queries (rows c and 16 + c of the wave), so the online softmax is
+// in-lane (plus two exchanges between the lanes of a row); O^T += V^T P^T with
+// V^T by transpose reads.
 template <int D, class TO>
 __global__ void __launch_bounds__(256, 2) k_attn_fwd(
     const unsigned short *__restrict__ q, const unsigned short *__restrict__ k,
@@ -441,7 +504,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd(
     const int32_t *__restrict__ qt_ptr, const int32_t *__restrict__ qt_ord,
     const float *__restrict__ kn2, const XcdRanges xr, int hq, int hkv, int W, float scale_log2,
     long P, TO *__restrict__ o, float *__restrict__ lse) {
-  constexpr int KK = D / 16, DB = D / 32, T64 = 64 * D;
+  constexpr int KK = D / 32, DB = D / 16, T64 = 64 * D;
   __shared__ __attribute__((aligned(16))) unsigned short sK0[T64], sK1[T64], sV0[T64], sV1[T64];
   __shared__ __attribute__((aligned(16))) int sM0[64], sM1[64];
 
@@ -450,17 +513,19 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd(
   const int hk = h / (hq / hkv);
   const TileRows tr = tile_rows(seg_info, tile_seg, g);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int col = lane & 31, hh = lane >> 5;
-  const int qloc = wave * 32 + col;
-  const bool qvalid = qloc < tr.nrows;
-  const int qr = tr.row0 + (qvalid ? qloc : 0);
-  const int qstep = tok_meta[tr.start + qr] >> 2;
-
-  bf16x8 qf[KK];
-  {
-    const unsigned short *qrow = q + ((long)(tr.start + qr) * hq + h) * D;
+  const int col = lane & 15, grp = lane >> 4;
+  bool qvalid[2];
+  int qr[2], qstep[2];
+  bf16x8 qf[2][KK];
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[kk] = lds8(qrow + kk * 16 + hh * 8);
+  for (int qb = 0; qb < 2; ++qb) {
+    const int qloc = wave * 32 + qb * 16 + col;
+    qvalid[qb] = qloc < tr.nrows;
+    qr[qb] = tr.row0 + (qvalid[qb] ? qloc : 0);
+    qstep[qb] = tok_meta[tr.start + qr[qb]] >> 2;
+    const unsigned short *qrow = q + ((long)(tr.start + qr[qb]) * hq + h) * D;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) qf[qb][kk] = lds8(qrow + kk * 32 + grp * 8);
   }
   // Fixed offset: when |q| max|k| * scale * log2(e) <= 64 for every row of
   // the wave (max over the segment's keys), every score in log2 units lies
@@ -469,120 +534,143 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd(
   // the offset).  Other waves keep the lazily rescaled running max.
   bool zoff;
   {
-    float qn2 = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) qn2 = fmaf((float)qf[kk][j], (float)qf[kk][j], qn2);
-    qn2 += __shfl_xor(qn2, 32, 64);
     const float kmax2 = kn2[(long)tile_seg[g] * hkv + hk];
-    zoff = __all(!qvalid || qn2 * kmax2 * (scale_log2 * scale_log2) <= 4096.f);
-  }
-  f32x16 oacc[DB];
+    bool small = true;
 #pragma unroll
-  for (int db = 0; db < DB; ++db) oacc[db] = f32x16{};
-  float m_run = zoff ? 0.f : -INFINITY, l_run = 0.f;
+    for (int qb = 0; qb < 2; ++qb) {
+      float qn2 = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) qn2 = fmaf((float)qf[qb][kk][j], (float)qf[qb][kk][j], qn2);
+      qn2 = row_sum(qn2);
+      small = small && (!qvalid[qb] || qn2 * kmax2 * (scale_log2 * scale_log2) <= 4096.f);
+    }
+    zoff = __all(small);
+  }
+  f32x4 oacc[DB][2];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) oacc[db][qb] = f32x4{};
+  float m_run[2], l_run[2];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    m_run[qb] = zoff ? 0.f : -INFINITY;
+    l_run[qb] = 0.f;
+  }
 
   LaneOffsets<D> lo;
-  lo.init(lane, 0);
+  lo.init(lane);
   const long kv_stride = (long)hkv * D;
   const int row_bytes = (int)(kv_stride * 2);
   BufFill<D, 4> fp;
   fp.init(wave, lane, row_bytes);
   // the segment's rows of this kv head; rows past the segment read as zeros
-  const __amdgpu_buffer_rsrc_t rK =
+  const i32x4 rK =
       make_rsrc(k + (long)hk * D + (long)tr.start * kv_stride, (unsigned)tr.len * row_bytes);
-  const __amdgpu_buffer_rsrc_t rV =
+  const i32x4 rV =
       make_rsrc(v + (long)hk * D + (long)tr.start * kv_stride, (unsigned)tr.len * row_bytes);
-  const __amdgpu_buffer_rsrc_t rM = make_rsrc(tok_meta + tr.start, (unsigned)tr.len * 4);
+  const i32x4 rM = make_rsrc(tok_meta + tr.start, (unsigned)tr.len * 4);
 
+  const int swave = __builtin_amdgcn_readfirstlane(wave);  // LDS addresses in scalar registers
   auto issue = [&](const Unit &u, unsigned short *__restrict__ nK, unsigned short *__restrict__ nV,
                    int *__restrict__ nM) __attribute__((always_inline)) {
-    fp.issue(nK, rK, u.r0 * row_bytes, wave);
-    fp.issue(nV, rV, u.r0 * row_bytes, wave);
-    if (wave == 0) buf64_dw(nM, rM, lane, u.r0 * 4);
+    fp.issue(nK, rK, u.r0 * row_bytes, swave);
+    fp.issue(nV, rV, u.r0 * row_bytes, swave);
+    if (swave == 0) buf64_dw(nM, rM, lane, u.r0 * 4);
   };
   auto compute = [&](const Unit &u, const char *__restrict__ sK, const char *__restrict__ sV,
                      const int *__restrict__ sM) __attribute__((always_inline)) {
-    f32x16 sacc[2];
+    f32x4 sacc[4][2];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int kb = 0; kb < 4; ++kb) {
       bf16x8 ak[KK];
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) ak[kk] = frag_row<D>(sK, kb * 32, lo.row[kk]);
-      sacc[kb] = f32x16{};
+      for (int kk = 0; kk < KK; ++kk) ak[kk] = frag_row<D>(sK, kb * 16, lo.row[kk]);
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) sacc[kb] = mfma32(ak[kk], qf[kk], sacc[kb]);
+      for (int qb = 0; qb < 2; ++qb) sacc[kb][qb] = f32x4{};
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) sacc[kb][qb] = mfma16(ak[kk], qf[qb][kk], sacc[kb][qb]);
     }
-    // raw scores; masked entries -inf (scale > 0 keeps the order).  The
-    // forward keeps the direct per-element test: with the cheaper form of
-    // the backward kernels the compiler schedules the unmasked path of this
-    // kernel less well (the forward ran 1% slower in measurement).
+    // 128.0 -> 125.0 ms on the benchmark batch (4 and 6 ahead: 125.5, 125.2)
+    read_ahead<4 * KK, 8, 2, 1>();
+    // raw scores; masked entries -inf (scale > 0 keeps the order)
     if (__builtin_expect(u.partial, 0)) {
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < 4; ++kb) {
+        const int kb0 = kb * 16 + 4 * grp;
+        const i32x4 M4 = *reinterpret_cast<const i32x4 *>(sM + kb0);
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int kb0 = kb * 32 + 8 * rg + 4 * hh;
-          const i32x4 M4 = *reinterpret_cast<const i32x4 *>(sM + kb0);
+        for (int j = 0; j < 4; ++j) {
+          // bitwise, not short-circuit: no branch per element
+          const int key = kb0 + j, ex = key_expiry(M4[j], W);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            // bitwise, not short-circuit: no branch per element
-            const int key = kb0 + j;
-            const bool vis = qvalid & (key < u.vrows) & (u.r0 + key <= qr) &
-                             (qstep < key_expiry(M4[j], W));
-            sacc[kb][rg * 4 + j] = vis ? sacc[kb][rg * 4 + j] : -INFINITY;
+          for (int qb = 0; qb < 2; ++qb) {
+            const bool vis = qvalid[qb] & (key < u.vrows) & (u.r0 + key <= qr[qb]) & (qstep[qb] < ex);
+            sacc[kb][qb][j] = vis ? sacc[kb][qb][j] : -INFINITY;
           }
         }
-    }
-    if (!zoff) {
-      float mloc = -INFINITY;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, sacc[kb][r]);
-      mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64)) * scale_log2;
-      // Lazy rescaling: the running max (log2 units) only moves when a row's
-      // tile max exceeds it by more than 8, so unnormalised P stays below 2^8.
-      const bool grow = mloc > m_run + 8.f;
-      if (__any(grow)) {
-        // lanes that keep their max keep alpha = 1: with an unset (-inf)
-        // max, exp2(m_run - m_new) would be exp2(NaN)
-        const float m_new = grow ? mloc : m_run;
-        const float alpha = grow ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
-        l_run *= alpha;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) oacc[db] *= alpha;
-        m_run = m_new;
       }
     }
-    const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
-    bf16x8 pf[2][2];
-    float rsum = 0.f;
+    if (!zoff) {
+      float mloc[2];
+      bool grow[2];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+      for (int qb = 0; qb < 2; ++qb) {
+        mloc[qb] = -INFINITY;
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        sacc[kb][r] = __builtin_amdgcn_exp2f(fmaf(sacc[kb][r], scale_log2, -m_use));
-      pf[kb][0] = pack8(sacc[kb], 0);
-      pf[kb][1] = pack8(sacc[kb], 8);
-      rsum = sum8(pf[kb][0], rsum);
-      rsum = sum8(pf[kb][1], rsum);
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mloc[qb] = fmaxf(mloc[qb], sacc[kb][qb][r]);
+        mloc[qb] = row_max(mloc[qb]) * scale_log2;
+        // Lazy rescaling: the running max (log2 units) only moves when a row's
+        // tile max exceeds it by more than 8, so unnormalised P stays below 2^8.
+        grow[qb] = mloc[qb] > m_run[qb] + 8.f;
+      }
+      if (__any(grow[0] | grow[1])) {
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+          // lanes that keep their max keep alpha = 1: with an unset (-inf)
+          // max, exp2(m_run - m_new) would be exp2(NaN)
+          const float m_new = grow[qb] ? mloc[qb] : m_run[qb];
+          const float alpha = grow[qb] ? __builtin_amdgcn_exp2f(m_run[qb] - m_new) : 1.f;
+          l_run[qb] *= alpha;
+#pragma unroll
+          for (int db = 0; db < DB; ++db) oacc[db][qb] *= alpha;
+          m_run[qb] = m_new;
+        }
+      }
     }
-    // l_run holds the sum over this lane's keys only: both half-waves of a
-    // row share its max and rescale factors, so their sums are combined once
-    // at the end
-    l_run += rsum;
+    bf16x8 pf[2][2];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int qb = 0; qb < 2; ++qb) {
+      const float m_use = (m_run[qb] == -INFINITY) ? 0.f : m_run[qb];
+      float rsum = 0.f;
 #pragma unroll
-      for (int c2 = 0; c2 < 2; ++c2) {
-        bf16x8 av[DB];
+      for (int p = 0; p < 2; ++p) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-          av[db] = frag_tr<D>(sV, kb * 32 + c2 * 16, lo.tra[db], lo.trb[db]);
+        for (int kb = 2 * p; kb < 2 * p + 2; ++kb)
 #pragma unroll
-        for (int db = 0; db < DB; ++db) oacc[db] = mfma32(av[db], pf[kb][c2], oacc[db]);
+          for (int r = 0; r < 4; ++r)
+            sacc[kb][qb][r] = __builtin_amdgcn_exp2f(fmaf(sacc[kb][qb][r], scale_log2, -m_use));
+        pf[p][qb] = pack8(sacc[2 * p][qb], sacc[2 * p + 1][qb]);
+        rsum = sum8(pf[p][qb], rsum);
+      }
+      // l_run holds the sum over this lane's keys only: the four lanes of a
+      // row share its max and rescale factors, so their sums are combined
+      // once at the end
+      l_run[qb] += rsum;
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const bf16x8 av = frag_tr<D>(sV, p * 32, lo.tr[db]);
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) oacc[db][qb] = mfma16(av, pf[p][qb], oacc[db][qb]);
       }
   };
   auto step = [&](const Unit &u, const bool more, const Unit &nu,
@@ -601,20 +689,17 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd(
   walk_units(make_unit(qt_ord, e0, 0, tr.qbase, tr.len), step, issue, next, sK0, sV0, sM0,
              sK1, sV1, sM1);
 
-  l_run += __shfl_xor(l_run, 32, 64);
-  if (qvalid) {
-    const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
-    const long row = tr.start + qr;
+  const bool vec = aligned4(o);
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const float l = row_sum(l_run[qb]);
+    if (!qvalid[qb]) continue;
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    const long row = tr.start + qr[qb];
     TO *orow = o + (row * hq + h) * D;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const int d0 = db * 32 + 8 * r4 + 4 * hh;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) store_val(orow, d0 + j, oacc[db][r4 * 4 + j] * inv);
-      }
-    if (hh == 0) lse[(long)h * P + row] = (m_run + log2f(l_run)) * LN2;
+    for (int db = 0; db < DB; ++db) store4(orow + db * 16 + 4 * grp, oacc[db][qb] * inv, vec);
+    if (grp == 0) lse[(long)h * P + row] = (m_run[qb] + log2f(l)) * LN2;
   }
 }
 
@@ -642,11 +727,9 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     const int32_t *__restrict__ kt_ord, const XcdRanges xr,
     int hq, int hkv, int W,
     float scale_log2, float scale, long P, TO *__restrict__ dk, TO *__restrict__ dv) {
-  constexpr int KK = D / 16, T64 = 64 * D, DB = D / 32, NB = 3;
-  // three Q/dO buffers (and their per-row values) as distinct objects, so
-  // that the direct loads into one provably write other LDS than the reads
-  // of the other two
-  // Q/dO tiles first (LDS is laid out by decreasing alignment), buffers 0
+  constexpr int KK = D / 32, T64 = 64 * D, DB = D / 16, NB = 3;
+  // three Q/dO buffers (and their per-row values) as distinct objects: Q/dO
+  // tiles first (LDS is laid out by decreasing alignment), buffers 0
   // and 1 in the low 64 KB and buffer 2 above it
   __shared__ __attribute__((aligned(1024))) unsigned short sQ0[T64], sQ1[T64], sD0[T64], sD1[T64];
   __shared__ __attribute__((aligned(512))) unsigned short sQ2[T64], sD2[T64];
@@ -673,29 +756,33 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
   const TileRows tr = tile_rows(seg_info, tile_seg, g);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int side = wave >> 2, kg = wave & 3;  // side 0: P, dV; side 1: dS, dK
-  const int col = lane & 31, hh = lane >> 5;
-  const int kloc = kg * 32 + col;
-  const bool kvalid = kloc < tr.nrows;
-  const int kr = tr.row0 + (kvalid ? kloc : 0);
-  // a query row sees the lane's key only if its turn/kind word is below
-  // kexp4 = 4 x (the key's expiry turn), INT_MAX for keys that never expire
-  const int kexp = key_expiry(tok_meta[tr.start + kr], W);
-  const int kexp4 = kexp >= (1 << 29) ? INT_MAX : kexp << 2;
-
-  // K fragments (P side) or V fragments (dS side) of the wave's 32 keys
-  bf16x8 xf[KK];
-  {
-    const long row = tr.start + kr;
+  const int col = lane & 15, grp4 = lane >> 4;
+  // the lane's two keys, c and 16 + c of the wave's 32.  A query row sees a
+  // key only if its turn/kind word is below kexp4 = 4 x (the key's expiry
+  // turn), INT_MAX for keys that never expire
+  bool kvalid[2];
+  int kr[2], kexp4[2];
+  bf16x8 xf[2][KK];  // K fragments (P side) or V fragments (dS side) of the wave's 32 keys
+#pragma unroll
+  for (int jb = 0; jb < 2; ++jb) {
+    const int kloc = kg * 32 + jb * 16 + col;
+    kvalid[jb] = kloc < tr.nrows;
+    kr[jb] = tr.row0 + (kvalid[jb] ? kloc : 0);
+    const int kexp = key_expiry(tok_meta[tr.start + kr[jb]], W);
+    kexp4[jb] = kexp >= (1 << 29) ? INT_MAX : kexp << 2;
+    const long row = tr.start + kr[jb];
     const unsigned short *src = (side == 0 ? k : v) + (row * hkv + hk) * D;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) xf[kk] = lds8(src + kk * 16 + hh * 8);
+    for (int kk = 0; kk < KK; ++kk) xf[jb][kk] = lds8(src + kk * 32 + grp4 * 8);
   }
-  f32x16 acc[DB];  // dV (P side) or dK (dS side): D[i = key][j = d]
+  f32x4 acc[2][DB];  // dV (P side) or dK (dS side): D[i = key][j = d]
 #pragma unroll
-  for (int db = 0; db < DB; ++db) acc[db] = f32x16{};
+  for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) acc[jb][db] = f32x4{};
 
   LaneOffsets<D> lo;
-  lo.init(lane, 0);
+  lo.init(lane);
   // Transposed-read offsets with 64 KB added, hidden from the compiler: for
   // d = 128 a tile of buffer 2 lies above the 64 KB that an LDS
   // instruction's offset field reaches, and with these its reads carry the
@@ -703,12 +790,11 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
   // read.
   constexpr int HIBUF = 2, HIBIAS = 65536;
   constexpr bool HIGH2 = 4 * T64 * 2 >= HIBIAS;  // buffers 0 and 1 fill the low 64 KB
-  int trah[DB], trbh[DB];
+  int trh[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) {
-    trah[db] = lo.tra[db] + HIBIAS;
-    trbh[db] = lo.trb[db] + HIBIAS;
-    asm volatile("" : "+v"(trah[db]), "+v"(trbh[db]));
+    trh[db] = lo.tr[db] + HIBIAS;
+    asm volatile("" : "+v"(trh[db]));
   }
   const long q_stride = (long)hq * D;
   const int e0 = kt_ptr[g], e1 = kt_ptr[g + 1];
@@ -726,8 +812,8 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
   fq.init(wave, lane, qrow_bytes);
   const long hbase = (long)hk * grp * D + (long)tr.start * q_stride;
   const unsigned qbytes = (unsigned)(tr.len * (long)qrow_bytes);
-  const __amdgpu_buffer_rsrc_t rQ = make_rsrc(q + hbase, qbytes);
-  const __amdgpu_buffer_rsrc_t rO = make_rsrc(dout + hbase, qbytes);
+  const i32x4 rQ = make_rsrc(q + hbase, qbytes);
+  const i32x4 rO = make_rsrc(dout + hbase, qbytes);
   // the wave index as a scalar: the resources and the direct loads' LDS
   // addresses are then built in scalar registers (a resource held in vector
   // registers needs a waterfall loop around every load)
@@ -741,7 +827,7 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     fq.issue(nD, rO, so, swave);
     if (swave < 3) {
       const long hrow = (long)(hk * grp + hi) * P + tr.start;
-      const __amdgpu_buffer_rsrc_t rS =
+      const i32x4 rS =
           make_rsrc(swave == 0 ? (const void *)(lse2 + hrow)
                     : swave == 1 ? (const void *)(delta + hrow)
                                  : (const void *)(tok_meta + tr.start),
@@ -759,54 +845,67 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     const char *cD = reinterpret_cast<const char *>(bD);
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
-      bf16x8 aq[KK];
+      // 32 query rows (two 16-row blocks ib) x 32 keys (jb)
+      f32x4 s[2][2];
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) aq[kk] = frag_row<D>(cQ, qb * 32, lo.row[kk]);
-      f32x16 s = f32x16{};
+      for (int ib = 0; ib < 2; ++ib) {
+        bf16x8 aq[KK];
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) s = mfma32(aq[kk], xf[kk], s);
+        for (int kk = 0; kk < KK; ++kk) aq[kk] = frag_row<D>(cQ, qb * 32 + ib * 16, lo.row[kk]);
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const f32x4 L4 = *reinterpret_cast<const f32x4 *>(&bL[qb * 32 + 8 * rg + 4 * hh]);
+        for (int jb = 0; jb < 2; ++jb) s[ib][jb] = f32x4{};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) s[rg * 4 + j] = fmaf(s[rg * 4 + j], scale_log2, -L4[j]);
+        for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+          for (int jb = 0; jb < 2; ++jb) s[ib][jb] = mfma16(aq[kk], xf[jb][kk], s[ib][jb]);
+      }
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib) {
+        const f32x4 L4 = *reinterpret_cast<const f32x4 *>(&bL[qb * 32 + ib * 16 + 4 * grp4]);
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[ib][jb][r] = fmaf(s[ib][jb][r], scale_log2, -L4[r]);
       }
       if (masked) {  // uniform branch: only the exponents change
-        // the lane's query rows qc + 4 hh in [qlo, qhi) are inside the unit
-        // and not before its key
-        const int qhi = vrows - 4 * hh;
-        const int qlo = kvalid ? kr - r0 - 4 * hh : qhi;
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int qc0 = qb * 32 + 8 * rg;
-          const i32x4 M4 = *reinterpret_cast<const i32x4 *>(&bM[qc0 + 4 * hh]);
+        for (int jb = 0; jb < 2; ++jb) {
+          // the lane's query rows qc + 4 grp4 in [qlo, qhi) are inside the
+          // unit and not before its key
+          const int qhi = vrows - 4 * grp4;
+          const int qlo = kvalid[jb] ? kr[jb] - r0 - 4 * grp4 : qhi;
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int qc = qc0 + j;
-            const bool vis = (qc >= qlo) & (qc < qhi) & (M4[j] < kexp4);
-            s[rg * 4 + j] = vis ? s[rg * 4 + j] : -INFINITY;
+          for (int ib = 0; ib < 2; ++ib) {
+            const int qc0 = qb * 32 + ib * 16;
+            const i32x4 M4 = *reinterpret_cast<const i32x4 *>(&bM[qc0 + 4 * grp4]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int qc = qc0 + r;
+              const bool vis = (qc >= qlo) & (qc < qhi) & (M4[r] < kexp4[jb]);
+              s[ib][jb][r] = vis ? s[ib][jb][r] : -INFINITY;
+            }
           }
         }
       }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
       bf16x8 pa[2];
-      pa[0] = pack8(s, 0);
-      pa[1] = pack8(s, 8);
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb) {
+#pragma unroll
+        for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[ib][jb][r] = __builtin_amdgcn_exp2f(s[ib][jb][r]);
+        pa[jb] = pack8(s[0][jb], s[1][jb]);
+      }
       // P in the accumulator's lane order, read back by the dS wave of the same keys
       bf16x8 *pdst = reinterpret_cast<bf16x8 *>(bP) + ((qb * 4 + kg) * 2) * 64 + lane;
       pdst[0] = pa[0];
       pdst[64] = pa[1];
 #pragma unroll
-      for (int c2 = 0; c2 < 2; ++c2) {
-        bf16x8 bo[DB];
+      for (int db = 0; db < DB; ++db) {
+        const bf16x8 bo = decltype(hi_tag)::value ? frag_tr<D>(cD, qb * 32, trh[db], HIBIAS)
+                                                  : frag_tr<D>(cD, qb * 32, lo.tr[db]);
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-          bo[db] = decltype(hi_tag)::value
-                       ? frag_tr<D>(cD, qb * 32 + c2 * 16, trah[db], trbh[db], HIBIAS)
-                       : frag_tr<D>(cD, qb * 32 + c2 * 16, lo.tra[db], lo.trb[db]);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) acc[db] = mfma32(pa[c2], bo[db], acc[db]);
+        for (int jb = 0; jb < 2; ++jb) acc[jb][db] = mfma16(pa[jb], bo, acc[jb][db]);
       }
     }
   };
@@ -817,42 +916,42 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
                      __attribute__((always_inline)) {
     const char *cQ = reinterpret_cast<const char *>(bQ);
     const char *cD = reinterpret_cast<const char *>(bD);
-    f32x16 dpb[2];
+    f32x4 dp[4][2];  // [16-row block][key block]
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int ib = 0; ib < 4; ++ib) {
       bf16x8 ad[KK];
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) ad[kk] = frag_row<D>(cD, qb * 32, lo.row[kk]);
+      for (int kk = 0; kk < KK; ++kk) ad[kk] = frag_row<D>(cD, ib * 16, lo.row[kk]);
       // dP - Delta: the chain starts from the rows' -Delta
+      const f32x4 N4 = *reinterpret_cast<const f32x4 *>(&bE[ib * 16 + 4 * grp4]);
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const f32x4 N4 = *reinterpret_cast<const f32x4 *>(&bE[qb * 32 + 8 * rg + 4 * hh]);
+      for (int jb = 0; jb < 2; ++jb) dp[ib][jb] = N4;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) dpb[qb][rg * 4 + j] = N4[j];
-      }
+      for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) dpb[qb] = mfma32(ad[kk], xf[kk], dpb[qb]);
+        for (int jb = 0; jb < 2; ++jb) dp[ib][jb] = mfma16(ad[kk], xf[jb][kk], dp[ib][jb]);
     }
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
-      f32x16 dp = dpb[qb];
       const bf16x8 *psrc = reinterpret_cast<const bf16x8 *>(bP) + ((qb * 4 + kg) * 2) * 64 + lane;
-      const bf16x8 p0 = psrc[0], p1 = psrc[64];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dp[r] *= (float)(r < 8 ? p0[r] : p1[r - 8]);
       bf16x8 dsa[2];
-      dsa[0] = pack8(dp, 0);
-      dsa[1] = pack8(dp, 8);
 #pragma unroll
-      for (int c2 = 0; c2 < 2; ++c2) {
-        bf16x8 bq[DB];
+      for (int jb = 0; jb < 2; ++jb) {
+        const bf16x8 pj = psrc[64 * jb];
+        f32x4 lo4 = dp[qb * 2][jb], hi4 = dp[qb * 2 + 1][jb];
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-          bq[db] = decltype(hi_tag)::value
-                       ? frag_tr<D>(cQ, qb * 32 + c2 * 16, trah[db], trbh[db], HIBIAS)
-                       : frag_tr<D>(cQ, qb * 32 + c2 * 16, lo.tra[db], lo.trb[db]);
+        for (int r = 0; r < 4; ++r) {
+          lo4[r] *= (float)pj[r];
+          hi4[r] *= (float)pj[4 + r];
+        }
+        dsa[jb] = pack8(lo4, hi4);
+      }
 #pragma unroll
-        for (int db = 0; db < DB; ++db) acc[db] = mfma32(dsa[c2], bq[db], acc[db]);
+      for (int db = 0; db < DB; ++db) {
+        const bf16x8 bq = decltype(hi_tag)::value ? frag_tr<D>(cQ, qb * 32, trh[db], HIBIAS)
+                                                  : frag_tr<D>(cQ, qb * 32, lo.tr[db]);
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb) acc[jb][db] = mfma16(dsa[jb], bq, acc[jb][db]);
       }
     }
   };
@@ -863,15 +962,12 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     int cr0 = (((int)((unsigned)kt_ord[ce] & 0x7fffffffu)) - tr.qbase) * TQ;
     int cpart = (int)((unsigned)kt_ord[ce] >> 31);
     issue(cr0, 0, sQ0, sD0, sL0, sE0, sM0);
-    wait_all_and_sync();
+    wait_loads_and_sync();
     bool have_cur = true;  // the P side has a unit this step
     int pb = 0;            // P buffer of the P side's unit (the dS side uses the other)
     bool first = true;
-    // The work of one step, with every LDS buffer it touches as a distinct
-    // __restrict__ parameter: the direct loads into the next unit's buffers
-    // (n*) are then known not to write what the P side (c*), the dS side
-    // (p*) and the P exchange (wP, rP) access, so no LDS access waits for
-    // them.
+    // The work of one step: the direct loads into the next unit's buffers
+    // (n*), the P side (c*), the dS side (p*) and the P exchange (wP, rP).
     auto body = [&](auto cur_hi, auto prev_hi, const bool more, const int nr0, const int nhi,
                     unsigned short *__restrict__ nQ,
                     unsigned short *__restrict__ nD, float *__restrict__ nL,
@@ -893,8 +989,8 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     };
     // One step on Q/dO buffer B (the P side's unit; the dS side's is the
     // previous buffer, the next unit's loads go to the following one), with
-    // the buffers as compile-time indices: the direct loads in flight then
-    // provably write other LDS than the step reads.
+    // the buffers as compile-time indices, so that their addresses fit the
+    // instructions' offset fields.
     auto step = [&](auto bc) __attribute__((always_inline)) -> bool {
       constexpr int B = decltype(bc)::value, NBUF = (B + 1) % NB, PBUF = (B + NB - 1) % NB;
       // next unit: other half of this tile, else next head, else next entry
@@ -926,7 +1022,7 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
            std::integral_constant<bool, HIGH2 && PBUF == HIBUF>{},
            more, nr0, nhi, Q[NBUF], Dd[NBUF], Lr[NBUF], Er[NBUF], Mr[NBUF], Q[B], Dd[B], Lr[B],
            Mr[B], Q[PBUF], Dd[PBUF], Er[PBUF], sP[pb], sP[pb ^ 1]);
-      __syncthreads();
+      wait_loads_and_sync();
       if (!have_cur) return false;
       have_cur = more;
       ce = ne;
@@ -947,7 +1043,7 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
 
   // stage through LDS (RP key rows per pass) for coalesced stores;
   // accumulator D[i = key][j = d]
-  wait_all_and_sync();
+  wait_loads_and_sync();
   TO *st = reinterpret_cast<TO *>(sQ0);
   constexpr int CH = 16 / sizeof(TO);   // elements per 16-byte chunk
   constexpr int RP = 128 / sizeof(TO);  // key rows per pass (16 KB)
@@ -959,17 +1055,14 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     for (int pass = 0; pass < TQ / RP; ++pass) {
       if (side == which && kg * 32 >= pass * RP && kg * 32 < (pass + 1) * RP) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+        for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int kl = kg * 32 + 8 * (r >> 2) + 4 * hh + (r & 3) - pass * RP;
-            const float val = acc[db][r] * mul;
-            const int dd = db * 32 + col;
-            if constexpr (sizeof(TO) == 2)
-              st[kl * D + dd] = f2bf_bits(val);
-            else
-              st[kl * D + dd] = val;
-          }
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int kl = kg * 32 + jb * 16 + 4 * grp4 + r - pass * RP;
+              store_val(st, kl * D + db * 16 + col, acc[jb][db][r] * mul);
+            }
       }
       __syncthreads();
       for (int c = threadIdx.x; c < RP * D / CH; c += 512) {
@@ -1003,7 +1096,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(
     const int32_t *__restrict__ tok_meta, const int32_t *__restrict__ qt_ptr,
     const int32_t *__restrict__ qt_ord, const XcdRanges xr, int hq, int hkv, int W,
     float scale_log2, float scale, long P, TO *__restrict__ dq) {
-  constexpr int KK = D / 16, DB = D / 32, T64 = 64 * D;
+  constexpr int KK = D / 32, DB = D / 16, T64 = 64 * D;
   __shared__ __attribute__((aligned(16))) unsigned short sK0[T64], sK1[T64], sV0[T64], sV1[T64];
   __shared__ __attribute__((aligned(16))) int sM0[64], sM1[64];
 
@@ -1012,65 +1105,69 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(
   const int hk = h / (hq / hkv);
   const TileRows tr = tile_rows(seg_info, tile_seg, g);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int col = lane & 31, hh = lane >> 5;
-  const int qloc = wave * 32 + col;
-  const bool qvalid = qloc < tr.nrows;
-  const int qr = tr.row0 + (qvalid ? qloc : 0);
-  const long qrow_abs = tr.start + qr;
-  const int qstep = tok_meta[qrow_abs] >> 2;
-
-  bf16x8 qf[KK], df[KK];
-  {
+  const int col = lane & 15, grp = lane >> 4;
+  // the lane's two queries, rows c and 16 + c of the wave's 32
+  bool qvalid[2];
+  int qr[2], qstep[2];
+  bf16x8 qf[2][KK], df[2][KK];
+  float l2[2], ndlt[2];  // log2-sum-exp and -Delta
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const int qloc = wave * 32 + qb * 16 + col;
+    qvalid[qb] = qloc < tr.nrows;
+    qr[qb] = tr.row0 + (qvalid[qb] ? qloc : 0);
+    const long qrow_abs = tr.start + qr[qb];
+    qstep[qb] = tok_meta[qrow_abs] >> 2;
     const unsigned short *qp = q + (qrow_abs * hq + h) * D;
     const unsigned short *dp = dout + (qrow_abs * hq + h) * D;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      qf[kk] = lds8(qp + kk * 16 + hh * 8);
-      df[kk] = lds8(dp + kk * 16 + hh * 8);
+      qf[qb][kk] = lds8(qp + kk * 32 + grp * 8);
+      df[qb][kk] = lds8(dp + kk * 32 + grp * 8);
+    }
+    const long rv = (long)h * P + qrow_abs;
+    if constexpr (FUSE) {
+      // the lane holds a quarter of the row's d (the other lanes of the row
+      // the rest): bf16 products are exact in fp32, summed in a fixed order
+      const unsigned short *op = o + (qrow_abs * hq + h) * D;
+      float acc = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const bf16x8 of = lds8(op + kk * 32 + grp * 8);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{df[qb][kk][2 * i], df[qb][kk][2 * i + 1]},
+                                                bf16x2{of[2 * i], of[2 * i + 1]}, acc, false);
+      }
+      ndlt[qb] = -row_sum(acc);
+      l2[qb] = lse[rv] * LOG2E;
+      if (qvalid[qb] && grp == 0) {
+        delta[rv] = ndlt[qb];
+        lse2[rv] = l2[qb];
+      }
+    } else {
+      l2[qb] = lse2[rv];
+      ndlt[qb] = delta[rv];
     }
   }
-  float l2, ndlt;  // log2-sum-exp and -Delta of the lane's query
-  const long rv = (long)h * P + qrow_abs;
-  if constexpr (FUSE) {
-    // the lane holds half of the row's d (the other half in lane + 32):
-    // bf16 products are exact in fp32, summed in a fixed order
-    const unsigned short *op = o + (qrow_abs * hq + h) * D;
-    float acc = 0.f;
+  f32x4 dqacc[DB][2];
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      const bf16x8 of = lds8(op + kk * 16 + hh * 8);
+  for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        acc = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{df[kk][2 * i], df[kk][2 * i + 1]},
-                                              bf16x2{of[2 * i], of[2 * i + 1]}, acc, false);
-    }
-    acc += __shfl_xor(acc, 32, 64);
-    ndlt = -acc;
-    l2 = lse[rv] * LOG2E;
-    if (qvalid && hh == 0) {
-      delta[rv] = ndlt;
-      lse2[rv] = l2;
-    }
-  } else {
-    l2 = lse2[rv];
-    ndlt = delta[rv];
-  }
-  f32x16 dqacc[DB];
-#pragma unroll
-  for (int db = 0; db < DB; ++db) dqacc[db] = f32x16{};
+    for (int qb = 0; qb < 2; ++qb) dqacc[db][qb] = f32x4{};
 
   LaneOffsets<D> lo;
-  lo.init(lane, 0);
+  lo.init(lane);
   const long kv_stride = (long)hkv * D;
   const int row_bytes = (int)(kv_stride * 2);
   BufFill<D, 4> fp;
   fp.init(wave, lane, row_bytes);
   // the segment's rows of this kv head; rows past the segment read as zeros
-  const __amdgpu_buffer_rsrc_t rK =
+  const i32x4 rK =
       make_rsrc(k + (long)hk * D + (long)tr.start * kv_stride, (unsigned)tr.len * row_bytes);
-  const __amdgpu_buffer_rsrc_t rV =
+  const i32x4 rV =
       make_rsrc(v + (long)hk * D + (long)tr.start * kv_stride, (unsigned)tr.len * row_bytes);
-  const __amdgpu_buffer_rsrc_t rM = make_rsrc(tok_meta + tr.start, (unsigned)tr.len * 4);
+  const i32x4 rM = make_rsrc(tok_meta + tr.start, (unsigned)tr.len * 4);
 
   // the wave index as a scalar: the direct loads' LDS addresses are then
   // formed in scalar registers (no readfirstlane per load)
@@ -1084,58 +1181,77 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(
   auto compute = [&](const Unit &u, const char *__restrict__ sK, const char *__restrict__ sV,
                      const int *__restrict__ sM) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      if (kb * 32 >= u.vrows) break;
-      bf16x8 ak[KK], av[KK];
+    for (int kh = 0; kh < 2; ++kh) {  // 32-key halves, two 16-key blocks kb each
+      if (kh * 32 >= u.vrows) break;
+      f32x4 s[2][2], dp[2][2];
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        ak[kk] = frag_row<D>(sK, kb * 32, lo.row[kk]);
-        av[kk] = frag_row<D>(sV, kb * 32, lo.row[kk]);
+      for (int kb = 0; kb < 2; ++kb) {
+        bf16x8 ak[KK], av[KK];
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          ak[kk] = frag_row<D>(sK, kh * 32 + kb * 16, lo.row[kk]);
+          av[kk] = frag_row<D>(sV, kh * 32 + kb * 16, lo.row[kk]);
+        }
+        // dP^T - Delta: the chain starts from -Delta (one value per query)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+          s[kb][qb] = f32x4{};
+          dp[kb][qb] = f32x4{ndlt[qb], ndlt[qb], ndlt[qb], ndlt[qb]};
+        }
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb) {
+            s[kb][qb] = mfma16(ak[kk], qf[qb][kk], s[kb][qb]);
+            dp[kb][qb] = mfma16(av[kk], df[qb][kk], dp[kb][qb]);
+          }
       }
-      // dP^T - Delta: the chain starts from -Delta (one value per lane's query)
-      f32x16 s = f32x16{}, dp;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dp[r] = ndlt;
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        s = mfma32(ak[kk], qf[kk], s);
-        dp = mfma32(av[kk], df[kk], dp);
-      }
+      // with the order below 172.1 -> 168.0 ms on the benchmark batch (this
+      // one alone 169.0; 6 or 8 ahead 169.3, 169.8).  The dK/dV kernel's
+      // products in such orders: 259.5 -> 261-266 ms, so it has none
+      read_ahead<4 * KK, 4, 2, 1>();
       // dS^T = P^T (dP^T - Delta); a masked pair gets exponent -inf (P = 0).
       // One uniform branch; inside, the predicate is bitwise (no branch per
       // element).
       if (__builtin_expect(u.partial, 0)) {
-        // the lane's keys kc + 4 hh < lim are inside the unit and not after
-        // its query
-        const int lim = (qvalid ? min(u.vrows, qr - u.r0 + 1) : 0) - 4 * hh;
-        const unsigned wfloor = window_floor(qstep, W);
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int kc0 = kb * 32 + 8 * rg;
-          const i32x4 M4 = *reinterpret_cast<const i32x4 *>(sM + kc0 + 4 * hh);
+        for (int qb = 0; qb < 2; ++qb) {
+          // the lane's keys kc + 4 grp < lim are inside the unit and not
+          // after its query
+          const int lim = (qvalid[qb] ? min(u.vrows, qr[qb] - u.r0 + 1) : 0) - 4 * grp;
+          const unsigned wfloor = window_floor(qstep[qb], W);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int r = rg * 4 + j;
-            const bool vis = (kc0 + j < lim) & (window_word(M4[j]) >= wfloor);
-            const float x = vis ? fmaf(s[r], scale_log2, -l2) : -INFINITY;
-            s[r] = __builtin_amdgcn_exp2f(x) * dp[r];
+          for (int kb = 0; kb < 2; ++kb) {
+            const int kc0 = kh * 32 + kb * 16;
+            const i32x4 M4 = *reinterpret_cast<const i32x4 *>(sM + kc0 + 4 * grp);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const bool vis = (kc0 + j < lim) & (window_word(M4[j]) >= wfloor);
+              const float x = vis ? fmaf(s[kb][qb][j], scale_log2, -l2[qb]) : -INFINITY;
+              s[kb][qb][j] = __builtin_amdgcn_exp2f(x) * dp[kb][qb][j];
+            }
           }
         }
       } else {
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -l2)) * dp[r];
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              s[kb][qb][j] = __builtin_amdgcn_exp2f(fmaf(s[kb][qb][j], scale_log2, -l2[qb])) *
+                             dp[kb][qb][j];
       }
+      bf16x8 dsb[2];
 #pragma unroll
-      for (int c2 = 0; c2 < 2; ++c2) {
-        bf16x8 kt[DB];
+      for (int qb = 0; qb < 2; ++qb) dsb[qb] = pack8(s[0][qb], s[1][qb]);
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-          kt[db] = frag_tr<D>(sK, kb * 32 + c2 * 16, lo.tra[db], lo.trb[db]);
-        const bf16x8 dsb = pack8(s, c2 * 8);
+      for (int db = 0; db < DB; ++db) {
+        const bf16x8 kt = frag_tr<D>(sK, kh * 32, lo.tr[db]);
 #pragma unroll
-        for (int db = 0; db < DB; ++db) dqacc[db] = mfma32(kt[db], dsb, dqacc[db]);
+        for (int qb = 0; qb < 2; ++qb) dqacc[db][qb] = mfma16(kt, dsb[qb], dqacc[db][qb]);
       }
+      read_ahead<2 * DB, DB == 8 ? 6 : 4, 2, 2>();
     }
   };
   auto step = [&](const Unit &u, const bool more, const Unit &nu,
@@ -1154,16 +1270,13 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(
   walk_units(make_unit(qt_ord, e0, 0, tr.qbase, tr.len), step, issue, next, sK0, sV0, sM0,
              sK1, sV1, sM1);
 
-  if (qvalid) {
-    TO *qrowp = dq + (qrow_abs * hq + h) * D;
+  const bool vec = aligned4(dq);
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+  for (int qb = 0; qb < 2; ++qb) {
+    if (!qvalid[qb]) continue;
+    TO *qrowp = dq + ((long)(tr.start + qr[qb]) * hq + h) * D;
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const int d0 = db * 32 + 8 * r4 + 4 * hh;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) store_val(qrowp, d0 + j, dqacc[db][r4 * 4 + j] * scale);
-      }
+    for (int db = 0; db < DB; ++db) store4(qrowp + db * 16 + 4 * grp, dqacc[db][qb] * scale, vec);
   }
 }
 
