@@ -409,6 +409,58 @@ __device__ __forceinline__ bool xcd_block(const XcdRanges &r, int nh, int grp, b
   return true;
 }
 
+// Longest first, in classes.  The idx-th block of an XCD's C tiles (lo ..) x
+// hkv kv heads, with the tiles sorted into eight classes of their number of
+// listed partners (ptr), the longest class first; inside a class kv head by kv
+// head and in tile order, so neighbouring blocks still share their tiles in
+// L2.  The ranges hold equal work, but a range run in tile order can meet a
+// long tile near its end: that costs the dK/dV kernel 20% on the 16-segment
+// small batch, 130% on one trajectory of it (1.7 blocks per CU) and 14% on one
+// trajectory of the 7B-class batch (list scheduling over its tile lists); in
+// classes 4%, 58% and 3%.  C <= MAX_CLASSED, blocks of 512
+// threads; scratch: 128 ints of LDS.  The result is the same for every thread.
+constexpr int MAX_CLASSED = 512;
+
+__device__ __forceinline__ void classed_block(const int32_t *ptr, int lo, int C, int hkv, int idx,
+                                              int *scratch, int &tile, int &hk) {
+  constexpr int NC = 8, WAVES = MAX_CLASSED / 64;
+  int *cnt = scratch, *wmax = scratch + NC * WAVES, *pick = wmax + WAVES;
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  const int len = t < C ? ptr[lo + t + 1] - ptr[lo + t] : 0;
+  int m = len;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+  if (lane == 0) wmax[wave] = m;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) m = max(m, wmax[w]);
+  const int cls = t < C ? (int)((long)len * NC / (m + 1)) : NC;
+  unsigned long long mine = 0;  // lanes of the thread's class
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const unsigned long long b = __ballot(cls == c);
+    if (cls == c) mine = b;
+    if (lane == 0) cnt[c * WAVES + wave] = __popcll(b);
+  }
+  __syncthreads();
+  // the class, kv head and place of the block (the same in every thread)
+  int c = NC - 1, n = 0, rest = idx;
+  for (;; --c) {
+    n = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) n += cnt[c * WAVES + w];
+    if (c == 0 || rest < n * hkv) break;
+    rest -= n * hkv;
+  }
+  hk = rest / n;
+  int before = 0;  // tiles of the class in the waves before
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) before += w < wave ? cnt[c * WAVES + w] : 0;
+  if (cls == c && before + __popcll(mine & ((1ull << lane) - 1)) == rest - hk * n) *pick = t;
+  __syncthreads();
+  tile = lo + *pick;
+}
+
 inline XcdRanges xcd_ranges(const int32_t (&b)[9]) {
   XcdRanges r;
   for (int i = 0; i < 9; ++i) r.b[i] = b[i];
@@ -740,17 +792,24 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
 
   int g, hk;
   {
-    // XCD x takes the tiles of its range in order and runs them kv head by
-    // kv head, so the blocks resident on one XCD are neighbouring k-tiles of
-    // one kv head: they walk the same q-tiles of a segment and share their
-    // Q/dO tiles in L2 (ordering the range longest column first instead mixes
-    // segments and was 7% slower)
+    // XCD x takes the tiles of its range kv head by kv head, so the blocks
+    // resident on one XCD are neighbouring k-tiles of one kv head: they walk
+    // the same q-tiles of a segment and share their Q/dO tiles in L2.  A range
+    // with more tiles than the classes take runs in tile order (its many
+    // blocks even out: 1% on the benchmark batch, where a full sort, which
+    // mixes segments, was 7% slower); so does one whose blocks all run at once.
     const int bx = blockIdx.x, x = bx & 7, i = bx >> 3;
     const int lo = xr.b[x], C = xr.b[x + 1] - lo;
-    if (C == 0) return;
-    hk = i / C;
-    if (hk >= hkv) return;
-    g = lo + (i - hk * C);
+    if (i >= C * hkv) return;
+    if (C <= MAX_CLASSED && C * hkv > 32) {
+      int *scratch = reinterpret_cast<int *>(sP);
+      classed_block(kt_ptr, lo, C, hkv, i, scratch, g, hk);
+      g = __builtin_amdgcn_readfirstlane(g);
+      hk = __builtin_amdgcn_readfirstlane(hk);
+    } else {
+      hk = i / C;
+      g = lo + (i - hk * C);
+    }
   }
   const int grp = hq / hkv;
   const TileRows tr = tile_rows(seg_info, tile_seg, g);

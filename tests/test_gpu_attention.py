@@ -15,6 +15,7 @@ import pytest
 
 from oracle import attention as OA
 from oracle import layout as OL
+from paper_2607_11185_amd import seg as S
 from paper_2607_11185_amd import workload as WL
 from tests.gpu_helpers import TOL, GpuRun, rel, say, vis_window
 
@@ -449,3 +450,34 @@ def test_action_rows_segment_equals_stepwise():
     b_o, b_l, b_t = by_target(sw_run, o2, l2)
     assert np.array_equal(a_t, b_t)
     assert rel(a_o, b_o) < 1e-2 and rel(a_l, b_l) < 1e-3
+
+
+# (kv heads, image tokens, turns): tiles x kv heads per eighth of the dK/dV
+# launch below and above the 32 blocks that run at once, and above the 512
+# tiles that the longest-first classes take
+@pytest.mark.parametrize("hkv,img,turns", [(1, 150, 5), (8, 150, 12), (5, 700, 9), (2, 40, 2)])
+def test_dkdv_block_order_covers_every_key(hkv, img, turns):
+    import torch
+    n_traj = 4 if turns != 2 else 4400
+    cfg = WL.Config("order", n_traj, (turns, turns), 30, img, (20, 90), 4, 2, 3, hkv, hkv, 64, 64, 100,
+                    seed=77)
+    run = GpuRun(cfg).packed_inputs()
+    cols = np.diff(run.host["xcd_cols"])
+    say(f"P={run.P} tiles per eighth {cols.min()}..{cols.max()} x {hkv}")
+    assert {1: cols.max() * hkv <= 32, 2: cols.max() > 512}.get(hkv, cols.max() * hkv > 32)
+    run.fwd()
+    dk, dv = (torch.full_like(t, float("nan")) for t in (run.k, run.v))
+    S.seg_attn_bwd(run.lay, run.q, run.k, run.v, run.o, run.lse, run.dout, run.scale, dk=dk, dv=dv)
+    assert bool(torch.isfinite(dk).all()) and bool(torch.isfinite(dv).all())
+    ref = OL.build(run.spans, cfg.window, cfg.seg_steps, 128, with_tiles=False, mode=cfg.mode)
+    segs = ref.segments if len(ref.segments) < 100 else ref.segments[::400]
+    for sg in segs:
+        hide = torch.from_numpy(~OL.visibility(sg, vis_window(cfg))).to(run.dev)
+        rows = slice(sg.start, sg.start + sg.length)
+        for h in range(hkv):
+            q, k, v, do, o = (x[rows, h].double() for x in (run.q, run.k, run.v, run.dout, run.o))
+            p = torch.softmax((q @ k.t() * run.scale).masked_fill(hide, float("-inf")), 1)
+            ds = p * (do @ v.t() - (do * o).sum(1, keepdim=True)) * run.scale
+            for name, got, want in (("dk", dk, ds.t() @ q), ("dv", dv, p.t() @ do)):
+                e = float((got[rows, h].double() - want).norm() / want.norm())
+                assert e < TOL, (name, sg.start, h, e)
