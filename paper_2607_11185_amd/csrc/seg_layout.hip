@@ -3,10 +3,12 @@
 // stream"), read with a sliding window of W screenshots and L-turn segments.
 //
 // Host part (seg_layout_query and the first half of seg_build_layout): cut each
-// trajectory's turns into segments and pack them; this is O(turns) arithmetic on
-// the span lists.  Device part: expand the per-segment span table into per-token
-// descriptors, the loss rows, and the 128x128 block-sparse tile map with its
-// transposed CSR and the exact visible-pair count of every segment.
+// trajectory's turns into segments and pack them, O(turns) arithmetic on the
+// span lists; for a build also four numbers per tile (its first and last turn,
+// its keys' earliest and latest expiry), the CSR pointers and visible-pair
+// counts that follow from them, and the attention kernels' launch schedule.
+// Device part, one kernel: expand these tables into per-token descriptors, the
+// loss rows, and the 128x128 block-sparse tile map with its transposed CSR.
 #include <algorithm>
 #include <climits>
 #include <cstring>
@@ -42,8 +44,14 @@ struct LossPiece {
 // Per-segment record used by the kernels (device copy lives in the workspace).
 struct DevSeg {
   int32_t start, len, qbase, nt;
-  int32_t piece_base, piece_count, pad0, pad1;
-  int64_t tri_base;  // offset of the segment's lower-triangular class matrix
+  int32_t piece_base, piece_count;
+};
+
+// What decides the class of a tile pair (see tile_class): turns of the tile's
+// first and last row, earliest and latest turn at which one of its keys
+// expires (INT32_MAX: never).
+struct TileSpan {
+  int32_t first_turn, last_turn, min_exp, max_exp;
 };
 
 struct Plan {
@@ -52,49 +60,67 @@ struct Plan {
   std::vector<DevSeg> dsegs;
   std::vector<Piece> pieces;
   std::vector<LossPiece> lpieces;
-  int32_t max_nt = 0;
+  // of a build only (plan_tiles)
+  std::vector<TileSpan> spans;          // [G]
+  std::vector<int32_t> qt_ptr, kt_ptr;  // [G+1]
+  std::vector<int64_t> seg_pairs;       // [S]
   // launch schedule of the attention kernels (see seg_layout)
-  std::vector<int32_t> row_work, col_work;  // [G] listed k-tiles / q-tiles of each tile
   int32_t xcd_rows[9] = {}, xcd_cols[9] = {};
 };
 
-// Listed partners of every tile of one segment, from its token runs.  Turns
-// never decrease along a segment, so a q-tile's most permissive row is its
-// first one; a k-tile's most permissive key is the one that expires last
-// (text and prompt never do, a screenshot of turn s at turn s + Wv).  An
+// Spans of every tile of one segment and its listed partners, from its token
+// runs.  Turns never decrease along a segment, so a q-tile's most permissive
+// row is its first one; a k-tile's most permissive key is the one that expires
+// last (text and prompt never do, a screenshot of turn s at turn s + Wv).  An
 // off-diagonal pair (q-tile i > k-tile j) holds a visible pair iff the first
 // row's turn of i is below the latest expiry in j, so k-tile j is listed by the
 // contiguous q-tiles j .. r_j - 1 (the diagonal always).
-void tile_work(const Piece *pc, int npc, int len, int tile, int Wv, int32_t *row_w,
+void tile_work(const Piece *pc, int npc, int len, int tile, int Wv, TileSpan *sp, int32_t *row_w,
                int32_t *col_w) {
   const int n = (len + tile - 1) / tile;
-  std::vector<int64_t> first_turn(n), last_exp(n, INT64_MIN);
   int k = 0;
   for (int t = 0; t < n; ++t) {
     const int r0 = t * tile, r1 = std::min(len, r0 + tile);
     while (k + 1 < npc && pc[k + 1].off <= r0) ++k;
-    first_turn[t] = pc[k].meta >> 2;
+    TileSpan d{pc[k].meta >> 2, 0, INT32_MAX, INT32_MIN};
     for (int i = k; i < npc && pc[i].off < r1; ++i) {
       if (pc[i].len == 0 || pc[i].off + pc[i].len <= r0) continue;
       const int kind = pc[i].meta & 3;
-      const int64_t e = kind == SEG_KIND_IMAGE ? (int64_t)(pc[i].meta >> 2) + Wv : INT64_MAX;
-      last_exp[t] = std::max(last_exp[t], e);
+      const int64_t e = kind == SEG_KIND_IMAGE ? (int64_t)(pc[i].meta >> 2) + Wv : INT32_MAX;
+      d.min_exp = (int32_t)std::min<int64_t>(d.min_exp, e);
+      d.max_exp = (int32_t)std::max<int64_t>(d.max_exp, std::min<int64_t>(e, INT32_MAX));
+      d.last_turn = pc[i].meta >> 2;
     }
+    sp[t] = d;
   }
-  std::vector<int32_t> diff(n + 1, 0);
+  std::fill(row_w, row_w + n, 0);
   for (int j = 0; j < n; ++j) {
     // first q-tile after j whose first row's turn has reached the expiry
-    const int r = (int)(std::lower_bound(first_turn.begin() + j + 1, first_turn.end(), last_exp[j]) -
-                        first_turn.begin());
+    const int r = (int)(std::lower_bound(sp + j + 1, sp + n, sp[j].max_exp,
+                                         [](const TileSpan &x, int32_t e) { return x.first_turn < e; }) -
+                        sp);
     col_w[j] = r - j;
-    diff[j + 1] += 1;
-    diff[r] -= 1;
+    if (j + 1 < n) ++row_w[j + 1];
+    if (r < n) --row_w[r];
   }
   int run = 0;
   for (int i = 0; i < n; ++i) {
-    run += diff[i];
+    run += row_w[i];
     row_w[i] = 1 + run;
   }
+}
+
+// Visible pairs of one segment: every row sees the rows up to itself, except
+// the screenshots of turns more than Wv - 1 before its own.
+int64_t count_pairs(const Piece *pc, int npc, int64_t len, int Wv) {
+  int64_t n = len * (len + 1) / 2;
+  int f = 0;  // first run of a turn that no longer sees run i
+  for (int i = 0; i < npc; ++i) {
+    if ((pc[i].meta & 3) != SEG_KIND_IMAGE) continue;
+    while (f < npc && (pc[f].meta >> 2) < (int64_t)(pc[i].meta >> 2) + Wv) ++f;
+    if (f < npc) n -= (int64_t)pc[i].len * (len - pc[f].off);
+  }
+  return n;
 }
 
 // Boundaries of eight consecutive tile ranges with about equal total work.
@@ -111,9 +137,9 @@ void balance8(const std::vector<int32_t> &w, int32_t *b) {
   b[8] = G;
 }
 
-// Byte offsets of the build workspace regions.
+// Byte offsets of the build workspace: the host tables, uploaded as one piece.
 struct BuildWs {
-  size_t dseg, piece, lpiece, cls, qcnt, kcnt, total;
+  size_t dseg, piece, lpiece, info, span, qptr, kptr, pairs, total;
 };
 
 BuildWs build_ws_layout(const seg_sizes &sz, size_t npieces, size_t nlpieces) {
@@ -124,12 +150,15 @@ BuildWs build_ws_layout(const seg_sizes &sz, size_t npieces, size_t nlpieces) {
     off = align_up(off + bytes);
     return o;
   };
-  w.dseg = take(sizeof(DevSeg) * std::max<int64_t>(1, sz.num_segments));
+  const size_t S = sz.num_segments, G = sz.num_qtiles;
+  w.dseg = take(sizeof(DevSeg) * std::max<size_t>(1, S));
   w.piece = take(sizeof(Piece) * std::max<size_t>(1, npieces));
   w.lpiece = take(sizeof(LossPiece) * std::max<size_t>(1, nlpieces));
-  w.cls = take(std::max<int64_t>(1, sz.tile_nnz_max));
-  w.qcnt = take(sizeof(int32_t) * (size_t)std::max<int64_t>(1, sz.num_qtiles));
-  w.kcnt = take(sizeof(int32_t) * (size_t)std::max<int64_t>(1, sz.num_qtiles));
+  w.info = take(sizeof(int32_t) * SEG_INFO_FIELDS * std::max<size_t>(1, S));
+  w.span = take(sizeof(TileSpan) * std::max<size_t>(1, G));
+  w.qptr = take(sizeof(int32_t) * (G + 1));
+  w.kptr = take(sizeof(int32_t) * (G + 1));
+  w.pairs = take(sizeof(int64_t) * std::max<size_t>(1, S));
   w.total = off;
   return w;
 }
@@ -267,7 +296,6 @@ Plan make_plan(const seg_problem *p) {
     d.qbase = (int32_t)qbase;
     d.nt = (int32_t)nt;
     d.piece_base = (int32_t)pl.pieces.size();
-    d.tri_base = tri;
     // pieces: prompt, then per turn j < b: screenshot if j > a - W, text
     int32_t off = 0, c = (int32_t)canon0[sg.traj];
     int32_t pr = p->prompt_len[sg.traj];
@@ -303,7 +331,6 @@ Plan make_plan(const seg_problem *p) {
     int32_t info[SEG_INFO_FIELDS] = {sg.traj, sg.a, sg.b, d.start, d.len, d.qbase,
                                      (int32_t)loss_base, (int32_t)(rows - loss_base)};
     pl.seg_info.insert(pl.seg_info.end(), info, info + SEG_INFO_FIELDS);
-    pl.max_nt = std::max<int32_t>(pl.max_nt, (int32_t)nt);
     qbase += nt;
     tri += nt * (nt + 1) / 2;
     SEG_CHECK(qbase <= INT32_MAX && tri <= INT32_MAX && rows <= INT32_MAX, SEG_ERR_CAPACITY,
@@ -311,21 +338,33 @@ Plan make_plan(const seg_problem *p) {
   }
   sz.num_qtiles = (int32_t)qbase;
   sz.tile_nnz_max = tri;
-  // launch schedule: per-tile work and eight balanced tile ranges per pass
-  {
-    const int Wv = anchored ? SEG_WINDOW_ANCHORED : p->window;
-    const int G = (int)qbase;
-    pl.row_work.assign(G, 0);
-    pl.col_work.assign(G, 0);
-    for (const DevSeg &d : pl.dsegs)
-      tile_work(pl.pieces.data() + d.piece_base, d.piece_count, d.len, tile, Wv,
-                pl.row_work.data() + d.qbase, pl.col_work.data() + d.qbase);
-    balance8(pl.row_work, pl.xcd_rows);
-    balance8(pl.col_work, pl.xcd_cols);
-  }
   sz.loss_rows = (int32_t)rows;
   sz.workspace_bytes = build_ws_layout(sz, pl.pieces.size(), pl.lpieces.size()).total;
   return pl;
+}
+
+// The per-tile part of a build: tile spans, CSR pointers, pair counts and the
+// launch schedule (eight balanced tile ranges per pass).
+void plan_tiles(const seg_problem *p, Plan &pl) {
+  const int Wv = p->mode == SEG_MODE_ANCHORED ? SEG_WINDOW_ANCHORED : p->window;
+  const size_t G = pl.sz.num_qtiles;
+  std::vector<int32_t> row_work(G), col_work(G);
+  pl.spans.resize(G);
+  for (const DevSeg &d : pl.dsegs) {
+    const Piece *pc = pl.pieces.data() + d.piece_base;
+    tile_work(pc, d.piece_count, d.len, p->tile, Wv, pl.spans.data() + d.qbase,
+              row_work.data() + d.qbase, col_work.data() + d.qbase);
+    pl.seg_pairs.push_back(count_pairs(pc, d.piece_count, d.len, Wv));
+  }
+  auto scan = [](const std::vector<int32_t> &w, std::vector<int32_t> &ptr) {
+    ptr.resize(w.size() + 1);
+    ptr[0] = 0;
+    for (size_t i = 0; i < w.size(); ++i) ptr[i + 1] = ptr[i] + w[i];
+  };
+  scan(row_work, pl.qt_ptr);
+  scan(col_work, pl.kt_ptr);
+  balance8(row_work, pl.xcd_rows);
+  balance8(col_work, pl.xcd_cols);
 }
 
 // ------------------------------------------------------------------ kernels
@@ -342,243 +381,161 @@ __device__ __forceinline__ int upper_index(int n, int x, F key) {
   return lo - 1;
 }
 
-__global__ void k_tokens(const DevSeg *__restrict__ segs, int nseg, const Piece *__restrict__ pieces,
-                         int32_t *__restrict__ tok_src, int32_t *__restrict__ tok_meta, int packed) {
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < packed; r += gridDim.x * blockDim.x) {
-    int s = upper_index(nseg, r, [&](int i) { return segs[i].start; });
-    int src = -1, meta = SEG_KIND_PAD;
-    if (s >= 0 && r < segs[s].start + segs[s].len) {
-      const DevSeg d = segs[s];
-      int pos = r - d.start;
-      const Piece *pc = pieces + d.piece_base;
-      int i = upper_index(d.piece_count, pos, [&](int k) { return pc[k].off; });
-      src = pc[i].canon + (pos - pc[i].off);
-      meta = pc[i].meta;
-    }
-    tok_src[r] = src;
-    tok_meta[r] = meta;
-  }
+// Class of the pair (q-tile i, k-tile j <= i) of a segment; 0: no visible pair.
+// Every row of a later tile is after every key, so the pair holds a visible
+// one iff i's first row is before j's latest expiry, and is FULL iff i's last
+// row is before j's earliest and i has all its rows.  A diagonal tile of more
+// than one row holds pairs in both orders.
+__device__ __forceinline__ int tile_class(const TileSpan &q, const TileSpan &k, bool diagonal,
+                                          bool whole, int tile) {
+  if (diagonal) return tile == 1 ? SEG_TILE_FULL : SEG_TILE_PARTIAL;
+  if (q.first_turn >= k.max_exp) return 0;
+  return whole && q.last_turn < k.min_exp ? SEG_TILE_FULL : SEG_TILE_PARTIAL;
 }
 
-__global__ void k_loss_rows(const LossPiece *__restrict__ lp, int nlp, int rows,
-                            int32_t *__restrict__ pred, int32_t *__restrict__ tgt,
-                            int32_t *__restrict__ traj) {
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < rows; r += gridDim.x * blockDim.x) {
-    int i = upper_index(nlp, r, [&](int k) { return lp[k].row_base; });
-    int o = r - lp[i].row_base;
-    pred[r] = lp[i].pos + o - 1;
-    tgt[r] = lp[i].canon + o;
-    traj[r] = lp[i].traj;
-  }
-}
+struct BuildArgs {
+  const DevSeg *segs;
+  const Piece *pieces;
+  const LossPiece *lp;
+  const int32_t *info, *qptr, *kptr;
+  const TileSpan *span;
+  const int64_t *pairs;
+  seg_layout out;
+  int S, P, R, G, nlp, tile;
+  int tok_blocks, loss_blocks, tile_blocks, copy_blocks;
+};
 
-__global__ void k_tile_seg(const DevSeg *__restrict__ segs, int nseg, int ntiles,
-                           int32_t *__restrict__ tile_seg) {
-  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < ntiles; g += gridDim.x * blockDim.x)
-    tile_seg[g] = upper_index(nseg, g, [&](int i) { return segs[i].qbase; });
-}
+constexpr int TOK_BLOCK = 1024;  // rows of a token block
 
-__device__ __forceinline__ int wave_sum_int(int v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ long long wave_sum_ll(long long v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// Classify every lower-triangular tile (i, j <= i) of q-tile g's segment.
-// Visibility of key k to query q (segment-relative rows): k <= q and
-// turn(q) < kexp(k), where kexp = turn(k) + W for screenshot tokens and
-// "never expires" otherwise.  Turns never decrease along a segment, so for a
-// key the most favourable query of a row range is the first one not before it.
-__global__ void __launch_bounds__(256) k_classify(
-    const DevSeg *__restrict__ segs, const int32_t *__restrict__ tile_seg,
-    const int32_t *__restrict__ tok_meta, int W, int tile, uint8_t *__restrict__ cls,
-    int32_t *__restrict__ qcnt, int32_t *__restrict__ kcnt, int64_t *__restrict__ seg_pairs) {
-  const int g = blockIdx.x;
-  const int s = tile_seg[g];
-  const DevSeg d = segs[s];
-  const int i = g - d.qbase;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int32_t *meta = tok_meta + d.start;
-  const int q_lo = i * tile, q_hi = min(d.len, (i + 1) * tile) - 1;
-  const int step_qhi = meta[q_hi] >> 2;
-  uint8_t *row_cls = cls + d.tri_base + (int64_t)i * (i + 1) / 2;
-  long long pairs = 0;
-  int nnz = 0;
-  for (int j = wave; j <= i; j += 4) {
-    const int k_lo = j * tile, k_hi = min(d.len, (j + 1) * tile) - 1;
-    bool any = false, all = true;
-    long long cnt = 0;
-    for (int k = k_lo + lane; k <= k_hi; k += 64) {
-      const int mk = meta[k];
-      const int kexp = ((mk & 3) == SEG_KIND_IMAGE) ? (mk >> 2) + W : INT_MAX;
-      const int qs = max(k, q_lo);
-      if (qs <= q_hi && (meta[qs] >> 2) < kexp) {
-        any = true;
-        // last row in [qs, q_hi] whose turn is < kexp
-        int lo = qs, hi = q_hi;
-        if (kexp != INT_MAX && (step_qhi >= kexp)) {
-          while (lo < hi) {
-            int mid = (lo + hi + 1) >> 1;
-            if ((meta[mid] >> 2) < kexp) lo = mid;
-            else hi = mid - 1;
-          }
-        } else {
-          lo = q_hi;
-        }
-        cnt += lo - qs + 1;
+// The whole layout in one launch; blocks of 256 threads take, in turn, runs of
+// packed rows, runs of loss rows, four q-tiles (CSR rows), four k-tiles
+// (transposed CSR) and runs of the tables that are copied.  Everything is a
+// few MB at most, so latency bounds it: no pass over the result of another,
+// and the class of a tile pair is two compares of its tiles' spans (tested key
+// by key against the token descriptors it took 312 us of the 390 us that the
+// 7B-class batch's build spent in nine kernels; this one takes 24 us).
+__global__ void __launch_bounds__(256) k_build(const BuildArgs a) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int b = blockIdx.x;
+  if (b < a.tok_blocks) {
+    // the rows of a block mostly lie in one segment: search from there
+    const int first = b * TOK_BLOCK, last = min(a.P, first + TOK_BLOCK);
+    const int s0 = max(0, upper_index(a.S, first, [&](int i) { return a.segs[i].start; }));
+    for (int r = first + tid; r < last; r += 256) {
+      int s = s0;
+      while (s + 1 < a.S && a.segs[s + 1].start <= r) ++s;
+      const DevSeg d = a.segs[s];
+      int src = -1, meta = SEG_KIND_PAD;
+      const int pos = r - d.start;
+      if (pos >= 0 && pos < d.len) {
+        const Piece *pc = a.pieces + d.piece_base;
+        const Piece p = pc[upper_index(d.piece_count, pos, [&](int k) { return pc[k].off; })];
+        src = p.canon + (pos - p.off);
+        meta = p.meta;
       }
-      // every row of the tile sees key k: k <= q_lo (causal; a 1x1 diagonal
-      // tile is full) and the last row's turn is before the key's expiry
-      if (!(k <= q_lo && step_qhi < kexp)) all = false;
+      a.out.tok_src[r] = src;
+      a.out.tok_meta[r] = meta;
     }
-    const bool t_any = __any(any);
-    const bool t_all = __all(all) && (q_hi - q_lo + 1 == tile) && (k_hi - k_lo + 1 == tile);
-    const long long t_cnt = wave_sum_ll(cnt);
-    if (lane == 0) {
-      uint8_t c = t_any ? (t_all ? SEG_TILE_FULL : SEG_TILE_PARTIAL) : 0;
-      row_cls[j] = c;
-      if (c) {
-        atomicAdd(&kcnt[d.qbase + j], 1);
-        ++nnz;
-      }
-      pairs += t_cnt;
+    return;
+  }
+  b -= a.tok_blocks;
+  if (b < a.loss_blocks) {
+    const int r = b * 256 + tid;
+    if (r < a.R) {
+      const LossPiece l = a.lp[upper_index(a.nlp, r, [&](int k) { return a.lp[k].row_base; })];
+      const int o = r - l.row_base;
+      a.out.loss_pred_row[r] = l.pos + o - 1;
+      a.out.loss_tgt_src[r] = l.canon + o;
+      a.out.loss_traj[r] = l.traj;
     }
+    return;
   }
-  __shared__ long long sp[4];
-  __shared__ int sn[4];
-  if (lane == 0) {
-    sp[wave] = pairs;
-    sn[wave] = nnz;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    qcnt[g] = sn[0] + sn[1] + sn[2] + sn[3];
-    long long t = sp[0] + sp[1] + sp[2] + sp[3];
-    atomicAdd((unsigned long long *)&seg_pairs[s], (unsigned long long)t);
-  }
-}
-
-// Exclusive scan of n counts into ptr[0..n] (one block of 1024 threads).
-__global__ void __launch_bounds__(1024) k_scan(const int32_t *__restrict__ cnt, int n,
-                                               int32_t *__restrict__ ptr,
-                                               int64_t *__restrict__ total) {
-  __shared__ int part[1024];
-  const int t = threadIdx.x;
-  const int per = (n + 1023) / 1024;
-  const int b = min(n, t * per), e = min(n, b + per);
-  int sum = 0;
-  for (int i = b; i < e; ++i) sum += cnt[i];
-  part[t] = sum;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    int v = t >= o ? part[t - o] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  int run = part[t] - sum;
-  for (int i = b; i < e; ++i) {
-    ptr[i] = run;
-    run += cnt[i];
-  }
-  if (t == 1023) {
-    ptr[n] = part[1023];
-    if (total) *total = part[1023];
-  }
-}
-
-// CSR rows: one wave per q-tile, k-tiles ascending.
-__global__ void __launch_bounds__(64) k_fill_rows(const DevSeg *__restrict__ segs,
-                                                  const int32_t *__restrict__ tile_seg,
-                                                  const uint8_t *__restrict__ cls,
-                                                  const int32_t *__restrict__ ptr,
-                                                  int32_t *__restrict__ col,
-                                                  uint8_t *__restrict__ ccls,
-                                                  int32_t *__restrict__ ord) {
-  const int g = blockIdx.x, lane = threadIdx.x;
-  const DevSeg d = segs[tile_seg[g]];
-  const int i = g - d.qbase;
-  const uint8_t *row = cls + d.tri_base + (int64_t)i * (i + 1) / 2;
-  int out = ptr[g];
-  for (int j0 = 0; j0 <= i; j0 += 64) {
-    const int j = j0 + lane;
-    const uint8_t c = j <= i ? row[j] : 0;
-    const unsigned long long m = __ballot(c != 0);
-    if (c) {
-      const int r = __popcll(m & ((1ull << lane) - 1));
-      col[out + r] = d.qbase + j;
-      ccls[out + r] = c;
-    }
-    out += __popcll(m);
-  }
-  // The walking order of the q-tile-stationary kernels: the same entries,
-  // FULL tiles first and PARTIAL ones after (each ascending), with bit 31
-  // marking PARTIAL.
-  out = ptr[g];
-  for (int pass = 0; pass < 2; ++pass) {
-    const uint8_t want = pass == 0 ? SEG_TILE_FULL : SEG_TILE_PARTIAL;
-    for (int j0 = 0; j0 <= i; j0 += 64) {
-      const int j = j0 + lane;
-      const uint8_t c = j <= i ? row[j] : 0;
-      const unsigned long long m = __ballot(c == want);
-      if (c == want) {
-        const int r = __popcll(m & ((1ull << lane) - 1));
-        ord[out + r] = (int32_t)((unsigned)(d.qbase + j) | (pass ? 0x80000000u : 0u));
-      }
-      out += __popcll(m);
-    }
-  }
-}
-
-// Transposed CSR columns: one wave per k-tile, q-tiles ascending.
-__global__ void __launch_bounds__(64) k_fill_cols(const DevSeg *__restrict__ segs,
-                                                  const int32_t *__restrict__ tile_seg,
-                                                  const uint8_t *__restrict__ cls,
-                                                  const int32_t *__restrict__ ptr,
-                                                  int32_t *__restrict__ rowi,
-                                                  uint8_t *__restrict__ ccls,
-                                                  int32_t *__restrict__ ord) {
-  const int g = blockIdx.x, lane = threadIdx.x;
-  const DevSeg d = segs[tile_seg[g]];
-  const int j = g - d.qbase;
-  const int e0 = ptr[g];
-  int out = e0, nfull = 0;
-  for (int i0 = j; i0 < d.nt; i0 += 64) {
-    const int i = i0 + lane;
-    const uint8_t c = i < d.nt ? cls[d.tri_base + (int64_t)i * (i + 1) / 2 + j] : 0;
-    const unsigned long long m = __ballot(c != 0);
-    if (c) {
-      const int r = __popcll(m & ((1ull << lane) - 1));
-      rowi[out + r] = d.qbase + i;
-      ccls[out + r] = c;
-    }
-    out += __popcll(m);
-    nfull += __popcll(__ballot(c == SEG_TILE_FULL));
-  }
-  // The walking order of the k-tile-stationary kernel: FULL q-tiles first,
-  // then PARTIAL ones, each descending, with bit 31 marking PARTIAL.
-  int rf = 0, rp = 0;  // ascending ranks so far within each class
-  for (int i0 = j; i0 < d.nt; i0 += 64) {
-    const int i = i0 + lane;
-    const uint8_t c = i < d.nt ? cls[d.tri_base + (int64_t)i * (i + 1) / 2 + j] : 0;
-    const unsigned long long mf = __ballot(c == SEG_TILE_FULL);
-    const unsigned long long mp = __ballot(c == SEG_TILE_PARTIAL);
+  b -= a.loss_blocks;
+  if (b < 2 * a.tile_blocks) {
+    const bool cols = b >= a.tile_blocks;
+    const int g = (cols ? b - a.tile_blocks : b) * 4 + wave;
+    if (g >= a.G) return;
+    const int s = upper_index(a.S, g, [&](int i) { return a.segs[i].qbase; });
+    const DevSeg d = a.segs[s];
+    const TileSpan *sp = a.span + d.qbase;
+    const int me = g - d.qbase;
+    const TileSpan mine = sp[me];
     const unsigned long long below = (1ull << lane) - 1;
-    if (c == SEG_TILE_FULL) ord[e0 + nfull - 1 - (rf + __popcll(mf & below))] = d.qbase + i;
-    if (c == SEG_TILE_PARTIAL)
-      ord[out - 1 - (rp + __popcll(mp & below))] =
-          (int32_t)((unsigned)(d.qbase + i) | 0x80000000u);
-    rf += __popcll(mf);
-    rp += __popcll(mp);
+    if (!cols) {
+      // CSR row of q-tile `me`: k-tiles ascending; then the walking order of
+      // the q-tile-stationary kernels: FULL tiles first and PARTIAL ones
+      // after (each ascending), with bit 31 marking PARTIAL
+      const bool whole = (long)(me + 1) * a.tile <= d.len;
+      const int e0 = a.qptr[g];
+      if (lane == 0) a.out.tile_seg[g] = s;
+      int out = e0, nfull = 0;
+      for (int j0 = 0; j0 <= me; j0 += 64) {
+        const int j = j0 + lane;
+        const int c = j <= me ? tile_class(mine, sp[j], j == me, whole, a.tile) : 0;
+        const unsigned long long m = __ballot(c != 0);
+        if (c) {
+          const int at = out + __popcll(m & below);
+          a.out.qt_col[at] = d.qbase + j;
+          a.out.qt_cls[at] = (uint8_t)c;
+        }
+        out += __popcll(m);
+        nfull += __popcll(__ballot(c == SEG_TILE_FULL));
+      }
+      int rf = 0, rp = 0;  // ranks so far within each class
+      for (int j0 = 0; j0 <= me; j0 += 64) {
+        const int j = j0 + lane;
+        const int c = j <= me ? tile_class(mine, sp[j], j == me, whole, a.tile) : 0;
+        const unsigned long long mf = __ballot(c == SEG_TILE_FULL), mp = __ballot(c == SEG_TILE_PARTIAL);
+        if (c == SEG_TILE_FULL) a.out.qt_ord[e0 + rf + __popcll(mf & below)] = d.qbase + j;
+        if (c == SEG_TILE_PARTIAL)
+          a.out.qt_ord[e0 + nfull + rp + __popcll(mp & below)] =
+              (int32_t)((unsigned)(d.qbase + j) | 0x80000000u);
+        rf += __popcll(mf);
+        rp += __popcll(mp);
+      }
+    } else {
+      // transposed CSR of k-tile `me`: its listed q-tiles me .. me + n - 1,
+      // ascending; then the walking order of the k-tile-stationary kernel:
+      // FULL q-tiles first, then PARTIAL ones, each descending, with bit 31
+      // marking PARTIAL
+      const int e0 = a.kptr[g], n = a.kptr[g + 1] - e0;
+      auto cls = [&](int k) {
+        const int i = me + k;
+        return k < n ? tile_class(sp[i], mine, k == 0, (long)(i + 1) * a.tile <= d.len, a.tile) : 0;
+      };
+      int nfull = 0;
+      for (int k0 = 0; k0 < n; k0 += 64) {
+        const int c = cls(k0 + lane);
+        if (c) {
+          a.out.kt_row[e0 + k0 + lane] = g + k0 + lane;
+          a.out.kt_cls[e0 + k0 + lane] = (uint8_t)c;
+        }
+        nfull += __popcll(__ballot(c == SEG_TILE_FULL));
+      }
+      int rf = 0, rp = 0;  // ascending ranks so far within each class
+      for (int k0 = 0; k0 < n; k0 += 64) {
+        const int c = cls(k0 + lane);
+        const unsigned long long mf = __ballot(c == SEG_TILE_FULL), mp = __ballot(c == SEG_TILE_PARTIAL);
+        if (c == SEG_TILE_FULL) a.out.kt_ord[e0 + nfull - 1 - (rf + __popcll(mf & below))] = g + k0 + lane;
+        if (c == SEG_TILE_PARTIAL)
+          a.out.kt_ord[e0 + n - 1 - (rp + __popcll(mp & below))] =
+              (int32_t)((unsigned)(g + k0 + lane) | 0x80000000u);
+        rf += __popcll(mf);
+        rp += __popcll(mp);
+      }
+    }
+    return;
   }
-}
-
-int grid_for(int64_t n, int block = 256) {
-  int64_t g = (n + block - 1) / block;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(g, 65536));
+  b -= 2 * a.tile_blocks;
+  for (int i = b * 256 + tid; i <= a.G; i += a.copy_blocks * 256) {
+    a.out.qt_ptr[i] = a.qptr[i];
+    a.out.kt_ptr[i] = a.kptr[i];
+  }
+  for (int i = b * 256 + tid; i < a.S * SEG_INFO_FIELDS; i += a.copy_blocks * 256)
+    a.out.seg_info[i] = a.info[i];
+  for (int i = b * 256 + tid; i < a.S; i += a.copy_blocks * 256) a.out.seg_pairs[i] = a.pairs[i];
+  if (b == 0 && tid == 0) *a.out.tile_nnz = a.qptr[a.G];
 }
 
 }  // namespace
@@ -601,6 +558,7 @@ extern "C" seg_status seg_build_layout(const seg_problem *p, const seg_sizes *sz
   return guarded([&] {
     SEG_CHECK(sz != nullptr && out != nullptr, SEG_ERR_ARG, "sizes or layout is NULL");
     Plan pl = make_plan(p);
+    plan_tiles(p, pl);
     SEG_CHECK(std::memcmp(&pl.sz, sz, sizeof(seg_sizes)) == 0, SEG_ERR_ARG,
               "sizes do not match seg_layout_query of this problem");
     SEG_CHECK(ws_bytes >= sz->workspace_bytes, SEG_ERR_WORKSPACE,
@@ -634,54 +592,48 @@ extern "C" seg_status seg_build_layout(const seg_problem *p, const seg_sizes *sz
       }
       return;
     }
-    BuildWs w = build_ws_layout(*sz, pl.pieces.size(), pl.lpieces.size());
-    char *base = static_cast<char *>(ws);
-    DevSeg *d_segs = reinterpret_cast<DevSeg *>(base + w.dseg);
-    Piece *d_pieces = reinterpret_cast<Piece *>(base + w.piece);
-    LossPiece *d_lp = reinterpret_cast<LossPiece *>(base + w.lpiece);
-    uint8_t *d_cls = reinterpret_cast<uint8_t *>(base + w.cls);
-    int32_t *d_qcnt = reinterpret_cast<int32_t *>(base + w.qcnt);
-    int32_t *d_kcnt = reinterpret_cast<int32_t *>(base + w.kcnt);
-
-    SEG_HIP(hipMemcpyAsync(out->seg_info, pl.seg_info.data(), sizeof(int32_t) * pl.seg_info.size(),
-                           hipMemcpyHostToDevice, stream));
-    SEG_HIP(hipMemcpyAsync(d_segs, pl.dsegs.data(), sizeof(DevSeg) * pl.dsegs.size(),
-                           hipMemcpyHostToDevice, stream));
-    SEG_HIP(hipMemcpyAsync(d_pieces, pl.pieces.data(), sizeof(Piece) * pl.pieces.size(),
-                           hipMemcpyHostToDevice, stream));
-    if (!pl.lpieces.empty())
-      SEG_HIP(hipMemcpyAsync(d_lp, pl.lpieces.data(), sizeof(LossPiece) * pl.lpieces.size(),
-                             hipMemcpyHostToDevice, stream));
+    const BuildWs w = build_ws_layout(*sz, pl.pieces.size(), pl.lpieces.size());
+    std::vector<char> tab(w.total);
+    auto put = [&](size_t off, const auto &v) {
+      if (!v.empty()) std::memcpy(tab.data() + off, v.data(), v.size() * sizeof(v[0]));
+    };
+    put(w.dseg, pl.dsegs);
+    put(w.piece, pl.pieces);
+    put(w.lpiece, pl.lpieces);
+    put(w.info, pl.seg_info);
+    put(w.span, pl.spans);
+    put(w.qptr, pl.qt_ptr);
+    put(w.kptr, pl.kt_ptr);
+    put(w.pairs, pl.seg_pairs);
+    SEG_HIP(hipMemcpyAsync(ws, tab.data(), w.total, hipMemcpyHostToDevice, stream));
     // the host tables are locals of this call: wait until they have been read
     SEG_HIP(hipStreamSynchronize(stream));
 
     ProfScope prof("layout", stream);
-    SEG_HIP(hipMemsetAsync(d_kcnt, 0, sizeof(int32_t) * G, stream));
-    SEG_HIP(hipMemsetAsync(out->seg_pairs, 0, sizeof(int64_t) * S, stream));
-    if (P > 0) {
-      k_tokens<<<grid_for(P), 256, 0, stream>>>(d_segs, S, d_pieces, out->tok_src, out->tok_meta, P);
-      SEG_LAUNCH_CHECK();
-    }
-    if (R > 0) {
-      k_loss_rows<<<grid_for(R), 256, 0, stream>>>(d_lp, (int)pl.lpieces.size(), R,
-                                                   out->loss_pred_row, out->loss_tgt_src,
-                                                   out->loss_traj);
-      SEG_LAUNCH_CHECK();
-    }
-    k_tile_seg<<<grid_for(G), 256, 0, stream>>>(d_segs, S, G, out->tile_seg);
-    SEG_LAUNCH_CHECK();
-    k_classify<<<G, 256, 0, stream>>>(d_segs, out->tile_seg, out->tok_meta, Wv, p->tile,
-                                      d_cls, d_qcnt, d_kcnt, out->seg_pairs);
-    SEG_LAUNCH_CHECK();
-    k_scan<<<1, 1024, 0, stream>>>(d_qcnt, G, out->qt_ptr, out->tile_nnz);
-    SEG_LAUNCH_CHECK();
-    k_scan<<<1, 1024, 0, stream>>>(d_kcnt, G, out->kt_ptr, nullptr);
-    SEG_LAUNCH_CHECK();
-    k_fill_rows<<<G, 64, 0, stream>>>(d_segs, out->tile_seg, d_cls, out->qt_ptr, out->qt_col,
-                                      out->qt_cls, out->qt_ord);
-    SEG_LAUNCH_CHECK();
-    k_fill_cols<<<G, 64, 0, stream>>>(d_segs, out->tile_seg, d_cls, out->kt_ptr, out->kt_row,
-                                      out->kt_cls, out->kt_ord);
+    const char *base = static_cast<const char *>(ws);
+    BuildArgs a{};
+    a.segs = reinterpret_cast<const DevSeg *>(base + w.dseg);
+    a.pieces = reinterpret_cast<const Piece *>(base + w.piece);
+    a.lp = reinterpret_cast<const LossPiece *>(base + w.lpiece);
+    a.info = reinterpret_cast<const int32_t *>(base + w.info);
+    a.qptr = reinterpret_cast<const int32_t *>(base + w.qptr);
+    a.kptr = reinterpret_cast<const int32_t *>(base + w.kptr);
+    a.span = reinterpret_cast<const TileSpan *>(base + w.span);
+    a.pairs = reinterpret_cast<const int64_t *>(base + w.pairs);
+    a.out = *out;
+    a.S = S;
+    a.P = P;
+    a.R = R;
+    a.G = G;
+    a.nlp = (int)pl.lpieces.size();
+    a.tile = p->tile;
+    a.tok_blocks = (int)((P + (int64_t)TOK_BLOCK - 1) / TOK_BLOCK);
+    a.loss_blocks = (int)((R + 255LL) / 256);
+    a.tile_blocks = (int)((G + 3LL) / 4);
+    a.copy_blocks = (int)std::min<int64_t>(64, (G + 256LL) / 256);
+    const int64_t blocks = (int64_t)a.tok_blocks + a.loss_blocks + 2LL * a.tile_blocks + a.copy_blocks;
+    SEG_CHECK(blocks <= INT_MAX, SEG_ERR_CAPACITY, "layout too large");
+    k_build<<<(unsigned)blocks, 256, 0, stream>>>(a);
     SEG_LAUNCH_CHECK();
   });
 }
