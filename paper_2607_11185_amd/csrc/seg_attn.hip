@@ -105,10 +105,32 @@ __device__ __forceinline__ u16x8 load8_bf(const float *p) {
 
 // ------------------------------------------------------------- prep kernels
 
-// fp32 -> bf16 copy (row-major, any shape)
-__global__ void k_f32_to_bf16(const float *__restrict__ x, unsigned short *__restrict__ y, long n) {
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-    y[i] = f2bf_bits(x[i]);
+// bf16 copies of a call's fp32 tensors, all in one launch (a launch of its own
+// for each of seven tensors was a fifth of a small call's time), 8 elements a
+// thread (every size is a multiple of d; 16-byte loads need only the 4-byte
+// alignment a float has); and zeros in `zero`.
+struct ToBf16 {
+  const float *x[4];
+  unsigned short *y[4];
+  long end[4];  // in 8-element chunks, running over the tensors
+};
+__global__ void __launch_bounds__(256) k_f32_to_bf16(const ToBf16 t, unsigned *__restrict__ zero,
+                                                     long nzero) {
+  const long at = (long)blockIdx.x * 256 + threadIdx.x, step = (long)gridDim.x * 256;
+  for (long i = at; i < nzero; i += step) zero[i] = 0;
+  for (long i = at; i < t.end[3]; i += step) {
+    const float *x = t.x[0];
+    unsigned short *y = t.y[0];
+    long first = 0;
+#pragma unroll
+    for (int k = 1; k < 4; ++k)
+      if (i >= t.end[k - 1]) {
+        x = t.x[k];
+        y = t.y[k];
+        first = t.end[k - 1];
+      }
+    *reinterpret_cast<u16x8 *>(y + (i - first) * 8) = load8_bf(x + (i - first) * 8);
+  }
 }
 
 // Delta[h][row] = sum_d dO[row][h][d] * O[row][h][d]  (D/8 lanes per (row, head)),
@@ -1394,10 +1416,21 @@ void check_common(const seg_layout *L, const seg_sizes *sz, seg_dtype dt, int hq
             (long long)sz->packed_tokens, hq);
 }
 
-void to_bf16(const void *x, unsigned short *y, long n, hipStream_t st) {
-  int grid = (int)std::min<long>(65536, (n + 255) / 256);
+// q, k, v and (backward) dO as bf16 in the workspace
+void to_bf16(const void *q, const void *k, const void *v, const void *d_o, unsigned short *q2,
+             unsigned short *k2, unsigned short *v2, unsigned short *do2, long nq, long nkv,
+             unsigned *zero, long nzero, hipStream_t st) {
+  ToBf16 t{{static_cast<const float *>(q), static_cast<const float *>(k), static_cast<const float *>(v),
+            static_cast<const float *>(d_o)},
+           {q2, k2, v2, do2},
+           {}};
+  t.end[0] = nq / 8;
+  t.end[1] = t.end[0] + nkv / 8;
+  t.end[2] = t.end[1] + nkv / 8;
+  t.end[3] = t.end[2] + (d_o ? nq / 8 : 0);
   ProfScope prof("attn_prep", st);
-  k_f32_to_bf16<<<std::max(1, grid), 256, 0, st>>>(static_cast<const float *>(x), y, n);
+  k_f32_to_bf16<<<(int)std::max<long>(1, std::min<long>(16384, (t.end[3] + 255) / 256)), 256, 0, st>>>(
+      t, zero, nzero);
   SEG_LAUNCH_CHECK();
 }
 
@@ -1407,7 +1440,7 @@ void fwd_impl(const seg_layout *L, const seg_sizes *sz, int hq, int hkv, float s
               float *lse, unsigned *kn2, hipStream_t st) {
   const int G = sz->num_qtiles;
   ProfScope prof("attn_fwd", st);
-  fill32(kn2, (long)sz->num_segments * hkv, 0u, st);
+  if (sizeof(TO) == 2) fill32(kn2, (long)sz->num_segments * hkv, 0u, st);  // else cleared by to_bf16
   k_key_norm<D><<<dim3(G, hkv), 256, 0, st>>>(k, L->seg_info, L->tile_seg, hkv, kn2);
   SEG_LAUNCH_CHECK();
   const XcdRanges xr = xcd_ranges(L->xcd_rows);
@@ -1488,9 +1521,8 @@ extern "C" seg_status seg_attn_fwd(const seg_layout *L, const seg_sizes *sz, seg
       unsigned short *q2 = reinterpret_cast<unsigned short *>(base + w.qb);
       unsigned short *k2 = reinterpret_cast<unsigned short *>(base + w.kb);
       unsigned short *v2 = reinterpret_cast<unsigned short *>(base + w.vb);
-      to_bf16(q, q2, P * hq * d, stream);
-      to_bf16(k, k2, P * hkv * d, stream);
-      to_bf16(v, v2, P * hkv * d, stream);
+      to_bf16(q, k, v, nullptr, q2, k2, v2, nullptr, P * hq * d, P * hkv * d, kn2,
+              (long)sz->num_segments * hkv, stream);
       qb = q2;
       kb = k2;
       vb = v2;
@@ -1532,10 +1564,7 @@ extern "C" seg_status seg_attn_bwd(const seg_layout *L, const seg_sizes *sz, seg
       unsigned short *k2 = reinterpret_cast<unsigned short *>(base + w.kb);
       unsigned short *v2 = reinterpret_cast<unsigned short *>(base + w.vb);
       unsigned short *do2 = reinterpret_cast<unsigned short *>(base + w.dob);
-      to_bf16(q, q2, P * hq * d, stream);
-      to_bf16(k, k2, P * hkv * d, stream);
-      to_bf16(v, v2, P * hkv * d, stream);
-      to_bf16(d_o, do2, P * hq * d, stream);
+      to_bf16(q, k, v, d_o, q2, k2, v2, do2, P * hq * d, P * hkv * d, nullptr, 0, stream);
       const float *o32 = static_cast<const float *>(o), *do32 = static_cast<const float *>(d_o);
       if (d == 128)
         bwd_impl<128, float, float>(L, sz, hq, hkv, softmax_scale, q2, k2, v2, do2, o32, do32,
