@@ -30,7 +30,7 @@ constexpr float LN2 = 0.6931471805599453f;
 // Epilogue of the logits GEMM (M = vocab, N = rows): writes zT, captures the
 // target logit and the per-(row, vocab tile) max / sum-exp partials.
 struct EpiLogits {
-  float *zt;        // [M][ldz] fp32
+  float *zt;        // [M][ldz] fp32, or NULL (a forward-only call needs the statistics alone)
   long ldz;
   float2 *stats;    // [ceil(M/128) slabs][N]: (max, sum exp(z - max)) in log2 units
   int nrows;        // N
@@ -69,7 +69,7 @@ struct EpiLogits {
           const int k = 16 * i + r;
           const float z = acc[i][j][r] * scale;
           if (WHOLE || k < left) {
-            if (nok) zp[(long)k * ldz] = z;
+            if (nok && zt) zp[(long)k * ldz] = z;
             mx = fmaxf(mx, z);
           }
         }
@@ -101,6 +101,13 @@ struct EpiLogits {
   }
 };
 
+// The row statistics and the loss of LOSS_ROWS rows per block.  16 threads
+// share a row, each taking every 16th slab, so a block reads 128-byte pieces
+// of the slab-major statistics (one block per row read 8 of every 64 bytes: 89
+// us for 7,680 rows x 1,187 slabs, now 26); their results are combined
+// in a fixed order.
+constexpr int LOSS_ROWS = 16;
+
 __global__ void __launch_bounds__(256) k_row_loss(
     const float2 *__restrict__ stats, int ntiles, int rows, const float *__restrict__ ztgt,
     const float *__restrict__ old_logp, const float *__restrict__ ref_logp,
@@ -108,36 +115,31 @@ __global__ void __launch_bounds__(256) k_row_loss(
     seg_loss_cfg cfg, float *__restrict__ logp, float *__restrict__ loss_tok,
     uint8_t *__restrict__ clipped, float *__restrict__ kl_tok, float *__restrict__ lse_out,
     float *__restrict__ g_out) {
-  __shared__ float2 red[256];
-  const int r = blockIdx.x, t = threadIdx.x;
+  constexpr int SL = 256 / LOSS_ROWS;
+  __shared__ float2 red[SL][LOSS_ROWS];
+  const int t = threadIdx.x % LOSS_ROWS, part = threadIdx.x / LOSS_ROWS;
+  const int r = blockIdx.x * LOSS_ROWS + t;
   float mx = -INFINITY, sm = 0.f;
-  for (int i = t; i < ntiles; i += 256) {
-    const float2 p = stats[(long)i * rows + r];
-    if (p.x == -INFINITY) continue;
-    if (p.x > mx) {
-      sm = sm * exp2f(mx - p.x) + p.y;
-      mx = p.x;
-    } else {
-      sm += p.y * exp2f(p.x - mx);
+  if (r < rows) {
+#pragma unroll 4
+    for (int i = part; i < ntiles; i += SL) {
+      const float2 p = stats[(long)i * rows + r];
+      const float m2 = fmaxf(mx, p.x);
+      // (an all -inf slab, or no slab yet, adds nothing)
+      sm = (mx == -INFINITY ? 0.f : sm * exp2f(mx - m2)) + (p.x == -INFINITY ? 0.f : p.y * exp2f(p.x - m2));
+      mx = m2;
     }
   }
-  red[t] = make_float2(mx, sm);
+  red[part][t] = make_float2(mx, sm);
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) {
-      const float2 a = red[t], b = red[t + o];
-      const float m2 = fmaxf(a.x, b.x);
-      float s2 = 0.f;
-      if (m2 != -INFINITY) {
-        if (a.x != -INFINITY) s2 += a.y * exp2f(a.x - m2);
-        if (b.x != -INFINITY) s2 += b.y * exp2f(b.x - m2);
-      }
-      red[t] = make_float2(m2, s2);
+  if (part == 0 && r < rows) {
+    for (int k = 1; k < SL; ++k) {
+      const float2 p = red[k][t];
+      const float m2 = fmaxf(mx, p.x);
+      sm = (mx == -INFINITY ? 0.f : sm * exp2f(mx - m2)) + (p.x == -INFINITY ? 0.f : p.y * exp2f(p.x - m2));
+      mx = m2;
     }
-    __syncthreads();
-  }
-  if (t == 0) {
-    const float lse = (red[0].x + log2f(red[0].y)) * LN2;
+    const float lse = (mx + log2f(sm)) * LN2;
     const float lp = ztgt[r] - lse;
     // an out-of-range trajectory index yields NaN rather than a stray read
     const int tj = row_traj[r];
@@ -170,12 +172,14 @@ __global__ void __launch_bounds__(256) k_row_loss(
   }
 }
 
-// loss_sum = loss_scale * sum(loss_tok), fixed-order reduction in one block.
-__global__ void __launch_bounds__(256) k_loss_sum(const float *__restrict__ loss_tok, int rows,
-                                                  float scale, float *__restrict__ out) {
+// loss_sum = loss_scale * sum(loss_tok), fixed-order reduction by one block of
+// 256 threads.
+__device__ __forceinline__ void loss_sum_block(const float *__restrict__ loss_tok, int rows,
+                                               float scale, float *__restrict__ out) {
   __shared__ double red[256];
   const int t = threadIdx.x;
   double s = 0.0;
+#pragma unroll 8
   for (int i = t; i < rows; i += 256) s += (double)loss_tok[i];
   red[t] = s;
   __syncthreads();
@@ -186,17 +190,38 @@ __global__ void __launch_bounds__(256) k_loss_sum(const float *__restrict__ loss
   if (t == 0) *out = (float)(red[0] * (double)scale);
 }
 
+__global__ void __launch_bounds__(256) k_loss_sum(const float *__restrict__ loss_tok, int rows,
+                                                  float scale, float *__restrict__ out) {
+  loss_sum_block(loss_tok, rows, scale, out);
+}
+
 // dzT = g[r] * (onehot(target[r]) - exp(z - lse[r])) from zT [V][Rp] to bf16
 // [V][Rp], zero in the padded columns.  Bound by HBM (6 bytes an element):
 // a thread keeps lse, g and target of its 8 columns in registers and walks
-// down the vocabulary rows of its block with 16-byte accesses.
-constexpr int DZ_COLS = 256, DZ_ROWS = 64;  // of a block of 256 threads
+// down the vocabulary rows of its block with 16-byte accesses.  One more row of
+// the grid's blocks has its first block form loss_sum.
+constexpr int DZ_COLS = 256;  // of a block of 256 threads
 
-__global__ void __launch_bounds__(256) k_dz(const float *__restrict__ zt, int V, int R, int Rp,
+// Vocabulary rows per block: about 1,024 blocks, and no longer ones than
+// hide the loads of lse, g and target (7,680 rows x 151,936: 1.86 ms with 32
+// rows, 1.34 with 64, 1.31 with 256; 1,024 x 32,000: 70 us with 24, 45 with
+// 64).
+inline int dz_rows(int V, int Rp) {
+  const long r = (long)V * ((Rp + DZ_COLS - 1) / DZ_COLS) / 1024 / 8 * 8;
+  return (int)std::min<long>(128, std::max<long>(8, r));
+}
+
+__global__ void __launch_bounds__(256) k_dz(const float *__restrict__ zt, int V, int R, int Rp, int vrows,
                                             const float *__restrict__ lse,
                                             const float *__restrict__ g,
                                             const int32_t *__restrict__ target,
-                                            unsigned short *__restrict__ dzt) {
+                                            unsigned short *__restrict__ dzt,
+                                            const float *__restrict__ loss_tok, float loss_scale,
+                                            float *__restrict__ loss_sum) {
+  if (blockIdx.y == gridDim.y - 1) {
+    if (blockIdx.x == 0) loss_sum_block(loss_tok, R, loss_scale, loss_sum);
+    return;
+  }
   const int r0 = blockIdx.x * DZ_COLS + (threadIdx.x & 31) * 8;
   if (r0 >= Rp) return;  // Rp is a multiple of 32
   float l[8], gr[8];
@@ -208,9 +233,9 @@ __global__ void __launch_bounds__(256) k_dz(const float *__restrict__ zt, int V,
     gr[j] = ok ? g[r0 + j] : 0.f;
     tg[j] = ok ? target[r0 + j] : -1;
   }
-  const int v1 = min(V, (int)(blockIdx.y + 1) * DZ_ROWS);
+  const int v1 = min(V, (int)(blockIdx.y + 1) * vrows);
 #pragma unroll 4
-  for (int v = blockIdx.y * DZ_ROWS + (threadIdx.x >> 5); v < v1; v += 8) {
+  for (int v = blockIdx.y * vrows + (threadIdx.x >> 5); v < v1; v += 8) {
     const f32x4 *src = reinterpret_cast<const f32x4 *>(zt + (long)v * Rp + r0);
     const f32x4 a = src[0], b = src[1];
     u16x8 o;
@@ -235,16 +260,51 @@ __global__ void __launch_bounds__(256) k_sum_parts(const float *__restrict__ par
   }
 }
 
-// y[r][:] = x[rowmap[r]][:] as bf16 (rows < rows_pad are zero beyond rows).
+// Preparation of a call in one launch: the gathered action rows as bf16
+// (y[r] = h[rowmap[r]], zero from `rows` to rows_pad), for fp32 inputs the
+// projection as bf16 (wb), and NaN in the target logits (a target outside the
+// vocabulary keeps it).  8 elements a thread where `vec` (the tensors start on
+// 16-byte boundaries; cols is a multiple of 8), else one by one.
 template <class TI>
-__global__ void k_gather_rows(const TI *__restrict__ x, long ldx, const int32_t *__restrict__ rowmap,
-                              int rows, int rows_pad, int cols, unsigned short *__restrict__ y) {
-  const long n = (long)rows_pad * cols;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    const int r = (int)(i / cols), c = (int)(i % cols);
-    unsigned short b = 0;
-    if (r < rows) b = load_bf(x, (long)(rowmap ? rowmap[r] : r) * ldx + c);
-    y[i] = b;
+__device__ __forceinline__ u16x8 load8(const TI *p, bool vec) {
+  u16x8 r;
+  if (vec && sizeof(TI) == 2) return *reinterpret_cast<const u16x8 *>(p);
+  if (vec) {
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(p), b = *reinterpret_cast<const f32x4 *>(p + 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      r[j] = f2bf_bits(a[j]);
+      r[4 + j] = f2bf_bits(b[j]);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) r[j] = load_bf(p, j);
+  }
+  return r;
+}
+
+template <class TI>
+__global__ void __launch_bounds__(256) k_lp_prep(const TI *__restrict__ h,
+                                                 const int32_t *__restrict__ rowmap, int rows,
+                                                 int rows_pad, int cols, bool hvec,
+                                                 unsigned short *__restrict__ y,
+                                                 const TI *__restrict__ w, long w8, bool wvec,
+                                                 unsigned short *__restrict__ wb,
+                                                 float *__restrict__ ztgt) {
+  const unsigned c8 = cols / 8;
+  const long n = (long)rows_pad * c8, step = (long)gridDim.x * 256;
+  const long at = (long)blockIdx.x * 256 + threadIdx.x;
+  for (long i = at; i < rows_pad; i += step) ztgt[i] = __builtin_nanf("");
+  for (long i = at; i < n; i += step) {
+    const int r = n >> 32 ? (int)(i / c8) : (int)((unsigned)i / c8);
+    const long c = i - (long)r * c8;
+    u16x8 v = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    if (r < rows) v = load8(h + (long)(rowmap ? rowmap[r] : r) * cols + c * 8, hvec);
+    *reinterpret_cast<u16x8 *>(y + i * 8) = v;
+  }
+  if constexpr (sizeof(TI) == 4) {
+    for (long i = at; i < w8; i += step)
+      *reinterpret_cast<u16x8 *>(wb + i * 8) = load8(w + i * 8, wvec);
   }
 }
 
@@ -314,31 +374,21 @@ void logprob_impl(int rows, int H, int V, const TI *h, const int32_t *row_index,
   float *g = reinterpret_cast<float *>(base + L.g);
   unsigned short *dzt = reinterpret_cast<unsigned short *>(base + L.dzt);
 
-  // gathered action rows (bf16)
-  {
-    ProfScope prof("lp_prep", st);
-    const long n = (long)Rp * H;
-    k_gather_rows<TI><<<(int)std::min<long>(65536, (n + 255) / 256), 256, 0, st>>>(
-        h, H, row_index, rows, Rp, H, hb);
-    SEG_LAUNCH_CHECK();
-  }
   const unsigned short *wb;
-  if constexpr (sizeof(TI) == 4) {
-    unsigned short *w2 = reinterpret_cast<unsigned short *>(base + L.wb);
-    const long n = (long)V * H;
+  {
+    unsigned short *w2 = sizeof(TI) == 4 ? reinterpret_cast<unsigned short *>(base + L.wb) : nullptr;
+    const long n8 = (long)Rp * (H / 8), w8 = sizeof(TI) == 4 ? (long)V * (H / 8) : 0;
+    auto vec = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
     ProfScope prof("lp_prep", st);
-    k_gather_rows<TI><<<(int)std::min<long>(65536, (n + 255) / 256), 256, 0, st>>>(
-        w, H, nullptr, V, V, H, w2);
+    k_lp_prep<TI><<<(int)std::min<long>(16384, (std::max(n8, w8) + 255) / 256), 256, 0, st>>>(
+        h, row_index, rows, Rp, H, vec(h), hb, w, w8, vec(w), w2, ztgt);
     SEG_LAUNCH_CHECK();
-    wb = w2;
-  } else {
-    wb = reinterpret_cast<const unsigned short *>(w);
+    wb = w2 ? w2 : reinterpret_cast<const unsigned short *>(w);
   }
   // 1. logits zT = s * W h^T with partial softmax stats; the target logit
   //    stays NaN for a target outside [0, vocab)
-  fill32(ztgt, Rp, 0xffffffffu, st);
   {
-    EpiLogits e{zt, Rp, stats, rows, target, ztgt, cfg.logit_scale};
+    EpiLogits e{cfg.want_grad ? zt : nullptr, Rp, stats, rows, target, ztgt, cfg.logit_scale};
     ProfScope prof("logits", st);
     gemm::Problems<EpiLogits, 1, 1> g{{{wb}}, {{hb}}, {{H}}, {{H}}, {H}, {V}, {rows}, {e}, {}, 1,
                                       0x7fffffff};
@@ -347,18 +397,21 @@ void logprob_impl(int rows, int H, int V, const TI *h, const int32_t *row_index,
   // 2. per-row loss
   {
   ProfScope prof("row_loss", st);
-  k_row_loss<<<rows, 256, 0, st>>>(stats, L.ntiles, rows, ztgt, old_logp, ref_logp, adv, row_traj,
+  k_row_loss<<<(rows + LOSS_ROWS - 1) / LOSS_ROWS, 256, 0, st>>>(stats, L.ntiles, rows, ztgt, old_logp, ref_logp, adv, row_traj,
                                    num_traj, cfg, logp, loss_tok, clipped, kl_tok, lse, g);
   SEG_LAUNCH_CHECK();
-  k_loss_sum<<<1, 256, 0, st>>>(loss_tok, rows, cfg.loss_scale, loss_sum);
-  SEG_LAUNCH_CHECK();
+  if (!cfg.want_grad) {
+    k_loss_sum<<<1, 256, 0, st>>>(loss_tok, rows, cfg.loss_scale, loss_sum);
+    SEG_LAUNCH_CHECK();
+    return;
   }
-  if (!cfg.want_grad) return;
+  }
   // 3. dz
   {
     ProfScope prof("dz", st);
-    k_dz<<<dim3((Rp + DZ_COLS - 1) / DZ_COLS, (V + DZ_ROWS - 1) / DZ_ROWS), 256, 0, st>>>(
-        zt, V, rows, Rp, lse, g, target, dzt);
+    const int vr = dz_rows(V, Rp);
+    k_dz<<<dim3((Rp + DZ_COLS - 1) / DZ_COLS, (V + vr - 1) / vr + 1), 256, 0, st>>>(
+        zt, V, rows, Rp, vr, lse, g, target, dzt, loss_tok, cfg.loss_scale, loss_sum);
     SEG_LAUNCH_CHECK();
   }
   // 4. dH = s * dz W: A = dz^T [V][Rp], B = W [V][H], contracting over the
