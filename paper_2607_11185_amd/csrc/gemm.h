@@ -5,6 +5,7 @@
 // thread with its accumulators and a Tile that says where they sit.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -351,9 +352,10 @@ __device__ __forceinline__ void tile_of(int idx, int nM, int nN, int &mt, int &n
 // wave of one is filled by the next); each sums NS products over their own K:
 //   C_p = sum_s A_ps B_ps^T
 // lda, ldb multiples of 8 (and at least the operand's width); N operands need
-// K a multiple of 8; 256 * ld * 2 < 2^30 (N), 64 * ld * 2 < 2^31 (T).  With
-// NS = 1 the K range may be cut into `splits` parts of k_part rows (a multiple
-// of 64), each a set of tiles of its own: the epilogue then gets partial sums.
+// K a multiple of 8; 256 * ld * 2 < 2^30 (N), 64 * ld * 2 < 2^31 (T).  The
+// steps of 64 of the K ranges, in order, may be cut into `splits` parts of
+// `part` steps, each a set of tiles of its own: the epilogue then gets partial
+// sums.
 template <class Epi, int NP, int NS>
 struct Problems {
   const unsigned short *A[NP][NS], *B[NP][NS];
@@ -362,7 +364,7 @@ struct Problems {
   int M[NP], N[NP];
   Epi ep[NP];
   int start[NP + 1];  // first tile of each problem; start[NP] = all tiles
-  int splits, k_part;
+  int splits, part;
 };
 
 #define GEMM_FENCE() asm volatile("" ::: "memory")
@@ -375,11 +377,8 @@ __global__ void __launch_bounds__(THREADS, 1) k_gemm(const Problems<Epi, NP, NS>
   __shared__ __attribute__((aligned(1024))) char lds[LDS_B + SB * SLOTS_B];
   int idx = xcd_index(g.start[NP] * g.splits);
   if (idx >= g.start[NP] * g.splits) return;
-  int split = 0;
-  if constexpr (NS == 1) {
-    split = idx / g.start[NP];
-    idx -= split * g.start[NP];
-  }
+  const int split = idx / g.start[NP];
+  idx -= split * g.start[NP];
   // the problem's fields by unrolled selects (no dynamic indexing of the
   // kernel argument, which would copy it to scratch)
   int M = g.M[0], N = g.N[0], first = 0;
@@ -421,7 +420,6 @@ __global__ void __launch_bounds__(THREADS, 1) k_gemm(const Problems<Epi, NP, NS>
     if (grp == 0) ldr.init<TA, BM>(pA[s], la[s], m0, M, w4, lane);
     else ldr.init<TB, BN>(pB[s], lb[s], n0, N, w4, lane);
   };
-  open(0);
   Frag<TA, BM, 2 * TM> fA;
   Frag<TB, BN, 4> fB;
   fA.init(0, wm * 32 * TM, lane);
@@ -433,15 +431,21 @@ __global__ void __launch_bounds__(THREADS, 1) k_gemm(const Problems<Epi, NP, NS>
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{};
 
-  int nk = 0, seg = 0, k_next = 0, K_seg = g.K[0];
-  if constexpr (NS == 1) {
-    k_next = split * g.k_part;
-    K_seg = min(K_seg, k_next + g.k_part);
-    nk = (K_seg - k_next + BK - 1) / BK;
-  } else {
+  // the part's first step and its number of steps
+  int nk = 0, seg = 0, k_next = split * g.part * BK, K_seg = g.K[0];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) nk += (g.K[s] + BK - 1) / BK;
-  }
+  for (int s = 0; s < NS; ++s) nk += (g.K[s] + BK - 1) / BK;
+  nk = min(g.part, nk - split * g.part);
+#pragma unroll
+  for (int s = 0; s + 1 < NS; ++s)
+    if (seg == s && k_next >= g.K[s]) {
+      k_next -= (g.K[s] + BK - 1) / BK * BK;
+      K_seg = g.K[s + 1];
+      seg = s + 1;
+    }
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    if (s == seg) open(s);
   const unsigned base = (unsigned)(unsigned long)(__attribute__((address_space(3))) char *)lds;
   // sets up the group's next step of loads
   auto prep = [&]() __attribute__((always_inline)) {
@@ -552,14 +556,14 @@ __global__ void __launch_bounds__(THREADS, 1) k_gemm(const Problems<Epi, NP, NS>
                lds + wave * (int)(sizeof(lds) / 8)});
 }
 
-inline int tiles_of(int M, int N, int TM) {
+inline long tiles_of(long M, long N, int TM) {
   return M <= 0 || N <= 0 ? 0 : ((M + bm_of(TM) - 1) / bm_of(TM)) * ((N + BN - 1) / BN);
 }
 
 template <bool TA, bool TB, int TM, class Epi, int NP, int NS>
 inline void launch_tm(Problems<Epi, NP, NS> &g, hipStream_t st) {
   g.start[0] = 0;
-  for (int q = 0; q < NP; ++q) g.start[q + 1] = g.start[q] + tiles_of(g.M[q], g.N[q], TM);
+  for (int q = 0; q < NP; ++q) g.start[q + 1] = g.start[q] + (int)tiles_of(g.M[q], g.N[q], TM);
   const long total = (long)g.start[NP] * g.splits;
   if (total == 0) return;
   k_gemm<TA, TB, TM, Epi, NP, NS><<<(unsigned)((total + 7) / 8 * 8), THREADS, 0, st>>>(g);
@@ -568,35 +572,188 @@ inline void launch_tm(Problems<Epi, NP, NS> &g, hipStream_t st) {
 
 constexpr int NUM_CU = 256;
 
-// Whole waves of blocks over the chip (one block per CU), in units of a
-// 256-row tile's time.  A 128-row tile takes 0.62 of that (1,190 against
-// 1,470 TFLOP/s at 8192^3).
-inline double wave_cost(long tiles, int TM) {
-  const double per = TM == 4 ? 1.0 : 0.62;
-  return per * (double)((tiles + NUM_CU - 1) / NUM_CU);
+// Sums the parts of split products and finishes them as their epilogues say:
+// 8 columns of a row a thread, parts in order.  Rows of N elements (a multiple
+// of 8), problem after problem, in each part.
+template <class TO, OutMode MODE, int NP>
+struct Finish {
+  EpiOut<TO, MODE> ep[NP];
+  int n8[NP];         // chunks of a row
+  long end[NP];       // chunks, running over the problems
+  const float *part;
+  int parts;
+};
+
+template <class TO, OutMode MODE, int NP>
+__global__ void __launch_bounds__(256) k_finish(const Finish<TO, MODE, NP> f) {
+  const long total = f.end[NP - 1];
+  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long)gridDim.x * 256) {
+    EpiOut<TO, MODE> e = f.ep[0];
+    int n8 = f.n8[0];
+    long first = 0;
+#pragma unroll
+    for (int q = 1; q < NP; ++q)
+      if (i >= f.end[q - 1]) {
+        e = f.ep[q];
+        n8 = f.n8[q];
+        first = f.end[q - 1];
+      }
+    const long m = (i - first) / n8, n = (i - first - m * n8) * 8;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < f.parts; ++k) {
+      const f32x4 *p = reinterpret_cast<const f32x4 *>(f.part + (k * total + i) * 8);
+      const f32x4 a = p[0], b = p[1];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        v[j] += a[j];
+        v[4 + j] += b[j];
+      }
+    }
+    TO *d = e.c + m * e.ldc + n;
+    const unsigned short *r = MODE == RESID ? e.r + m * e.ldr + n : nullptr;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      v[j] *= e.scale;
+      if constexpr (MODE == RESID) v[j] += bf_bits2f(r[j]);
+      if constexpr (MODE == ACC)
+        if (!e.first) v[j] += (float)d[j];
+    }
+    if constexpr (sizeof(TO) == 2) {
+      if (e.vec) {
+        u16x8 o;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = f2bf_bits(v[j]);
+        *reinterpret_cast<u16x8 *>(d) = o;
+        continue;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) store_val(d, j, v[j]);
+  }
 }
 
-// All products of the group with one launch.  Tiles of 128 rows where the last
-// wave of 256-row ones would leave so much of the chip idle that they lose.
+// Workspace for partial sums.
+struct Scratch {
+  float *p;
+  long elems;
+};
+
+// How a group of products is launched: rows of a tile and parts of K, by the
+// time that each choice is expected to take: whole waves of blocks over the
+// chip (one block per CU), a step of 64 at 1.5 us (the rate of the full chip;
+// a 128-row tile takes 0.62 of it: 1,190 against 1,470 TFLOP/s at 8192^3) and
+// 4 us to start and end a block; the partial sums written and read at 4 TB/s
+// and a launch to finish them.  So 128-row tiles serve grids whose last wave of
+// 256-row ones would be nearly empty, and long sums over few tiles are cut.
+// Measured: 1,024 x 2,048 over K = 32,000 (32 tiles) 783 us in one part, 105 +
+// 15 us in eight.
+struct Choice {
+  int tm, parts, part;  // part: steps of 64
+};
+
+inline Choice choose(long t4, long t2, long steps, double elems, long scratch) {
+  Choice best{4, 1, (int)steps};
+  double best_us = 0;
+  for (int s = 1; s <= 16; ++s) {
+    const long per = (steps + s - 1) / s;
+    if (s > 1 && (per < 8 || s * elems > (double)scratch || (s - 1) * per >= steps)) continue;
+    for (int tm = 4; tm >= 2; tm -= 2) {
+      const double waves = (double)(((tm == 4 ? t4 : t2) * s + NUM_CU - 1) / NUM_CU);
+      const double us = waves * ((tm == 4 ? 1.5 : 0.93) * per + 4) + (s > 1 ? s * elems / 5e5 + 5 : 0);
+      if ((s == 1 && tm == 4) || us < best_us) {
+        best = Choice{tm, s, (int)per};
+        best_us = us;
+      }
+    }
+  }
+  return best;
+}
+
+template <class Epi, int NP, int NS>
+inline Choice choose_for(const Problems<Epi, NP, NS> &g, long scratch, long rows = 0) {
+  long t4 = 0, t2 = 0, steps = 0;
+  double elems = 0;
+  bool whole = true;  // rows of whole 8-element chunks
+  for (int q = 0; q < NP; ++q) {
+    const long M = rows ? rows : g.M[q];
+    t4 += tiles_of(M, g.N[q], 4);
+    t2 += tiles_of(M, g.N[q], 2);
+    elems += (double)M * g.N[q];
+    whole = whole && g.N[q] % 8 == 0;
+  }
+  for (int s = 0; s < NS; ++s) steps += (g.K[s] + BK - 1) / BK;
+  return choose(t4, t2, steps, elems, whole ? scratch : 0);
+}
+
+// All products of the group with one launch.
 template <bool TA, bool TB, class Epi, int NP, int NS>
 inline void launch(Problems<Epi, NP, NS> g, hipStream_t st) {
+  const Choice c = choose_for(g, 0);
   g.splits = 1;
-  g.k_part = 0x7fffffff;
-  long t4 = 0, t2 = 0;
-  for (int q = 0; q < NP; ++q) {
-    t4 += tiles_of(g.M[q], g.N[q], 4);
-    t2 += tiles_of(g.M[q], g.N[q], 2);
-  }
-  if (wave_cost(t2, 2) < wave_cost(t4, 4)) launch_tm<TA, TB, 2>(g, st);
+  g.part = c.part;
+  if (c.tm == 2) launch_tm<TA, TB, 2>(g, st);
   else launch_tm<TA, TB, 4>(g, st);
+}
+
+// The same, cut into parts of K where that is faster and `sc` holds them.
+// rows > 0: the parts are chosen as for products of that many rows (a whole
+// batch whose chunks of rows are multiplied one by one: a row's sum must not
+// depend on the chunking); M must not be larger.
+template <bool TA, bool TB, class TO, OutMode MODE, int NP, int NS>
+inline void launch(const Problems<EpiOut<TO, MODE>, NP, NS> &g, const Scratch &sc, long rows,
+                   hipStream_t st) {
+  const Choice c = choose_for(g, sc.elems, rows);
+  if (c.parts == 1) {
+    launch<TA, TB>(g, st);
+    return;
+  }
+  typedef EpiOut<float, ST> Part;
+  Problems<Part, NP, NS> h{};
+  Finish<TO, MODE, NP> f{};
+  long total = 0;
+  for (int q = 0; q < NP; ++q) total += (long)g.M[q] * g.N[q];
+  long at = 0;
+  for (int q = 0; q < NP; ++q) {
+    for (int s = 0; s < NS; ++s) {
+      h.A[q][s] = g.A[q][s];
+      h.B[q][s] = g.B[q][s];
+      h.lda[q][s] = g.lda[q][s];
+      h.ldb[q][s] = g.ldb[q][s];
+    }
+    h.M[q] = g.M[q];
+    h.N[q] = g.N[q];
+    h.ep[q] = Part::make(sc.p + at, g.N[q], 1.f, nullptr, 0, true, total);
+    at += (long)g.M[q] * g.N[q];
+    f.ep[q] = g.ep[q];
+    f.n8[q] = g.N[q] / 8;
+    f.end[q] = at / 8;
+  }
+  for (int s = 0; s < NS; ++s) h.K[s] = g.K[s];
+  h.splits = c.parts;
+  h.part = c.part;
+  if (c.tm == 2) launch_tm<TA, TB, 2>(h, st);
+  else launch_tm<TA, TB, 4>(h, st);
+  f.part = sc.p;
+  f.parts = c.parts;
+  k_finish<TO, MODE, NP><<<(unsigned)std::min<long>(8192, (total / 8 + 255) / 256), 256, 0, st>>>(f);
+  SEG_LAUNCH_CHECK();
 }
 
 // One product.
 template <bool TA, bool TB, class Epi>
+inline Problems<Epi, 1, 1> one(const unsigned short *A, long lda, const unsigned short *B, long ldb,
+                               int M, int N, int K, const Epi &ep) {
+  return Problems<Epi, 1, 1>{{{A}}, {{B}}, {{lda}}, {{ldb}}, {K}, {M}, {N}, {ep}, {}, 1, 0};
+}
+template <bool TA, bool TB, class Epi>
 inline void launch_one(const unsigned short *A, long lda, const unsigned short *B, long ldb, int M,
                        int N, int K, const Epi &ep, hipStream_t st) {
-  Problems<Epi, 1, 1> g{{{A}}, {{B}}, {{lda}}, {{ldb}}, {K}, {M}, {N}, {ep}, {}, 1, 0};
-  launch<TA, TB>(g, st);
+  launch<TA, TB>(one<TA, TB>(A, lda, B, ldb, M, N, K, ep), st);
+}
+template <bool TA, bool TB, class Epi>
+inline void launch_one(const unsigned short *A, long lda, const unsigned short *B, long ldb, int M,
+                       int N, int K, const Epi &ep, const Scratch &sc, long rows, hipStream_t st) {
+  launch<TA, TB>(one<TA, TB>(A, lda, B, ldb, M, N, K, ep), sc, rows, st);
 }
 
 }  // namespace gemm

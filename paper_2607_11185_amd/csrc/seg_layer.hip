@@ -382,9 +382,10 @@ Dims dims_of(const seg_sizes &sz, const seg_layer_cfg &c) {
 }
 
 struct LayerWs {
-  size_t pos, a, m, wgu, attn;                                   // forward
+  size_t pos, a, m, wgu, sums, attn;                             // forward
   size_t dy1, dO, dq, dk, dv;  // backward
   size_t g, u, dm, dg, du, dbf, part;
+  long sum_elems;
   size_t total;
 };
 
@@ -403,6 +404,11 @@ LayerWs layer_ws(const seg_sizes &sz, const seg_layer_cfg &c, int bwd) {
   w.a = take(C * H * 2);
   w.m = take(C * I * 2);
   w.wgu = take(2 * Ip * H * 2);
+  // partial sums of products cut over K: what the largest cut product takes, up
+  // to 128 MB (larger ones fill the chip uncut); the same for every chunk size
+  w.sum_elems = (long)std::min<size_t>(
+      (size_t)32 << 20, 16 * std::max(std::max(P, H) * std::max<size_t>(H, m.QD + 2 * m.KD), H * I));
+  w.sums = take(w.sum_elems * 4);
   w.attn = take(seg_attn_workspace_bytes(&sz, SEG_BF16, c.hq, c.hkv, c.d, bwd));
   if (bwd) {
     w.dy1 = take(P * H * 2);
@@ -519,6 +525,7 @@ void layer_fwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
   const long P = m.P;
   const int H = m.H, I = m.I;
   int32_t *pos = reinterpret_cast<int32_t *>(base + W.pos);
+  const gemm::Scratch sums{reinterpret_cast<float *>(base + W.sums), W.sum_elems};
   unsigned short *a = US(base + W.a), *mb = US(base + W.m), *wgu = US(base + W.wgu);
   unsigned short *q = US(sv.q), *k = US(sv.k), *v = US(sv.v), *o = US(sv.o), *y1 = US(sv.y1);
   {
@@ -538,7 +545,7 @@ void layer_fwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
         {cr, cr, cr}, {m.QD, m.KD, m.KD},
         {OutBf::make(q + r0 * m.QD, m.QD), OutBf::make(k + r0 * m.KD, m.KD),
          OutBf::make(v + r0 * m.KD, m.KD)}, {}, 1, 0};
-    gemm::launch<false, false>(g, st);
+    gemm::launch<false, false>(g, sums, P, st);
   }
   {
     ProfScope prof("ly_rope", st);
@@ -557,7 +564,7 @@ void layer_fwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
     {
       ProfScope prof("ly_proj", st);
       gemm::launch_one<false, false>(o + r0 * m.QD, m.QD, CUS(w.wo), m.QD, cr, H, m.QD,
-                                     OutResid::make(y1 + r0 * H, H, 1.f, x + r0 * H, H), st);
+                                     OutResid::make(y1 + r0 * H, H, 1.f, x + r0 * H, H), sums, P, st);
     }
     {
       ProfScope prof("ly_norm", st);
@@ -566,7 +573,7 @@ void layer_fwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
     ProfScope prof("ly_mlp", st);
     gate_up(a, wgu, cr, H, I, EpiSwiGLU{mb, nullptr, nullptr, I, I}, st);
     gemm::launch_one<false, false>(mb, I, CUS(w.wd), I, cr, H, I,
-                                   OutResid::make(y + r0 * H, H, 1.f, y1 + r0 * H, H), st);
+                                   OutResid::make(y + r0 * H, H, 1.f, y1 + r0 * H, H), sums, P, st);
   }
 }
 
@@ -578,6 +585,7 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
   const long P = m.P;
   const int H = m.H, I = m.I;
   int32_t *pos = reinterpret_cast<int32_t *>(base + W.pos);
+  const gemm::Scratch sums{reinterpret_cast<float *>(base + W.sums), W.sum_elems};
   unsigned short *a = US(base + W.a), *gb = US(base + W.g), *ub = US(base + W.u), *mb = US(base + W.m),
                  *wgu = US(base + W.wgu);
   unsigned short *dy1 = US(base + W.dy1), *dO = US(base + W.dO), *dq = US(base + W.dq),
@@ -608,14 +616,14 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
     {
       ProfScope prof("ly_mlp", st);
       gate_up(a, wgu, cr, H, I, EpiSwiGLU{mb, gb, ub, I, I}, st);  // m, g, u
-      gemm::launch_one<false, true>(dy1c, H, CUS(w.wd), I, cr, I, H, OutBf::make(dm, I), st);  // dm = dy wd
+      gemm::launch_one<false, true>(dy1c, H, CUS(w.wd), I, cr, I, H, OutBf::make(dm, I), sums, P, st);  // dm = dy wd
       const long n8 = (long)cr * I / 8;
       k_swiglu_bwd<<<blocks_for(n8), 256, 0, st>>>(gb, ub, dm, dgb, dub, n8);
       SEG_LAUNCH_CHECK();
       // db = dg wg + du wu, one sum over both contractions
       gemm::Problems<OutF32, 1, 2> g{{{dgb, dub}}, {{CUS(w.wg), CUS(w.wu)}}, {{I, I}}, {{H, H}}, {I, I},
                                      {cr}, {H}, {OutF32::make(dbf, H)}, {}, 1, 0};
-      gemm::launch<false, true>(g, st);
+      gemm::launch<false, true>(g, sums, P, st);
     }
     {
       // dWd += dy^T m, dWg += dg^T b, dWu += du^T b in one launch
@@ -626,7 +634,7 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
           {I, H, H},
           {OutGrad::make(gr.wd, I, 1.f, nullptr, 0, first), OutGrad::make(gr.wg, H, 1.f, nullptr, 0, first),
            OutGrad::make(gr.wu, H, 1.f, nullptr, 0, first)}, {}, 1, 0};
-      gemm::launch<true, true>(g, st);
+      gemm::launch<true, true>(g, sums, 0, st);
     }
     {
       ProfScope prof("ly_norm", st);
@@ -634,9 +642,9 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
     }
     ProfScope prof("ly_proj", st);
     gemm::launch_one<true, true>(dy1c, H, o + r0 * m.QD, m.QD, H, m.QD, cr,
-                                 OutGrad::make(gr.wo, m.QD, 1.f, nullptr, 0, r0 == 0), st);  // dWo
+                                 OutGrad::make(gr.wo, m.QD, 1.f, nullptr, 0, r0 == 0), sums, 0, st);  // dWo
     gemm::launch_one<false, true>(dy1c, H, CUS(w.wo), m.QD, cr, m.QD, H,
-                                  OutBf::make(dO + r0 * m.QD, m.QD), st);
+                                  OutBf::make(dO + r0 * m.QD, m.QD), sums, P, st);
   }
   check_status(seg_attn_bwd(L, sz, SEG_BF16, m.hq, m.hkv, m.d, 1.f / std::sqrt((float)m.d), q, k, v,
                             o, sv.lse, dO, dq, dk, dv, base + W.attn, ws_bytes - W.attn, st));
@@ -665,7 +673,7 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
                                      {{CUS(w.wq), CUS(w.wk), CUS(w.wv)}}, {{m.QD, m.KD, m.KD}},
                                      {{H, H, H}}, {m.QD, m.KD, m.KD}, {cr}, {H},
                                      {OutF32::make(dbf, H)}, {}, 1, 0};
-      gemm::launch<false, true>(g, st);
+      gemm::launch<false, true>(g, sums, P, st);
     }
     {
       // dWq += dq^T a, dWk += dk^T a, dWv += dv^T a in one launch
@@ -676,7 +684,7 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
           {{m.QD}, {m.KD}, {m.KD}}, {{H}, {H}, {H}}, {cr}, {m.QD, m.KD, m.KD}, {H, H, H},
           {OutGrad::make(gr.wq, H, 1.f, nullptr, 0, first), OutGrad::make(gr.wk, H, 1.f, nullptr, 0, first),
            OutGrad::make(gr.wv, H, 1.f, nullptr, 0, first)}, {}, 1, 0};
-      gemm::launch<true, true>(g, st);
+      gemm::launch<true, true>(g, sums, 0, st);
     }
     ProfScope prof("ly_norm", st);
     rms_bwd(x + r0 * H, w.g1, sv.rstd1 + r0, dbf, cr, H, pos + r0, dy1 + r0 * H, dx + r0 * H, part,

@@ -249,17 +249,6 @@ __global__ void __launch_bounds__(256) k_dz(const float *__restrict__ zt, int V,
   }
 }
 
-// out = scale * (part[0] + part[1] + ...) over n elements, in that order
-template <class TO>
-__global__ void __launch_bounds__(256) k_sum_parts(const float *__restrict__ part, int parts, long n,
-                                                   float scale, TO *__restrict__ out) {
-  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256) {
-    float s = 0.f;
-    for (int k = 0; k < parts; ++k) s += part[k * n + i];
-    store_val(out, i, s * scale);
-  }
-}
-
 // Preparation of a call in one launch: the gathered action rows as bf16
 // (y[r] = h[rowmap[r]], zero from `rows` to rows_pad), for fp32 inputs the
 // projection as bf16 (wb), and NaN in the target logits (a target outside the
@@ -336,28 +325,6 @@ LpWs lp_ws(int rows, int hidden, int vocab, seg_dtype dt) {
   return w;
 }
 
-// Parts to cut dH's contraction over the vocabulary into: its R x H output has
-// few tiles (32 for 1,024 rows of width 2,048), so whole-K tiles would leave
-// most of the chip idle or its last wave nearly empty.  Cost of s parts: the
-// waves of tiles at 1/s of the K range each, plus the fp32 partial sums
-// written and read again (about 4 TB/s against 5.6 TFLOP/s per CU).  Measured,
-// 1,024 rows x 2,048 x vocabulary 32,000: 783 us in one part, 112 us in eight.
-// The partials take the place of zT, which is no longer needed.
-int dh_parts(int rows, int H, int V, int Rp, int *k_part) {
-  const long tiles = gemm::tiles_of(rows, H, 4);
-  const double tile_us = 2.0 * 256 * 256 * V / 5.6e6;
-  int best = 1;
-  double best_us = 0;
-  for (int s = 1; s <= 16; ++s) {
-    if (s > 1 && ((long)s * rows * H > (long)V * Rp || V / s < 1024)) break;
-    const double waves = (double)((tiles * s + gemm::NUM_CU - 1) / gemm::NUM_CU);
-    const double us = waves * (tile_us / s + 4) + (s > 1 ? 8.0 * s * rows * H / 4e6 + 5 : 0);
-    if (s == 1 || us < best_us) best = s, best_us = us;
-  }
-  *k_part = ((V + best - 1) / best + gemm::BK - 1) / gemm::BK * gemm::BK;
-  return (V + *k_part - 1) / *k_part;
-}
-
 template <class TI, class TO>
 void logprob_impl(int rows, int H, int V, const TI *h, const int32_t *row_index, const TI *w,
                   const int32_t *target, const float *old_logp, const float *ref_logp,
@@ -391,7 +358,7 @@ void logprob_impl(int rows, int H, int V, const TI *h, const int32_t *row_index,
     EpiLogits e{cfg.want_grad ? zt : nullptr, Rp, stats, rows, target, ztgt, cfg.logit_scale};
     ProfScope prof("logits", st);
     gemm::Problems<EpiLogits, 1, 1> g{{{wb}}, {{hb}}, {{H}}, {{H}}, {H}, {V}, {rows}, {e}, {}, 1,
-                                      0x7fffffff};
+                                      (H + gemm::BK - 1) / gemm::BK};
     gemm::launch_tm<false, false, 4>(g, st);
   }
   // 2. per-row loss
@@ -418,22 +385,10 @@ void logprob_impl(int rows, int H, int V, const TI *h, const int32_t *row_index,
   //    vocabulary rows of both
   {
     ProfScope prof("dh", st);
-    TO *out = static_cast<TO *>(dh);
-    int k_part = 0;
-    const int parts = dh_parts(rows, H, V, Rp, &k_part);
-    if (parts == 1) {
-      gemm::launch_one<true, true>(dzt, Rp, wb, H, rows, H, V,
-                                   EpiOut<TO, ST>::make(out, H, cfg.logit_scale), st);
-    } else {
-      const long n = (long)rows * H;
-      gemm::Problems<EpiOut<float, ST>, 1, 1> p{
-          {{dzt}}, {{wb}}, {{Rp}}, {{H}}, {V}, {rows}, {H},
-          {EpiOut<float, ST>::make(zt, H, 1.f, nullptr, 0, true, n)}, {}, parts, k_part};
-      gemm::launch_tm<true, true, 4>(p, st);
-      k_sum_parts<TO><<<(int)std::min<long>(8192, (n + 255) / 256), 256, 0, st>>>(
-          zt, parts, n, cfg.logit_scale, out);
-      SEG_LAUNCH_CHECK();
-    }
+    // zT has served: its place holds partial sums when the vocabulary is cut
+    gemm::launch_one<true, true>(dzt, Rp, wb, H, rows, H, V,
+                                 EpiOut<TO, ST>::make(static_cast<TO *>(dh), H, cfg.logit_scale),
+                                 gemm::Scratch{zt, (long)V * Rp}, 0, st);
   }
   //    dW = s * dz^T h: A = dz^T along its rows (zero in the padded columns),
   //    B = h [Rp][H] (zero in the padded rows)
