@@ -184,7 +184,10 @@ seg_status seg_build_layout(const seg_problem *p, const seg_sizes *sz, seg_layou
 
 /* Workspace of seg_attn_fwd (bwd = 0: the largest key norm of each segment
  * and kv head, plus bf16 copies of fp32 inputs) or seg_attn_bwd (bwd = 1:
- * per-row -Delta and log2-sum-exp, plus bf16 copies of fp32 inputs). */
+ * per-row -Delta and log2-sum-exp, plus bf16 copies of fp32 inputs, and for
+ * batches with fewer tiles x kv heads than CUs the fp32 parts of dk and dv;
+ * seg_attn_bwd also takes a workspace without room for those parts, and then
+ * sums dk and dv in one part). */
 size_t seg_attn_workspace_bytes(const seg_sizes *sz, seg_dtype dt, int32_t hq, int32_t hkv,
                                 int32_t d, int32_t bwd);
 
@@ -228,7 +231,8 @@ seg_status seg_attn_bwd(const seg_layout *L, const seg_sizes *sz, seg_dtype dt, 
  * first call there).  The call allocates nothing and needs
  * seg_attn_workspace_bytes(sz, dt, hq, hkv, d, 1) <= SEG_ATTN_BWD_SCRATCH_BYTES
  * (bf16: 8 * hq * packed_tokens bytes rounded up to 256, e.g. 28 heads x
- * 299,000 packed rows); a larger problem returns SEG_ERR_WORKSPACE before any
+ * 299,000 packed rows; the parts of dk and dv are only asked for where they
+ * fit too); a larger problem returns SEG_ERR_WORKSPACE before any
  * launch.  `stream` must belong to the current device.  Every call on a GPU
  * shares that GPU's scratch (nothing in it needs to start at zero: each call
  * writes what it reads), so calls that overlap on one GPU, on different

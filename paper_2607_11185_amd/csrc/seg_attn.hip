@@ -790,7 +790,9 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd(
 // the step is unrolled three ways so that each is a compile-time buffer).
 // Units are 64-row halves of the listed q-tiles, for every query head of the
 // group, in the order of `kt_ord` (FULL q-tiles first, then the PARTIAL
-// ones, each from the segment's last q-tile down).  No atomics.
+// ones, each from the segment's last q-tile down).  No atomics.  parts > 1: a
+// block takes one of `parts` shares of the group's query heads and writes its
+// sums (fp32) to that part's array; k_sum_parts adds the parts.
 template <int D, class TO>
 __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     const unsigned short *__restrict__ q, const unsigned short *__restrict__ k,
@@ -800,7 +802,8 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     const int32_t *__restrict__ tok_meta, const int32_t *__restrict__ kt_ptr,
     const int32_t *__restrict__ kt_ord, const XcdRanges xr,
     int hq, int hkv, int W,
-    float scale_log2, float scale, long P, TO *__restrict__ dk, TO *__restrict__ dv) {
+    float scale_log2, float scale, long P, TO *__restrict__ dk, TO *__restrict__ dv, int parts,
+    long part_stride) {
   constexpr int KK = D / 32, T64 = 64 * D, DB = D / 16, NB = 3;
   // three Q/dO buffers (and their per-row values) as distinct objects: Q/dO
   // tiles first (LDS is laid out by decreasing alignment), buffers 0
@@ -812,7 +815,7 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
   __shared__ __attribute__((aligned(16))) float sE0[64], sE1[64], sE2[64];
   __shared__ __attribute__((aligned(16))) int sM0[64], sM1[64], sM2[64];
 
-  int g, hk;
+  int g, hk, part;
   {
     // XCD x takes the tiles of its range kv head by kv head, so the blocks
     // resident on one XCD are neighbouring k-tiles of one kv head: they walk
@@ -822,18 +825,24 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     // mixes segments, was 7% slower); so does one whose blocks all run at once.
     const int bx = blockIdx.x, x = bx & 7, i = bx >> 3;
     const int lo = xr.b[x], C = xr.b[x + 1] - lo;
-    if (i >= C * hkv) return;
-    if (C <= MAX_CLASSED && C * hkv > 32) {
+    const int nh = hkv * parts;  // a kv head's parts count as heads of their own
+    if (i >= C * nh) return;
+    int hp;
+    if (C <= MAX_CLASSED && C * nh > 32) {
       int *scratch = reinterpret_cast<int *>(sP);
-      classed_block(kt_ptr, lo, C, hkv, i, scratch, g, hk);
+      classed_block(kt_ptr, lo, C, nh, i, scratch, g, hp);
       g = __builtin_amdgcn_readfirstlane(g);
-      hk = __builtin_amdgcn_readfirstlane(hk);
+      hp = __builtin_amdgcn_readfirstlane(hp);
     } else {
-      hk = i / C;
-      g = lo + (i - hk * C);
+      hp = i / C;
+      g = lo + (i - hp * C);
     }
+    hk = hp / parts;
+    part = hp - hk * parts;
   }
   const int grp = hq / hkv;
+  // the block's query heads of the group
+  const int h0 = part * grp / parts, h1 = (part + 1) * grp / parts;
   const TileRows tr = tile_rows(seg_info, tile_seg, g);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int side = wave >> 2, kg = wave & 3;  // side 0: P, dV; side 1: dS, dK
@@ -1039,10 +1048,10 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
 
   if (e0 < e1) {
     // Unit state as scalars: walking-order entry, half, query head, first row.
-    int ce = e0, chalf = 0, chi = 0;
+    int ce = e0, chalf = 0, chi = h0;
     int cr0 = (((int)((unsigned)kt_ord[ce] & 0x7fffffffu)) - tr.qbase) * TQ;
     int cpart = (int)((unsigned)kt_ord[ce] >> 31);
-    issue(cr0, 0, sQ0, sD0, sL0, sE0, sM0);
+    issue(cr0, h0, sQ0, sD0, sL0, sE0, sM0);
     wait_loads_and_sync();
     bool have_cur = true;  // the P side has a unit this step
     int pb = 0;            // P buffer of the P side's unit (the dS side uses the other)
@@ -1079,7 +1088,7 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
       bool more = false;
       if (have_cur) {
         const bool second = chalf == 0 && cr0 + 64 < tr.len;
-        const bool head = !second && chi + 1 < grp;
+        const bool head = !second && chi + 1 < h1;
         const bool entry = !second && !head && ce + 1 < e1;
         more = second || head || entry;
         if (second) {
@@ -1093,7 +1102,7 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
           const unsigned x = (unsigned)kt_ord[ne];
           nr0 = ((int)(x & 0x7fffffffu) - tr.qbase) * TQ;
           npart = (int)(x >> 31);
-          nhi = 0;
+          nhi = h0;
         }
       }
       unsigned short *const Q[NB] = {sQ0, sQ1, sQ2}, *const Dd[NB] = {sD0, sD1, sD2};
@@ -1131,7 +1140,7 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
   const float mul = side == 0 ? 1.f : scale;
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
-    TO *dst = which == 0 ? dv : dk;
+    TO *dst = (which == 0 ? dv : dk) + part * part_stride;
 #pragma unroll
     for (int pass = 0; pass < TQ / RP; ++pass) {
       if (side == which && kg * 32 >= pass * RP && kg * 32 < (pass + 1) * RP) {
@@ -1157,6 +1166,29 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
       }
       __syncthreads();
     }
+  }
+}
+
+// dk and dv [P, hkv, D] from `parts` fp32 arrays (dk then dv in each), summed in
+// order, 8 elements a thread; padding rows are not written.
+template <class TO>
+__global__ void __launch_bounds__(256) k_sum_parts(const float *__restrict__ part, int parts, long P,
+                                                   int width, const int32_t *__restrict__ tok_meta,
+                                                   TO *__restrict__ dk, TO *__restrict__ dv) {
+  const long n = P * width, n8 = n / 8;
+  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < 2 * n8; i += (long)gridDim.x * 256) {
+    const bool second = i >= n8;
+    const long at = (second ? i - n8 : i) * 8;
+    if ((tok_meta[at / width] & 3) == SEG_KIND_PAD) continue;
+    f32x4 a = f32x4{}, b = f32x4{};
+    for (int k = 0; k < parts; ++k) {
+      const f32x4 *p = reinterpret_cast<const f32x4 *>(part + k * 2 * n + i * 8);
+      a += p[0];
+      b += p[1];
+    }
+    TO *d = (second ? dv : dk) + at;
+    store4(d, a, true);
+    store4(d + 4, b, true);
   }
 }
 
@@ -1364,8 +1396,23 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_dq(
 // ------------------------------------------------------------- host side
 
 struct AttnWs {
-  size_t kn2, delta, lse2, qb, kb, vb, dob, total;
+  size_t kn2, delta, lse2, qb, kb, vb, dob, part, base, total;  // base: without the dK/dV parts
+  int parts;
 };
+
+// Shares of a kv head's query heads that dK/dV blocks take.  With fewer blocks
+// (tiles x kv heads) than CUs a block's walk over all heads of the group is the
+// kernel's time, so the heads are shared out, up to a block per CU: 4q/1kv,
+// 1,088 rows: 55 us in one part, 19 in four and 4 for the sums.  The parts'
+// fp32 sums stay within the fixed scratch of seg_attn_bwd_noalloc, so that both
+// entry points take the same path.
+int dkdv_parts(const seg_sizes &sz, size_t base, size_t part_bytes, int hq, int hkv) {
+  const long blocks = (long)sz.num_qtiles * hkv;
+  if (blocks <= 0) return 1;
+  long n = std::min<long>(hq / hkv, (256 + blocks - 1) / blocks);
+  while (n > 1 && base + n * part_bytes > SEG_ATTN_BWD_SCRATCH_BYTES) --n;
+  return (int)std::max<long>(1, n);
+}
 
 AttnWs attn_ws(const seg_sizes &sz, seg_dtype dt, int hq, int hkv, int d, int bwd) {
   AttnWs w{};
@@ -1386,6 +1433,13 @@ AttnWs attn_ws(const seg_sizes &sz, seg_dtype dt, int hq, int hkv, int d, int bw
     w.kb = take(P * hkv * d * 2);
     w.vb = take(P * hkv * d * 2);
     if (bwd) w.dob = take(P * hq * d * 2);
+  }
+  w.base = std::max<size_t>(off, 256);
+  w.parts = 1;
+  if (bwd) {
+    const size_t bytes = P * hkv * d * 2 * sizeof(float);
+    w.parts = dkdv_parts(sz, off, bytes, hq, hkv);
+    if (w.parts > 1) w.part = take(w.parts * bytes);
   }
   w.total = std::max<size_t>(off, 256);
   return w;
@@ -1456,7 +1510,7 @@ void bwd_impl(const seg_layout *L, const seg_sizes *sz, int hq, int hkv, float s
               const unsigned short *q, const unsigned short *k, const unsigned short *v,
               const unsigned short *dout, const TI *o_raw, const TI *dout_raw,
               const float *lse, float *delta, float *lse2, void *dq, void *dk, void *dv,
-              hipStream_t st) {
+              int parts, float *part, hipStream_t st) {
   const int G = sz->num_qtiles;
   const long P = sz->packed_tokens;
   // bf16 inputs: the dQ kernel forms -Delta and the log2-sum-exp of its rows
@@ -1482,10 +1536,20 @@ void bwd_impl(const seg_layout *L, const seg_sizes *sz, int hq, int hkv, float s
   {
     ProfScope prof("attn_bwd_dkdv", st);
     const XcdRanges xc = xcd_ranges(L->xcd_cols);
-    k_attn_bwd_dkdv<D, TO><<<xcd_grid(xc, hkv), 512, 0, st>>>(
-        q, k, v, dout, lse2, delta, L->seg_info, L->tile_seg, L->tok_meta, L->kt_ptr, L->kt_ord,
-        xc, hq, hkv, L->window, scale * LOG2E, scale, P,
-        static_cast<TO *>(dk), static_cast<TO *>(dv));
+    if (parts > 1) {
+      const long n = P * hkv * D;
+      k_attn_bwd_dkdv<D, float><<<xcd_grid(xc, hkv * parts), 512, 0, st>>>(
+          q, k, v, dout, lse2, delta, L->seg_info, L->tile_seg, L->tok_meta, L->kt_ptr, L->kt_ord,
+          xc, hq, hkv, L->window, scale * LOG2E, scale, P, part, part + n, parts, 2 * n);
+      SEG_LAUNCH_CHECK();
+      k_sum_parts<TO><<<(int)std::max<long>(1, std::min<long>(4096, (n / 4 + 255) / 256)), 256, 0, st>>>(
+          part, parts, P, hkv * D, L->tok_meta, static_cast<TO *>(dk), static_cast<TO *>(dv));
+    } else {
+      k_attn_bwd_dkdv<D, TO><<<xcd_grid(xc, hkv), 512, 0, st>>>(
+          q, k, v, dout, lse2, delta, L->seg_info, L->tile_seg, L->tok_meta, L->kt_ptr, L->kt_ord,
+          xc, hq, hkv, L->window, scale * LOG2E, scale, P, static_cast<TO *>(dk),
+          static_cast<TO *>(dv), 1, 0);
+    }
     SEG_LAUNCH_CHECK();
   }
 }
@@ -1549,8 +1613,10 @@ extern "C" seg_status seg_attn_bwd(const seg_layout *L, const seg_sizes *sz, seg
   return guarded([&] {
     check_common(L, sz, dt, hq, hkv, d);
     const AttnWs w = attn_ws(*sz, dt, hq, hkv, d, 1);
-    SEG_CHECK(ws_bytes >= w.total, SEG_ERR_WORKSPACE, "workspace of %zu bytes < required %zu",
-              ws_bytes, w.total);
+    SEG_CHECK(ws_bytes >= w.base, SEG_ERR_WORKSPACE, "workspace of %zu bytes < required %zu",
+              ws_bytes, w.base);
+    // (a workspace without room for the parts of dK/dV serves in one part)
+    const int parts = ws_bytes >= w.total ? w.parts : 1;
     if (sz->num_qtiles == 0) return;
     SEG_CHECK(q && k && v && o && lse && d_o && dq && dk && dv && ws, SEG_ERR_ARG,
               "a tensor pointer is NULL");
@@ -1559,6 +1625,7 @@ extern "C" seg_status seg_attn_bwd(const seg_layout *L, const seg_sizes *sz, seg
     const long P = sz->packed_tokens;
     float *delta = reinterpret_cast<float *>(base + w.delta);
     float *lse2 = reinterpret_cast<float *>(base + w.lse2);
+    float *part = reinterpret_cast<float *>(base + w.part);
     if (dt == SEG_F32) {
       unsigned short *q2 = reinterpret_cast<unsigned short *>(base + w.qb);
       unsigned short *k2 = reinterpret_cast<unsigned short *>(base + w.kb);
@@ -1568,10 +1635,10 @@ extern "C" seg_status seg_attn_bwd(const seg_layout *L, const seg_sizes *sz, seg
       const float *o32 = static_cast<const float *>(o), *do32 = static_cast<const float *>(d_o);
       if (d == 128)
         bwd_impl<128, float, float>(L, sz, hq, hkv, softmax_scale, q2, k2, v2, do2, o32, do32,
-                                    lse, delta, lse2, dq, dk, dv, stream);
+                                    lse, delta, lse2, dq, dk, dv, parts, part, stream);
       else
         bwd_impl<64, float, float>(L, sz, hq, hkv, softmax_scale, q2, k2, v2, do2, o32, do32, lse,
-                                   delta, lse2, dq, dk, dv, stream);
+                                   delta, lse2, dq, dk, dv, parts, part, stream);
     } else {
       const unsigned short *qb = static_cast<const unsigned short *>(q);
       const unsigned short *kb = static_cast<const unsigned short *>(k);
@@ -1581,11 +1648,11 @@ extern "C" seg_status seg_attn_bwd(const seg_layout *L, const seg_sizes *sz, seg
       if (d == 128)
         bwd_impl<128, unsigned short, unsigned short>(L, sz, hq, hkv, softmax_scale, qb, kb, vb,
                                                       dob, o16, dob, lse, delta, lse2, dq, dk,
-                                                      dv, stream);
+                                                      dv, parts, part, stream);
       else
         bwd_impl<64, unsigned short, unsigned short>(L, sz, hq, hkv, softmax_scale, qb, kb, vb,
                                                      dob, o16, dob, lse, delta, lse2, dq, dk,
-                                                     dv, stream);
+                                                     dv, parts, part, stream);
     }
   });
 }
@@ -1631,7 +1698,7 @@ extern "C" seg_status seg_attn_bwd_noalloc(const seg_layout *L, const seg_sizes 
   void *ptr = nullptr;
   const seg_status st = guarded([&] {
     check_common(L, sz, dt, hq, hkv, d);
-    const size_t need = attn_ws(*sz, dt, hq, hkv, d, 1).total;
+    const size_t need = attn_ws(*sz, dt, hq, hkv, d, 1).base;
     SEG_CHECK(need <= SEG_ATTN_BWD_SCRATCH_BYTES, SEG_ERR_WORKSPACE,
               "the backward needs %zu bytes of workspace, above the %zu-byte fixed scratch of "
               "seg_attn_bwd_noalloc (use seg_attn_bwd with a workspace)",
