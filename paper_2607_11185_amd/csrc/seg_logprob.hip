@@ -37,6 +37,10 @@ struct EpiLogits {
   const int32_t *target;  // [N]
   float *ztgt;      // [N]
   float scale;
+  // zT is larger than the 256 MB last-level cache: its stores go past the
+  // caches (a smaller one's stay, for the pass over it that follows: 1,024 x
+  // 32,000, 46 us with them in the cache, 52 without)
+  bool stream;
   static constexpr bool kSwap = false;
   // A lane holds 32 of the 128 vocabulary rows of one column n (three other
   // lanes the rest), so maximum, exponentials and sum mostly stay in the lane;
@@ -48,6 +52,35 @@ struct EpiLogits {
     static_assert(NI == 8, "logits epilogue expects 128-row wave tiles");
     const int slab_row = t.m0 + t.wr;
     if (slab_row >= t.M) return;
+    if (zt) {
+      // 16 rows x 64 columns at a time through the wave's LDS: column c of row
+      // r in place c ^ 16 (r / 4), stored 16 bytes a lane, 256 to a row (4
+      // bytes a lane, 64 to a row: 7.3 ms for 7,680 rows x 3,584 x 151,936; so
+      // 6.8, past the caches 6.6)
+      float *w = reinterpret_cast<float *>(t.lds);
+      const int lane = t.grp * 16 + t.col, n = t.n0 + t.wc + t.col * 4;
+      float *zp = zt + (long)slab_row * ldz + n;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            w[(4 * t.grp + r) * 64 + ((16 * j + t.col) ^ (16 * t.grp))] = acc[i][j][r] * scale;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const int rr = p * 4 + t.grp, row = 16 * i + rr;
+          const f32x4 v = *reinterpret_cast<const f32x4 *>(w + rr * 64 + ((4 * t.col) ^ (16 * p)));
+          if (n < ldz && slab_row + row < t.M) {
+            f32x4 *d = reinterpret_cast<f32x4 *>(zp + (long)row * ldz);
+            if (stream) __builtin_nontemporal_store(v, d);
+            else *d = v;
+          }
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
     if (slab_row + 128 <= t.M) slab<true>(acc, t, slab_row);
     else slab<false>(acc, t, slab_row);
   }
@@ -60,7 +93,6 @@ struct EpiLogits {
       const bool nok = n < t.N;
       // the lane's rows are base + k, k = 16 i + r
       const int base = slab_row + 4 * t.grp, left = t.M - base;
-      float *zp = zt + (long)base * ldz + n;
       float mx = -INFINITY;
 #pragma unroll
       for (int i = 0; i < NI; ++i)
@@ -68,10 +100,7 @@ struct EpiLogits {
         for (int r = 0; r < 4; ++r) {
           const int k = 16 * i + r;
           const float z = acc[i][j][r] * scale;
-          if (WHOLE || k < left) {
-            if (nok && zt) zp[(long)k * ldz] = z;
-            mx = fmaxf(mx, z);
-          }
+          if (WHOLE || k < left) mx = fmaxf(mx, z);
         }
       mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
@@ -355,7 +384,8 @@ void logprob_impl(int rows, int H, int V, const TI *h, const int32_t *row_index,
   // 1. logits zT = s * W h^T with partial softmax stats; the target logit
   //    stays NaN for a target outside [0, vocab)
   {
-    EpiLogits e{cfg.want_grad ? zt : nullptr, Rp, stats, rows, target, ztgt, cfg.logit_scale};
+    EpiLogits e{cfg.want_grad ? zt : nullptr, Rp, stats, rows, target, ztgt, cfg.logit_scale,
+                (long)V * Rp * 4 > (256L << 20)};
     ProfScope prof("logits", st);
     gemm::Problems<EpiLogits, 1, 1> g{{{wb}}, {{hb}}, {{H}}, {{H}}, {H}, {V}, {rows}, {e}, {}, 1,
                                       (H + gemm::BK - 1) / gemm::BK};
