@@ -110,6 +110,16 @@ def test_layer_wide_gemm_parity():
     assert _big_tiles(lr.P, cfg.hq * cfg.head_dim) >= 192
 
 
+@pytest.mark.parametrize("chunk", [0, 1100])
+def test_layer_cut_products(chunk):
+    """Few output tiles and long contractions, so the products are cut over K:
+    projections and data gradients (store, residual, concatenated contractions
+    of ragged lengths) and weight gradients (first and accumulated chunk)."""
+    cfg = MED.with_(num_traj=2, steps=(6, 7), seed=51)
+    lr = _full_parity("cut", cfg, 1096, 2200, chunk)
+    assert 2 * _big_tiles(lr.P, 1096) < 256
+
+
 def _random_layer_case(i):
     """Seeded random layer problem: widths (multiples of 8 only), head shape,
     segment window and length, buffers, row chunking and mode drawn from one
