@@ -178,7 +178,7 @@ seg_status seg_layout_query(const seg_problem *p, seg_sizes *out);
  * sliding-window visibility and the tile map).  `sz` must be the result of
  * seg_layout_query(p); `ws` >= sz->workspace_bytes.  The segment table is
  * computed on the host and uploaded to `ws`; the call waits on `stream` once
- * after that small upload, then enqueues the token, loss-row and tile kernels. */
+ * after that small upload, then enqueues the kernel that writes every array. */
 seg_status seg_build_layout(const seg_problem *p, const seg_sizes *sz, seg_layout *out,
                             void *ws, size_t ws_bytes, hipStream_t stream);
 
