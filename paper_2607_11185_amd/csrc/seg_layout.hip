@@ -77,10 +77,11 @@ struct Plan {
 // contiguous q-tiles j .. r_j - 1 (the diagonal always).
 void tile_work(const Piece *pc, int npc, int len, int tile, int Wv, TileSpan *sp, int32_t *row_w,
                int32_t *col_w) {
-  const int n = (len + tile - 1) / tile;
+  // 64-bit: any tile edge up to 2^31 - 1 is taken, so len + tile may pass it
+  const int n = (int)(((int64_t)len + tile - 1) / tile);
   int k = 0;
   for (int t = 0; t < n; ++t) {
-    const int r0 = t * tile, r1 = std::min(len, r0 + tile);
+    const int64_t r0 = (int64_t)t * tile, r1 = std::min<int64_t>(len, r0 + tile);
     while (k + 1 < npc && pc[k + 1].off <= r0) ++k;
     TileSpan d{pc[k].meta >> 2, 0, INT32_MAX, INT32_MIN};
     for (int i = k; i < npc && pc[i].off < r1; ++i) {

@@ -193,6 +193,30 @@ def test_build_and_compute_reject_bad_args_before_any_launch():
         assert b"kl" in L.seg_last_error()
 
 
+@pytest.mark.parametrize("tile", [128, 2 ** 31 - 25, 2 ** 31 - 24, 2 ** 31 - 1])
+def test_build_plans_tiles_of_any_edge(tile):
+    """The host plan of a build (tile lists and launch schedule) where segment
+    length + tile edge passes 2^31: 16 segments of one tile each make eight
+    ranges of two.  The schedule is set before the device is used, so a machine
+    without one shows it (there the call then ends with a HIP error)."""
+    import torch
+    L = _lib_or_skip()
+    if torch.cuda.is_available():
+        pytest.skip("passes host memory where a GPU would write")
+    sp = WL.explicit_spans([1] * 16, [5] * 16, [0] * 16, [20] * 16, [4] * 16)
+    pr = S.Problem.from_spans(sp, 1, 1, 0, 0, tile)
+    sz = S.seg_layout_query(pr)
+    assert sz.num_qtiles == 16 and sz.max_seg_len == 25
+    buf = np.zeros(max(1 << 16, sz.workspace_bytes), np.uint8)
+    lay = _lib.SegLayout()
+    for f in S.Layout.FIELDS:
+        setattr(lay, f, buf.ctypes.data)
+    st = L.seg_build_layout(ctypes.byref(pr.c()), ctypes.byref(sz), ctypes.byref(lay), buf.ctypes.data,
+                            buf.nbytes, None)
+    assert st == _lib.SEG_ERR_HIP
+    assert list(lay.xcd_rows) == list(lay.xcd_cols) == list(range(0, 17, 2))
+
+
 def test_noalloc_backward_rejects_before_any_launch():
     """The fixed-scratch backward checks its size limit and the shapes on the
     host: no device is touched for a rejected call."""

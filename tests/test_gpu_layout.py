@@ -214,6 +214,17 @@ def test_tile_one(mode):
     _check_all(_gpu(sp, 2, 2, 1, mode=mode), ref)
 
 
+@pytest.mark.parametrize("tile", [2 ** 30, 2 ** 31 - 1])
+def test_one_tile_per_segment(tile):
+    """Tile edges so large that segment length + tile passes 2^31 (the larger
+    one): every segment is one tile, listed by itself."""
+    sp = WL.explicit_spans([3, 2], [4, 0], [5, 6, 7, 8, 9], [9, 8, 7, 6, 5], [3, 2, 1, 2, 3])
+    ref = OL.build(sp, 2, 1, tile)
+    got = _gpu(sp, 2, 1, tile)
+    _check_all(got, ref)
+    assert got["qt_ptr"].tolist() == list(range(6))
+
+
 # ---- anchored mode (the App. D algorithm as printed)
 
 def test_anchored_hand_worked():
