@@ -420,10 +420,12 @@ __global__ void __launch_bounds__(256) k_build(const BuildArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int b = blockIdx.x;
   if (b < a.tok_blocks) {
-    // the rows of a block mostly lie in one segment: search from there
-    const int first = b * TOK_BLOCK, last = min(a.P, first + TOK_BLOCK);
+    // the rows of a block mostly lie in one segment: search from there (the
+    // end of the last block may lie past 2^31 - 1, so rows count from its first)
+    const int first = b * TOK_BLOCK, n = min(TOK_BLOCK, a.P - first);
     const int s0 = max(0, upper_index(a.S, first, [&](int i) { return a.segs[i].start; }));
-    for (int r = first + tid; r < last; r += 256) {
+    for (int o = tid; o < n; o += 256) {
+      const int r = first + o;
       int s = s0;
       while (s + 1 < a.S && a.segs[s + 1].start <= r) ++s;
       const DevSeg d = a.segs[s];
@@ -529,13 +531,14 @@ __global__ void __launch_bounds__(256) k_build(const BuildArgs a) {
     return;
   }
   b -= 2 * a.tile_blocks;
-  for (int i = b * 256 + tid; i <= a.G; i += a.copy_blocks * 256) {
+  // (64-bit: an index steps past tables of up to 2^31 - 1 entries)
+  for (long i = b * 256 + tid; i <= a.G; i += a.copy_blocks * 256) {
     a.out.qt_ptr[i] = a.qptr[i];
     a.out.kt_ptr[i] = a.kptr[i];
   }
-  for (int i = b * 256 + tid; i < a.S * SEG_INFO_FIELDS; i += a.copy_blocks * 256)
+  for (long i = b * 256 + tid; i < a.S * SEG_INFO_FIELDS; i += a.copy_blocks * 256)
     a.out.seg_info[i] = a.info[i];
-  for (int i = b * 256 + tid; i < a.S; i += a.copy_blocks * 256) a.out.seg_pairs[i] = a.pairs[i];
+  for (long i = b * 256 + tid; i < a.S; i += a.copy_blocks * 256) a.out.seg_pairs[i] = a.pairs[i];
   if (b == 0 && tid == 0) *a.out.tile_nnz = a.qptr[a.G];
 }
 

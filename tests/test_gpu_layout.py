@@ -225,6 +225,38 @@ def test_one_tile_per_segment(tile):
     assert got["qt_ptr"].tolist() == list(range(6))
 
 
+def test_rows_up_to_the_int32_limit():
+    """The last rows of a layout with 2^31 - 4 packed rows and 2^31 - 8 loss rows
+    (42 GB of arrays): four one-turn segments of a prompt token and trained
+    text."""
+    import torch
+    x = 2 ** 29 - 2
+    sp = WL.explicit_spans([1] * 4, [1] * 4, [0] * 4, [x] * 4, [x] * 4)
+    pr = S.Problem.from_spans(sp, 1, 1, 0, 0, 2 ** 30)
+    sz = S.seg_layout_query(pr)
+    P, R = sz.packed_tokens, sz.loss_rows
+    assert (P, R, sz.num_qtiles) == (2 ** 31 - 4, 2 ** 31 - 8, 4)
+    say(f"  P={P} R={R}")
+    lay = S.Layout(sz, torch.device("cuda"))
+    names = ("tok_src", "tok_meta", "loss_pred_row", "loss_tgt_src", "loss_traj")
+    for f in names:
+        getattr(lay, f)[-5000:].fill_(-7)
+    S.seg_build_layout(pr, sz, "cuda", out=lay)
+    for n, fs in ((P, names[:2]), (R, names[2:])):
+        for rows in (np.arange(5000), np.arange(n // 2 - 2500, n // 2 + 2500), np.arange(n - 5000, n)):
+            traj, o = np.divmod(rows, x + 1 if n == P else x)
+            want = ({"tok_src": rows, "tok_meta": np.where(o == 0, 0, 1 << 2 | 2)} if n == P else
+                    {"loss_pred_row": traj * (x + 1) + o, "loss_tgt_src": traj * (x + 1) + o + 1,
+                     "loss_traj": traj})
+            for f in fs:
+                got = getattr(lay, f)[int(rows[0]):int(rows[-1]) + 1].cpu().numpy()
+                assert np.array_equal(got.astype(np.int64), want[f]), (f, rows[0])
+    assert lay.qt_ptr.cpu().tolist() == [0, 1, 2, 3, 4] and int(lay.tile_nnz.cpu()[0]) == 4
+    assert lay.seg_pairs.cpu().tolist() == [(x + 1) * (x + 2) // 2] * 4
+    del lay
+    torch.cuda.empty_cache()
+
+
 # ---- anchored mode (the App. D algorithm as printed)
 
 def test_anchored_hand_worked():
