@@ -271,7 +271,10 @@ __global__ void __launch_bounds__(256) k_dz(const float *__restrict__ zt, int V,
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const float z = j < 4 ? a[j] : b[j - 4];
-      const float p = __builtin_amdgcn_exp2f((z - l[j]) * LOG2E);
+      // (x log2(e) rounded once in front of the hardware exponential is 16
+      // times further from e^x at x = -12 and no faster at 7,680 rows x 151,936:
+      // 1.30 against 1.31 ms; 49 against 51 us at 1,024 x 32,000)
+      const float p = expf(z - l[j]);
       o[j] = r0 + j < R ? f2bf_bits(gr[j] * ((v == tg[j] ? 1.f : 0.f) - p)) : 0;
     }
     *reinterpret_cast<u16x8 *>(dzt + (long)v * Rp + r0) = o;

@@ -306,3 +306,43 @@ def test_gemm_edges(R, H, V, dtype):
     for n in ("dh", "dw"):
         if np.linalg.norm(ref[n]) > 1e-6:
             assert rel(out[n].float().cpu().numpy(), ref[n]) < 2.0 ** -8, n
+
+
+def test_probabilities_of_the_score_gradient():
+    """Every bf16 dz is the rounding of a probability as exact as a fp32
+    exponential gives it, far from the maximum too.  Rows of h are one-hot in
+    their own column and carry two more values, so dW holds dz itself, and z =
+    w1 h1 + w2 (16 bits at most) is exact in fp32; with a zero row of W as the
+    target, logp = -lse, and old_logp = logp, A = -1 make dz = -exp(z - lse)."""
+    import torch
+    rng = np.random.default_rng(8)
+    R, H, V = 32, 40, 32768
+    h = np.zeros((R, H), np.float32)
+    h[np.arange(R), np.arange(R)] = 1
+    h[:, R] = 1 + rng.permutation(R) / 128
+    h[:, R + 1] = 1
+    w = np.zeros((V, H), np.float32)
+    w[1:, R] = -(32 + rng.integers(0, 128, V - 1) / 4)
+    w[1:, R + 1] = rng.integers(0, 256, V - 1) / 256
+    z = w[:, R:R + 1].astype(np.float64) * h[:, R].astype(np.float64) + w[:, R + 1:R + 2]
+    assert np.array_equal(z, z.astype(np.float32).astype(np.float64))
+    t = lambda x, d: torch.from_numpy(x).to("cuda").to(d)
+    hb, wb = t(h, torch.bfloat16), t(w, torch.bfloat16)
+    assert np.array_equal(wb.float().cpu().numpy(), w) and np.array_equal(hb.float().cpu().numpy(), h)
+    zero = t(np.zeros(R, np.int32), torch.int32)
+    args = lambda old: (hb, None, wb, zero, old, t(-np.ones(1, np.float32), torch.float32), zero,
+                        S.LossCfg(0.2, 0.2))
+    old = S.seg_logprob_loss(*args(torch.zeros(R, device="cuda")))["logp"].clone()
+    out = S.seg_logprob_loss(*args(old))
+    assert torch.equal(out["logp"], old) and not out["clipped"].any()
+    lse = -old.cpu().numpy()
+    x = (z[1:].astype(np.float32) - lse).astype(np.float64)  # the kernel's own exponent
+    want = torch.from_numpy(-np.exp(x)).to(torch.float32).to(torch.bfloat16).float().numpy()
+    got = out["dw"].cpu().numpy()[1:, :R]
+    assert np.abs(got / want - 1).max() < 2.0 ** -6
+    # an fp32 exponential is within one unit in the last place: a relative error
+    # of p of at most 2^-23, which takes it over a rounding boundary of bf16 (one
+    # per relative step of 2^-8 or more) with a probability of at most 2^-15
+    off = float((got != want).mean())
+    say(f"  dz off the rounded exact value: {off:.1e} of {got.size}")
+    assert off < 2.0 ** -15
