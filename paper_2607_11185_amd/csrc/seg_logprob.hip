@@ -45,7 +45,10 @@ struct EpiLogits {
   // A lane holds 32 of the 128 vocabulary rows of one column n (three other
   // lanes the rest), so maximum, exponentials and sum mostly stay in the lane;
   // a wave covers one 128-row slab.  Only the slab that the vocabulary ends in
-  // tests its rows, and only waves that hold a target look for it.
+  // tests its rows, and only waves that hold a target look for it.  The
+  // exponents come from the logits as they are stored, scaled and rounded first:
+  // scale * log2(e) as one rounded factor moved every exponent of a row the same
+  // way, up to 6e-8 of the logit (log-probs up to 1.7 times further off).
   template <int NI, int NJ>
   __device__ __forceinline__ void operator()(const f32x4 (&acc)[NI][NJ],
                                              const gemm::Tile &t) const {
@@ -104,7 +107,7 @@ struct EpiLogits {
         }
       mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float mx2 = mx * LOG2E, s2 = scale * LOG2E;
+      const float mx2 = mx * LOG2E;
       float sm = 0.f;
       if (mx != -INFINITY) {
 #pragma unroll
@@ -112,7 +115,7 @@ struct EpiLogits {
 #pragma unroll
           for (int r = 0; r < 4; ++r)
             if (WHOLE || 16 * i + r < left)
-              sm += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], s2, -mx2));
+              sm += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r] * scale, LOG2E, -mx2));
       }
       sm += __shfl_xor(sm, 16, 64);
       sm += __shfl_xor(sm, 32, 64);

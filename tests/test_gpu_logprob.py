@@ -346,3 +346,29 @@ def test_probabilities_of_the_score_gradient():
     off = float((got != want).mean())
     say(f"  dz off the rounded exact value: {off:.1e} of {got.size}")
     assert off < 2.0 ** -15
+
+
+def test_log_probs_with_a_logit_scale():
+    """The softmax statistics are those of the scaled logits: no error that
+    grows with them beyond the rounding of log2(e) and ln(2) to fp32 (1.6e-8
+    together).  Products of two bf16 numbers and a six-bit scale are exact in
+    fp32, a zero row of W as the target leaves logp = -lse, and the roundings of
+    single rows (up to 2^-23) average out over 4,096 rows."""
+    import torch
+    rng = np.random.default_rng(9)
+    R, H, V, scale = 4096, 8, 512, 45 / 16
+    h, w = np.zeros((R, H), np.float32), np.zeros((V, H), np.float32)
+    h[:, 0] = rng.integers(64, 192, R) / 128
+    w[1:, 0] = rng.integers(64, 256, V - 1) / 16
+    z = scale * h[:, :1].astype(np.float64) * w[:, 0].astype(np.float64)
+    assert np.array_equal(z, z.astype(np.float32).astype(np.float64))
+    zi = torch.zeros(R, dtype=torch.int32, device="cuda")
+    t = lambda x: torch.from_numpy(x).to("cuda").to(torch.bfloat16)
+    out = S.seg_logprob_loss(t(h), None, t(w), zi, torch.zeros(R, device="cuda"),
+                             torch.ones(1, device="cuda"), zi,
+                             S.LossCfg(0.2, 0.2, logit_scale=scale, want_grad=False))
+    m = z.max(1, keepdims=True)
+    lse = (m + np.log(np.exp(z - m).sum(1, keepdims=True)))[:, 0]
+    bias = float((-out["logp"].cpu().numpy().astype(np.float64) / lse - 1).mean())
+    say(f"  mean relative error of lse (up to {lse.max():.0f}): {bias:.1e}")
+    assert abs(bias) < 2.5e-8
