@@ -803,7 +803,7 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     const int32_t *__restrict__ kt_ord, const XcdRanges xr,
     int hq, int hkv, int W,
     float scale_log2, float scale, long P, TO *__restrict__ dk, TO *__restrict__ dv, int parts,
-    long part_stride) {
+    long part_stride, int classed) {
   constexpr int KK = D / 32, T64 = 64 * D, DB = D / 16, NB = 3;
   // three Q/dO buffers (and their per-row values) as distinct objects: Q/dO
   // tiles first (LDS is laid out by decreasing alignment), buffers 0
@@ -822,13 +822,14 @@ __global__ void __launch_bounds__(512, 1) k_attn_bwd_dkdv(
     // the same q-tiles of a segment and share their Q/dO tiles in L2.  A range
     // with more tiles than the classes take runs in tile order (its many
     // blocks even out: 1% on the benchmark batch, where a full sort, which
-    // mixes segments, was 7% slower); so does one whose blocks all run at once.
+    // mixes segments, was 7% slower); so does one whose blocks all run at once
+    // and a batch of short walks (`classed`, see bwd_impl).
     const int bx = blockIdx.x, x = bx & 7, i = bx >> 3;
     const int lo = xr.b[x], C = xr.b[x + 1] - lo;
     const int nh = hkv * parts;  // a kv head's parts count as heads of their own
     if (i >= C * nh) return;
     int hp;
-    if (C <= MAX_CLASSED && C * nh > 32) {
+    if (classed && C <= MAX_CLASSED && C * nh > 32) {
       int *scratch = reinterpret_cast<int *>(sP);
       classed_block(kt_ptr, lo, C, nh, i, scratch, g, hp);
       g = __builtin_amdgcn_readfirstlane(g);
@@ -1536,11 +1537,18 @@ void bwd_impl(const seg_layout *L, const seg_sizes *sz, int hq, int hkv, float s
   {
     ProfScope prof("attn_bwd_dkdv", st);
     const XcdRanges xc = xcd_ranges(L->xcd_cols);
+    // Sorting its range into classes costs a block about 2 us.  Where every
+    // segment is one tile all walks are equal and nothing is won (8q/8kv, 300
+    // segments: 240 us sorted, 224 in order); where the longest walk is below
+    // four tiles x heads, less than the sort (8q/8kv, 100 segments of 3 tiles:
+    // 295 against 283); from four on, more (8q/4kv, 50 of 2: 82 against 87).
+    const int lmax = (int)((sz->max_seg_len + (long)TQ - 1) / TQ), share = (hq / hkv + parts - 1) / parts;
+    const int classed = lmax >= 2 && (long)lmax * share >= 4;
     if (parts > 1) {
       const long n = P * hkv * D;
       k_attn_bwd_dkdv<D, float><<<xcd_grid(xc, hkv * parts), 512, 0, st>>>(
           q, k, v, dout, lse2, delta, L->seg_info, L->tile_seg, L->tok_meta, L->kt_ptr, L->kt_ord,
-          xc, hq, hkv, L->window, scale * LOG2E, scale, P, part, part + n, parts, 2 * n);
+          xc, hq, hkv, L->window, scale * LOG2E, scale, P, part, part + n, parts, 2 * n, classed);
       SEG_LAUNCH_CHECK();
       k_sum_parts<TO><<<(int)std::max<long>(1, std::min<long>(4096, (n / 4 + 255) / 256)), 256, 0, st>>>(
           part, parts, P, hkv * D, L->tok_meta, static_cast<TO *>(dk), static_cast<TO *>(dv));
@@ -1548,7 +1556,7 @@ void bwd_impl(const seg_layout *L, const seg_sizes *sz, int hq, int hkv, float s
       k_attn_bwd_dkdv<D, TO><<<xcd_grid(xc, hkv), 512, 0, st>>>(
           q, k, v, dout, lse2, delta, L->seg_info, L->tile_seg, L->tok_meta, L->kt_ptr, L->kt_ord,
           xc, hq, hkv, L->window, scale * LOG2E, scale, P, static_cast<TO *>(dk),
-          static_cast<TO *>(dv), 1, 0);
+          static_cast<TO *>(dv), 1, 0, classed);
     }
     SEG_LAUNCH_CHECK();
   }

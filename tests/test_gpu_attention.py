@@ -481,3 +481,72 @@ def test_dkdv_block_order_covers_every_key(hkv, img, turns):
             for name, got, want in (("dk", dk, ds.t() @ q), ("dv", dv, p.t() @ do)):
                 e = float((got[rows, h].double() - want).norm() / want.norm())
                 assert e < TOL, (name, sg.start, h, e)
+
+
+class _Spans:
+    """Attention over segments of given lengths (one turn of text each), on the
+    GPU: inputs, forward outputs and the float64 dk and dv."""
+
+    def __init__(self, lens, hq, hkv, d, dtype="bf16", buffer=0, seed=0):
+        import torch
+        n = len(lens)
+        sp = WL.explicit_spans([1] * n, [1] * n, [0] * n, [x - 1 for x in lens], [1] * n)
+        self.lay = S.seg_build_layout(S.Problem.from_spans(sp, 1, 1, 0, buffer), device="cuda")
+        self.P = self.lay.sizes.packed_tokens
+        info = self.lay.host()["seg_info"]
+        self.rows = [slice(int(a), int(a) + int(b)) for a, b in info[:, 3:5]]
+        self.grp, self.hkv, self.scale = hq // hkv, hkv, d ** -0.5
+        g = torch.Generator(device="cuda")
+        g.manual_seed(seed)
+        dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+        self.q, self.k, self.v, self.dout = (
+            torch.randn(self.P, h, d, generator=g, device="cuda", dtype=torch.float32).to(dt)
+            for h in (hq, hkv, hkv, hq))
+        self.o, self.lse = S.seg_attn_fwd(self.lay, self.q, self.k, self.v, self.scale)
+
+    def bwd(self, ws=None, noalloc=False):
+        """dq, dk, dv over NaN: what no kernel writes stays NaN."""
+        import torch
+        out = [torch.full_like(t, float("nan")) for t in (self.q, self.k, self.v)]
+        a = (self.lay, self.q, self.k, self.v, self.o, self.lse, self.dout, self.scale)
+        if noalloc:
+            S.seg_attn_bwd_noalloc(*a, *out)
+        else:
+            S.seg_attn_bwd(*a, *out, ws=ws)
+        torch.cuda.synchronize()
+        return out
+
+    def check(self, dk, dv):
+        import torch
+        real = torch.zeros(self.P, dtype=torch.bool, device="cuda")
+        for r in self.rows:
+            real[r] = True
+        for t in (dk, dv):
+            assert bool(torch.isfinite(t[real]).all()) and bool(torch.isnan(t[~real]).all())
+        bf = lambda t: t.to(torch.bfloat16).double()  # the kernels round fp32 inputs
+        for r in self.rows[::max(1, len(self.rows) // 12)]:
+            n = r.stop - r.start
+            hide = torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1)
+            for h in range(self.hkv):
+                wk, wv = 0, 0
+                for j in range(h * self.grp, (h + 1) * self.grp):
+                    q, do, o = bf(self.q[r, j]), bf(self.dout[r, j]), self.o[r, j].double()
+                    k, v = bf(self.k[r, h]), bf(self.v[r, h])
+                    p = torch.softmax((q @ k.t() * self.scale).masked_fill(hide, float("-inf")), 1)
+                    ds = p * (do @ v.t() - (do * o).sum(1, keepdim=True)) * self.scale
+                    wk, wv = wk + ds.t() @ q, wv + p.t() @ do
+                for name, got, want in (("dk", dk[r, h], wk), ("dv", dv[r, h], wv)):
+                    e = float((got.double() - want).norm() / want.norm())
+                    assert e < TOL, (name, r.start, h, e)
+
+
+# (tiles of a segment, segments, kv heads, query heads of each): more blocks of
+# an eighth than run at once, on both sides of the rule that sorts them (at
+# least two tiles, and four tiles x heads)
+@pytest.mark.parametrize("tiles,segs,hkv,grp", [(1, 50, 8, 1), (1, 50, 8, 8), (3, 33, 8, 1), (4, 25, 8, 1),
+                                                (2, 50, 4, 2)])
+def test_dkdv_short_walks_cover_every_key(tiles, segs, hkv, grp):
+    run = _Spans([tiles * 128 - 7 * (i % 11) for i in range(segs)], hkv * grp, hkv, 64)
+    cols = np.diff(run.lay.host()["xcd_cols"])
+    assert cols.max() * hkv > 32
+    run.check(*run.bwd()[1:])
