@@ -1403,16 +1403,40 @@ struct AttnWs {
 
 // Shares of a kv head's query heads that dK/dV blocks take.  With fewer blocks
 // (tiles x kv heads) than CUs a block's walk over all heads of the group is the
-// kernel's time, so the heads are shared out, up to a block per CU: 4q/1kv,
-// 1,088 rows: 55 us in one part, 19 in four and 4 for the sums.  The parts'
-// fp32 sums stay within the fixed scratch of seg_attn_bwd_noalloc, so that both
-// entry points take the same path.
-int dkdv_parts(const seg_sizes &sz, size_t base, size_t part_bytes, int hq, int hkv) {
-  const long blocks = (long)sz.num_qtiles * hkv;
+// kernel's time, so the heads are shared out: 4q/1kv, 1,088 rows: 55 us in one
+// part, 19 in four and 4 for the sums.  A block owns its CU, so
+//  - more blocks than CUs run in two rounds, and two rounds of half a walk win
+//    nothing where both hold walks of about the same length: where every segment
+//    is one tile (12q/4kv, 60 of 128 rows: backward 53 us in one part, 83 in two),
+//    or where an eighth of the work lies in the first columns of one segment and
+//    its blocks exceed an XCD's 32 CUs (16q/4kv d = 64, 8,000 rows: 783 and 825;
+//    7,100 rows, 32 blocks: 1,092 and 959).  Where an eighth holds whole segments
+//    the second round is their short walks (16q/2kv, 20 of 700: 267 and 241);
+//  - only the longest share counts: a group of 7 in five parts waits for two
+//    heads as in four;
+//  - a walk must get shorter by more than the sums cost: 1.6 us (d = 64: 1.1) for
+//    64 rows of a head against a launch of 4.4 us or, if longer, the parts written
+//    and read at 2.7 TB/s (16q/8kv, one of 100 rows: 27.0 us in one part, 29.4 in
+//    two; one of 200: 37.7 and 36.5; three of 1,000: 117 and 123).
+// The parts' fp32 sums stay within the fixed scratch of seg_attn_bwd_noalloc, so
+// that both entry points take the same path.
+int dkdv_parts(const seg_sizes &sz, size_t base, size_t part_bytes, int hq, int hkv, int d) {
+  const long blocks = (long)sz.num_qtiles * hkv, grp = hq / hkv;
   if (blocks <= 0) return 1;
-  long n = std::min<long>(hq / hkv, (256 + blocks - 1) / blocks);
+  long n = std::min<long>(grp, (256 + blocks - 1) / blocks);
+  if (n > 1 && blocks * n > 256) {
+    // columns of an eighth of the lower triangles that starts with a longest segment
+    const long tiles = ((long)sz.max_seg_len + TQ - 1) / TQ;
+    long c = 0;
+    for (long work = 0; c < tiles && 8 * work < sz.tile_nnz_max; ++c) work += tiles - c;
+    if (tiles == 1 || (n == 2 && c < tiles && c * hkv * n > 32)) n = 256 / blocks;
+  }
   while (n > 1 && base + n * part_bytes > SEG_ATTN_BWD_SCRATCH_BYTES) --n;
-  return (int)std::max<long>(1, n);
+  if (n <= 1) return 1;
+  const long share = (grp + n - 1) / n;
+  n = (grp + share - 1) / share;
+  const double saved = (double)(grp - share) * (((long)sz.max_seg_len + 63) / 64) * (d == 128 ? 1.6 : 1.1);
+  return saved < std::max(4.4, n * 2.0 * part_bytes / 2.7e6) ? 1 : (int)n;
 }
 
 AttnWs attn_ws(const seg_sizes &sz, seg_dtype dt, int hq, int hkv, int d, int bwd) {
@@ -1439,7 +1463,7 @@ AttnWs attn_ws(const seg_sizes &sz, seg_dtype dt, int hq, int hkv, int d, int bw
   w.parts = 1;
   if (bwd) {
     const size_t bytes = P * hkv * d * 2 * sizeof(float);
-    w.parts = dkdv_parts(sz, off, bytes, hq, hkv);
+    w.parts = dkdv_parts(sz, off, bytes, hq, hkv, d);
     if (w.parts > 1) w.part = take(w.parts * bytes);
   }
   w.total = std::max<size_t>(off, 256);

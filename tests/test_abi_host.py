@@ -311,3 +311,25 @@ def test_layer_sizing_and_argument_checks():
     st = L.seg_layer_fwd(ctypes.byref(lay), ctypes.byref(sz), ctypes.byref(cfg.c()), ctypes.byref(w),
                          1, 1, ctypes.byref(sv), 1, f, None)
     assert st == _lib.SEG_ERR_ARG and b"NULL" in L.seg_last_error()
+
+
+# (rows of each segment, query heads, kv heads, d, parts of dK/dV that the
+# backward's workspace holds), on both sides of each line of the rule
+@pytest.mark.parametrize("lens,hq,hkv,d,want", [
+    ([15] * 2, 16, 8, 64, 1), ([100], 16, 8, 128, 1), ([100], 12, 4, 128, 3),      # the sums' launch
+    ([200], 16, 8, 128, 2), ([1000] * 3, 16, 8, 64, 1), ([1000] * 3, 12, 4, 64, 3),  # their traffic
+    ([128] * 60, 12, 4, 64, 1), ([128] * 60, 8, 1, 64, 4),                         # even walks
+    ([8000], 12, 4, 128, 1), ([8000], 16, 4, 64, 1), ([7100], 16, 4, 64, 2),       # two rounds of halves
+    ([8000], 16, 2, 64, 3), ([700] * 20, 16, 2, 128, 2), ([700] * 20, 7, 1, 128, 3),
+    ([500], 7, 1, 64, 7), ([2000], 28, 4, 64, 4), ([1000] * 3, 16, 4, 64, 2),      # the longest share
+    ([4000], 16, 8, 64, 1), ([2000] * 4, 28, 4, 64, 1), ([500], 8, 8, 64, 1)])
+def test_dkdv_parts_by_sizes(lens, hq, hkv, d, want):
+    L = _lib_or_skip()
+    n = len(lens)
+    sp = WL.explicit_spans([1] * n, [1] * n, [0] * n, [x - 1 for x in lens], [1] * n)
+    sz = S.seg_layout_query(S.Problem.from_spans(sp, 1, 1))
+    total = L.seg_attn_workspace_bytes(ctypes.byref(sz), _lib.SEG_BF16, hq, hkv, d, 1)
+    base = 2 * (-(-4 * hq * sum(lens) // 256) * 256)   # -Delta and log2-sum-exp
+    part = sum(lens) * hkv * d * 2 * 4
+    assert max(1, (total - base) // part) == want
+    assert total - base < (want if want > 1 else 0) * part + 256
