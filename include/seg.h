@@ -25,8 +25,9 @@
  *  - No exception crosses the ABI.  A non-OK status leaves a thread-local
  *    message readable with seg_last_error().
  *  - Reductions run in a fixed order: repeated calls on the same inputs give
- *    bitwise-identical outputs.  Integer atomics are used only where their
- *    result does not depend on order.
+ *    bitwise-identical outputs (seg_attn_bwd: with workspaces that both have, or
+ *    both lack, the room for the parts of dk and dv).  Integer atomics are used
+ *    only where their result does not depend on order.
  *  - Numeric kernels compute in bf16 with fp32 accumulation (MFMA).  SEG_F32
  *    inputs are rounded to bf16 (nearest-even) when loaded; outputs are written
  *    in the input dtype unless stated otherwise.
@@ -187,7 +188,7 @@ seg_status seg_build_layout(const seg_problem *p, const seg_sizes *sz, seg_layou
  * per-row -Delta and log2-sum-exp, plus bf16 copies of fp32 inputs, and for
  * batches with fewer tiles x kv heads than CUs the fp32 parts of dk and dv;
  * seg_attn_bwd also takes a workspace without room for those parts, and then
- * sums dk and dv in one part). */
+ * sums dk and dv in one part, in another order: their last bits may differ). */
 size_t seg_attn_workspace_bytes(const seg_sizes *sz, seg_dtype dt, int32_t hq, int32_t hkv,
                                 int32_t d, int32_t bwd);
 

@@ -15,6 +15,7 @@ import pytest
 
 from oracle import attention as OA
 from oracle import layout as OL
+from paper_2607_11185_amd import _lib
 from paper_2607_11185_amd import seg as S
 from paper_2607_11185_amd import workload as WL
 from tests.gpu_helpers import TOL, GpuRun, rel, say, vis_window
@@ -550,3 +551,36 @@ def test_dkdv_short_walks_cover_every_key(tiles, segs, hkv, grp):
     cols = np.diff(run.lay.host()["xcd_cols"])
     assert cols.max() * hkv > 32
     run.check(*run.bwd()[1:])
+
+
+# (rows of each segment, kv heads, query heads of each, d, dtype, buffer rows, parts):
+# even and uneven shares of the heads, ragged last tiles, padding rows
+@pytest.mark.parametrize("lens,hkv,grp,d,dtype,buffer,parts", [
+    ([300], 1, 2, 64, "bf16", 0, 2), ([257, 500, 90], 2, 3, 128, "bf16", 0, 3),
+    ([400, 130, 700], 1, 7, 128, "f32", 800, 7), ([1000] * 3, 4, 7, 64, "bf16", 0, 3),
+    ([1000] * 3, 2, 8, 128, "f32", 1100, 4), ([128] * 60, 1, 8, 64, "bf16", 0, 4)])
+def test_dkdv_parts(lens, hkv, grp, d, dtype, buffer, parts):
+    """dk and dv summed in parts: against float64, repeated, through the
+    allocation-free entry point, and with a workspace that has no room for the
+    parts (one byte short of them, and none at all), which sums in one part."""
+    import torch
+    run = _Spans(lens, hkv * grp, hkv, d, dtype, buffer)
+    ws = S.attn_workspace(run.lay, S._dtype_code(run.q), hkv * grp, hkv, d, True)
+    held = parts * run.P * hkv * d * 2 * 4
+    base = (ws.numel() - held) // 256 * 256
+    assert base >= 8 * run.P * hkv * grp and base + held <= ws.numel() < base + held + 256
+    ws.fill_(255)  # NaN wherever the call reads what it has not written
+    whole = run.bwd(ws)
+    run.check(*whole[1:])
+    for other in (run.bwd(ws), run.bwd(noalloc=True)):
+        assert all(torch.equal(a.nan_to_num(7), b.nan_to_num(7)) for a, b in zip(whole, other))
+    short = run.bwd(ws[:ws.numel() - 1])
+    run.check(*short[1:])
+    least = run.bwd(ws[:base])
+    assert all(torch.equal(a.nan_to_num(7), b.nan_to_num(7)) for a, b in zip(short, least))
+    assert torch.equal(short[0].nan_to_num(7), whole[0].nan_to_num(7))
+    for a, b in zip(short[1:], whole[1:]):  # the same sum in another order, then rounded
+        e = float((a.double() - b.double()).nan_to_num(0).norm() / b.double().nan_to_num(0).norm())
+        assert e < (2 ** -8 if dtype == "bf16" else 1e-5), e
+    with pytest.raises(_lib.SegError):
+        run.bwd(ws[:base - 1])
