@@ -257,6 +257,19 @@ def test_rows_up_to_the_int32_limit():
     torch.cuda.empty_cache()
 
 
+# (turns, segments' turns): token runs below and above the 1 MB that are uploaded
+# from where they were made
+@pytest.mark.parametrize("turns,L,apart", [(400, 5, False), (600, 5, True)])
+def test_many_turns(turns, L, apart):
+    n = 2 * turns
+    i = np.arange(n)
+    sp = WL.explicit_spans([turns] * 2, [3, 0], 1 + i % 3, 1 + i % 2, i % 5 == 0)
+    ref = OL.build(sp, 2, L, 128)
+    runs = sum(len(np.unique(sg.step[sg.kind == 2])) for sg in ref.segments)
+    assert (16 * runs > 1 << 20) == apart, runs
+    _check_all(_gpu(sp, 2, L, 128), ref)
+
+
 # ---- anchored mode (the App. D algorithm as printed)
 
 def test_anchored_hand_worked():
