@@ -669,20 +669,27 @@ inline Choice choose(long t4, long t2, long steps, double elems, long scratch) {
   return best;
 }
 
-template <class Epi, int NP, int NS>
-inline Choice choose_for(const Problems<Epi, NP, NS> &g, long scratch, long rows = 0) {
+// The choice for a group of np products (rows M, or `rows` where not 0, and
+// columns N) that each sum over the ns ranges K.
+inline Choice choose_group(int np, const int *M, const int *N, int ns, const int *K, long scratch,
+                           long rows) {
   long t4 = 0, t2 = 0, steps = 0;
   double elems = 0;
   bool whole = true;  // rows of whole 8-element chunks
-  for (int q = 0; q < NP; ++q) {
-    const long M = rows ? rows : g.M[q];
-    t4 += tiles_of(M, g.N[q], 4);
-    t2 += tiles_of(M, g.N[q], 2);
-    elems += (double)M * g.N[q];
-    whole = whole && g.N[q] % 8 == 0;
+  for (int q = 0; q < np; ++q) {
+    const long m = rows ? rows : M[q];
+    t4 += tiles_of(m, N[q], 4);
+    t2 += tiles_of(m, N[q], 2);
+    elems += (double)m * N[q];
+    whole = whole && N[q] % 8 == 0;
   }
-  for (int s = 0; s < NS; ++s) steps += (g.K[s] + BK - 1) / BK;
+  for (int s = 0; s < ns; ++s) steps += (K[s] + BK - 1) / BK;
   return choose(t4, t2, steps, elems, whole ? scratch : 0);
+}
+
+template <class Epi, int NP, int NS>
+inline Choice choose_for(const Problems<Epi, NP, NS> &g, long scratch, long rows = 0) {
+  return choose_group(NP, g.M, g.N, NS, g.K, scratch, rows);
 }
 
 // All products of the group with one launch.

@@ -748,6 +748,17 @@ void layer_bwd_impl(const seg_layout *L, const seg_sizes *sz, const seg_layer_cf
 
 using namespace seg;
 
+// For tests (not in seg.h; host only): how a group of the layer's products is
+// launched.  rows as in gemm::launch; out = {rows of a tile, parts of K}.
+extern "C" void seg_layer_gemm_choice(const seg_sizes *sz, const seg_layer_cfg *cfg, int32_t bwd,
+                                      int32_t np, const int32_t *M, const int32_t *N, int32_t ns,
+                                      const int32_t *K, int64_t rows, int32_t *out) {
+  const gemm::Choice c =
+      gemm::choose_group(np, M, N, ns, K, layer_ws(*sz, *cfg, bwd).sum_elems, rows);
+  out[0] = gemm::bm_of(c.tm);
+  out[1] = c.parts;
+}
+
 extern "C" size_t seg_layer_workspace_bytes(const seg_sizes *sz, const seg_layer_cfg *cfg,
                                             int32_t bwd) {
   if (!sz || !cfg || cfg->hidden < 1 || cfg->inter < 1 || cfg->hq < 1 || cfg->hkv < 1 ||

@@ -17,6 +17,7 @@ import pytest
 
 from oracle import layer as OLY
 from oracle import layout as OL
+from paper_2607_11185_amd import _lib
 from paper_2607_11185_amd import seg as S
 from paper_2607_11185_amd import workload as WL
 from tests.gpu_helpers import TOL, GpuRun, rel, say, vis_window
@@ -81,17 +82,36 @@ def _np(t):
     return t.float().cpu().numpy().astype(np.float64)
 
 
-def _big_tiles(M, N):
-    """256x256 tiles of an M x N product: the data-gradient and projection
-    GEMMs take the 256-wide kernel from 192 tiles on."""
-    return -(-M // 256) * -(-N // 256)
+def _choices(lr, chunk_rows):
+    """(rows of a tile, parts of K) of each group of the layer's products, as
+    the library launches them for chunks of chunk_rows rows (row-wise products
+    as for the whole batch), and what the row-wise ones of a chunk would take by
+    itself."""
+    import ctypes
+    f = _lib.lib().seg_layer_gemm_choice
+    f.restype = None
+    f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p,
+                  ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
+    c, H, I, P = lr.cfg, lr.H, lr.I, lr.P
+    QD, KD = c.hq * c.head_dim, c.hkv * c.head_dim
+    cr = min(chunk_rows or 65536, P)
+    # rows and columns of each product of the group, the ranges of K
+    groups = {"qkv": ([cr] * 3, [QD, KD, KD], [H]), "wo": ([cr], [H], [QD]), "wd": ([cr], [H], [I]),
+              "dm": ([cr], [I], [H]), "db": ([cr], [H], [I, I]), "dO": ([cr], [QD], [H]),
+              "da": ([cr], [H], [QD, KD, KD])}
+    grads = {"grad_mlp": ([H, I, I], [I, H, H], [cr]), "grad_wo": ([H], [QD], [cr]),
+             "grad_qkv": ([QD, KD, KD], [H] * 3, [cr])}
 
-
-# GEMMs on the 256-wide kernel: ~4.9k packed rows at the 7B-class widths
-# (hidden 3584, 28q/4kv, d = 128) with an MLP width of 3072, so dm, db, dO and
-# the dq/dk/dv data gradients (and the forward projections) pass 192 tiles
-WIDE = (MED.with_(hq=28, hkv=4, head_dim=128, steps=(4, 5), img_len=300, text_len=(60, 120),
-                  seed=33), 3584, 3072)
+    def choice(M, N, K, rows):
+        arr = [(ctypes.c_int32 * len(x))(*x) for x in (M, N, K)]
+        out = (ctypes.c_int32 * 2)()
+        cfg = lr.lc.c()
+        f(ctypes.addressof(lr.lay.sizes), ctypes.addressof(cfg), 1, len(M), arr[0], arr[1], len(K),
+          arr[2], rows, out)
+        return tuple(out)
+    whole = {n: choice(*g, P) for n, g in groups.items()}
+    whole.update({n: choice(*g, 0) for n, g in grads.items()})
+    return whole, {n: choice(*g, 0) for n, g in groups.items()}
 
 
 @pytest.mark.parametrize("name", list(CASES))
@@ -100,24 +120,47 @@ def test_layer_full_parity(name):
     _full_parity(name, cfg, H, I, chunk)
 
 
-def test_layer_wide_gemm_parity():
-    """Full parity where the layer's GEMMs run the 256x256 kernels with the
-    accumulate / fp32-store epilogues of the backward (dx and all nine weight
-    gradients against the oracle)."""
-    cfg, H, I = WIDE
-    lr = _full_parity("wide", cfg, H, I, 0)
-    assert _big_tiles(lr.P, H) >= 192 and _big_tiles(lr.P, I) >= 192
-    assert _big_tiles(lr.P, cfg.hq * cfg.head_dim) >= 192
+# The 7B-class widths (hidden 3584, 28q/4kv, d = 128) with an MLP width of 3072:
+# uncut products in tiles of 256 rows and, with a few more packed rows, of 128
+WIDE = MED.with_(hq=28, hkv=4, head_dim=128, steps=(4, 5), text_len=(60, 120), seed=33)
+ROWWISE = ("wo", "wd", "db", "dO", "da")
 
 
-@pytest.mark.parametrize("chunk", [0, 1100])
-def test_layer_cut_products(chunk):
-    """Few output tiles and long contractions, so the products are cut over K:
-    projections and data gradients (store, residual, concatenated contractions
-    of ragged lengths) and weight gradients (first and accumulated chunk)."""
-    cfg = MED.with_(num_traj=2, steps=(6, 7), seed=51)
-    lr = _full_parity("cut", cfg, 1096, 2200, chunk)
-    assert 2 * _big_tiles(lr.P, 1096) < 256
+@pytest.mark.parametrize("img,tile_rows", [(270, 256), (300, 128)])
+def test_layer_wide_gemm_parity(img, tile_rows):
+    """Full parity where the layer's products run uncut: dx and all nine weight
+    gradients against the oracle.  The residual, fp32 and concatenated products
+    (two and three ranges of K) take the tile under test, dm and the weight
+    gradients tiles of 256 rows."""
+    lr = _full_parity(f"wide_{tile_rows}", WIDE.with_(img_len=img), 3584, 3072, 0)
+    got, _ = _choices(lr, 0)
+    assert {got[n] for n in ROWWISE} == {(tile_rows, 1)}, got
+    assert {got[n] for n in ("dm", "grad_mlp", "grad_wo", "grad_qkv")} == {(256, 1)}, got
+
+
+# Few output tiles and long contractions, so products are cut over K.  (workload,
+# hidden, MLP width, chunk_rows, products that are cut): the row-wise ones need few
+# rows (store of one and of three products, residual, fp32, two and three ranges
+# of K; hidden and MLP width end inside a step), the weight gradients many (in one chunk and
+# accumulated over several)
+CUT_ROWS = MED.with_(num_traj=1, steps=(2, 3), hq=33, hkv=3, seed=51)
+CUT_GRADS = MED.with_(num_traj=2, steps=(6, 7), seed=51)
+CUT = {
+    "rows": (CUT_ROWS, 2056, 1544, 0, ("qkv", "dm", *ROWWISE)),
+    "rows_chunked": (CUT_ROWS, 2056, 1544, 200, ("qkv", "dm", *ROWWISE)),
+    "grads": (CUT_GRADS, 520, 1032, 0, ("grad_mlp", "grad_wo", "grad_qkv")),
+    "grads_two_chunks": (CUT_GRADS, 520, 648, 2100, ("grad_mlp", "grad_wo", "grad_qkv")),
+    "wide_grads": (CUT_GRADS, 1096, 2200, 0, ("grad_wo", "grad_qkv")),
+    "wide_grads_chunked": (CUT_GRADS, 1096, 2200, 1100, ("grad_wo", "grad_qkv")),
+}
+
+
+@pytest.mark.parametrize("name", list(CUT))
+def test_layer_cut_products(name):
+    cfg, H, I, chunk, cut = CUT[name]
+    lr = _full_parity("cut_" + name, cfg, H, I, chunk)
+    got, _ = _choices(lr, chunk)
+    assert all(got[n][1] > 1 for n in cut), got
 
 
 def _random_layer_case(i):
@@ -175,15 +218,23 @@ def _full_parity(name, cfg, H, I, chunk):
     return lr
 
 
-def test_layer_chunking_keeps_rowwise_results_bitwise():
+# (workload, hidden, MLP width, chunk_rows); CUT_ROWS: the batch's row-wise
+# products are cut, and a chunk on its own would be cut into other parts
+@pytest.mark.parametrize("cfg,H,I,chunk,cut", [(*CASES["d64_gqa2_ragged"][:3], 131, False),
+                                               (CUT_ROWS, 2056, 1544, 200, True)],
+                         ids=["uncut", "cut"])
+def test_layer_chunking_keeps_rowwise_results_bitwise(cfg, H, I, chunk, cut):
     """Row chunking only changes the order of the weight-gradient sums."""
-    cfg, H, I, _ = CASES["d64_gqa2_ragged"]
     lr = LayerRun(cfg.with_(seed=21), H, I, 0)
+    whole, alone = _choices(lr, chunk)
+    if cut:
+        assert all(whole[n][1] > 1 for n in ("qkv", "dm", *ROWWISE)), whole
+        assert all(whole[n][1] != alone[n][1] for n in ("qkv", "wo", "db", "dO", "da")), (whole, alone)
     y0, s0, dx0, g0 = lr.gpu()
     y0, dx0 = y0.clone(), dx0.clone()
     s0 = {n: t.clone() for n, t in s0.items()}
     g0 = {n: t.clone() for n, t in g0.items()}
-    lr.lc.chunk_rows = 131
+    lr.lc.chunk_rows = chunk
     y1, s1, dx1, g1 = lr.gpu()
     import torch
     assert torch.equal(y0, y1)
