@@ -131,6 +131,17 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8 &a, const bf16x8 &b, const 
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// The direct global->LDS loads of gemm.h and seg_attn.hip are volatile asm
+// statements, and what orders them against the reads of the LDS they fill is not
+// visible in their operands.  It rests on three things.  The compiler moves
+// volatile statements, LDS accesses and barriers past one another in no
+// direction, so a load stays behind the barrier that ends the reads of its LDS
+// and before the wait (vmcnt) and barrier that precede the next reads.  The LDS's
+// address goes into the statement, so the compiler cannot take that LDS as never
+// written.  And M0, which the statements write, is declared: it is a reserved
+// register (the compiler says so, hence the pragma) that nothing else here uses.
+#pragma clang diagnostic ignored "-Winline-asm"
+
 // dst[i] = value for i < n 32-bit words.  Compute entry points clear their
 // outputs with this kernel rather than hipMemsetAsync, so a caller can
 // capture them in a HIP graph and replay it.

@@ -225,7 +225,7 @@ __device__ __forceinline__ void dma16(unsigned dst, int voff, gemm_i32x4 rs) {
       "buffer_load_dwordx4 %1, %2, 0 offen lds"
       :
       : "s"(dst), "v"(voff), "s"(rs)
-      : "memory");
+      : "memory", "m0");
 #endif
 }
 

@@ -339,18 +339,18 @@ __device__ __forceinline__ unsigned lds_addr(const void *p) {
 // with the builtin the compiler makes every LDS wait drain the LDS queue while
 // such a load is in flight.  They have no register result; the end of a step
 // waits for them (wait_loads_and_sync).  No memory clobber: LDS is only read
-// again behind that barrier, and a clobber would turn the scalar loads of the
-// walking order into vector loads, whose waits drain these loads.
+// again behind that barrier (see common.h), and a clobber would turn the scalar
+// loads of the walking order into vector loads, whose waits drain these loads.
 __device__ __forceinline__ void dma16(unsigned dst, int voff, i32x4 rs, int soff) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(dst), "v"(voff), "s"(rs), "s"(soff));
+               :: "s"(dst), "v"(voff), "s"(rs), "s"(soff) : "m0");
 #endif
 }
 __device__ __forceinline__ void dma4(unsigned dst, int voff, i32x4 rs, int soff) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
-               :: "s"(dst), "v"(voff), "s"(rs), "s"(soff));
+               :: "s"(dst), "v"(voff), "s"(rs), "s"(soff) : "m0");
 #endif
 }
 
