@@ -43,7 +43,7 @@ struct LossPiece {
 
 // Per-segment record used by the kernels (device copy lives in the workspace).
 struct DevSeg {
-  int32_t start, len, qbase, nt;
+  int32_t start, len, qbase;
   int32_t piece_base, piece_count;
 };
 
@@ -300,7 +300,6 @@ Plan make_plan(const seg_problem *p) {
     d.start = (int32_t)starts[i];
     d.len = (int32_t)sg.len;
     d.qbase = (int32_t)qbase;
-    d.nt = (int32_t)nt;
     d.piece_base = (int32_t)pl.pieces.size();
     // pieces: prompt, then per turn j < b: screenshot if j > a - W, text
     int32_t off = 0, c = (int32_t)canon0[sg.traj];

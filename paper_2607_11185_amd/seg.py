@@ -128,7 +128,7 @@ class Layout:
 
 def seg_build_layout(problem: Problem, sizes: Optional[SegSizes] = None, device="cuda",
                      out: Optional[Layout] = None) -> Layout:
-    """Build every layout array on the device (token, loss-row and tile kernels).
+    """Build every layout array on the device.
 
     ``out`` reuses the arrays of an earlier layout of the same sizes.
     """
