@@ -133,10 +133,10 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8 &a, const bf16x8 &b, const 
 
 // The direct global->LDS loads of gemm.h and seg_attn.hip are volatile asm
 // statements, and what orders them against the reads of the LDS they fill is not
-// visible in their operands.  It rests on three things.  The compiler moves
-// volatile statements, LDS accesses and barriers past one another in no
-// direction, so a load stays behind the barrier that ends the reads of its LDS
-// and before the wait (vmcnt) and barrier that precede the next reads.  The LDS's
+// visible in their operands.  It rests on three things.  Volatile statements keep
+// their order against each other and against barriers, and LDS accesses cross no
+// barrier, so a load stays behind the barrier that ends the reads of its LDS and
+// before the wait (vmcnt) and barrier that precede the next reads.  The LDS's
 // address goes into the statement, so the compiler cannot take that LDS as never
 // written.  And M0, which the statements write, is declared: it is a reserved
 // register (the compiler says so, hence the pragma) that nothing else here uses.
